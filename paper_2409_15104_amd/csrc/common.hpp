@@ -100,6 +100,37 @@ struct FwdParams {
     int32_t seg_tiles;
 };
 
+// Work order of the attention kernels.  The units of a launch are numbered KV-head-major, the heaviest items of a KV
+// head first; consecutive block ids go round-robin over the 8 XCDs, each with an L2 of its own.  XCD x takes units
+// unit(x, 0), unit(x, 1), ... unit(x, count - 1):
+//  * 1, 2 or 4 KV heads: 8 / n XCDs per KV head, its units dealt to them in turn, each turn starting somewhere else (the
+//    multiplicative hash: with a fixed start the one real unit per KV group of a decode key range, whose distance is the
+//    group size, would always fall to the same XCDs).  (One contiguous range per XCD would
+//    give the first XCD the heaviest items of the head and the last one the lightest: a causal 3072-row prefill of 4
+//    query heads on one KV head spent 2x as long on the first XCD as on average.)
+//  * otherwise one contiguous range per XCD: with 8 KV heads every L2 then holds one of them.
+struct WorkOrder {
+    int log_shares;       // log2 of the XCDs per KV head, -1: contiguous ranges
+    int per_kvh;          // units per KV head
+    int64_t total, count;
+    __device__ __forceinline__ WorkOrder(int n_items, int group, int n_kv_heads) {
+        per_kvh = n_items * group;
+        total = (int64_t)per_kvh * n_kv_heads;
+        log_shares = n_kv_heads == 1 ? 3 : n_kv_heads == 2 ? 2 : n_kv_heads == 4 ? 1 : -1;
+        count = (total + 7) >> 3;     // with shares: ceil(per_kvh / shares), the same number
+    }
+    // unit number `i` < count of XCD x, or -1 if there is none
+    __device__ __forceinline__ int64_t unit(int x, int64_t i) const {
+        if (log_shares > 0) {
+            const uint32_t turn = ((uint32_t)i * 2654435761u >> 29) + x;
+            const int64_t j = (i << log_shares) + (turn & ((1u << log_shares) - 1));
+            return j < per_kvh ? (int64_t)(x >> log_shares) * per_kvh + j : -1;
+        }
+        const int64_t u = x * count + i;
+        return u < total ? u : -1;
+    }
+};
+
 __device__ __forceinline__ uint32_t k_lds_off(int key, int chunk16) {
     return (uint32_t)(key * kRowBytes + ((chunk16 ^ (key & 15)) << 4));
 }

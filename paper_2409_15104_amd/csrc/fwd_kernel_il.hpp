@@ -74,16 +74,16 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
     unsigned char* const lds_v1 = lds_all + 3 * kTileBytes;
 
     // ---- persistent workgroups: the grid holds n_slots workgroups per XCD (hardware deals block
-    // ids round-robin over the 8 XCDs); each XCD owns one contiguous logical range of the
-    // (KV-head-major, longest-rows-first) work order.  Dense calls: its workgroups walk it in snake order
+    // ids round-robin over the 8 XCDs); each XCD owns a share of the (KV-head-major, longest-rows-first)
+    // work order (WorkOrder).  Dense calls: its workgroups walk it in snake order
     // (slot, then reversed slot, ...), which evens out the causal length differences.  Work-list calls
     // (p.sched): items differ in length by orders of magnitude and the XCDs do not run at the same speed, so
     // every workgroup draws its next item from its XCD's counter, and from the next XCD's once that share is
     // used up; the heaviest items come first in the list, so the launch ends on the lightest ones.
     constexpr bool dynamic = kList;
     const int n_items_eff = dynamic ? min(*p.n_work, p.n_items) : p.n_items;
-    const int64_t total = (int64_t)n_items_eff * p.n_q_heads;
-    const int64_t per_xcd = (total + 7) >> 3;
+    const WorkOrder order(n_items_eff, p.group, p.n_kv_heads);
+    const int64_t per_xcd = order.count;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n_slots = (int)(gridDim.x >> 3);
     const int slot = (int)(blockIdx.x >> 3);
@@ -120,10 +120,7 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
                 int x = lds_sched[2], t = lds_sched[3], got = -1;
                 while (t < 8) {
                     const int v = atomicAdd(&p.sched[x], 1);
-                    if (v < per_xcd && (int64_t)x * per_xcd + v < total) {
-                        got = (int)(x * per_xcd + v);
-                        break;
-                    }
+                    if (v < per_xcd && (got = (int)order.unit(x, v)) >= 0) break;
                     x = (x + 1) & 7;
                     ++t;
                 }
@@ -159,10 +156,10 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
     } else {
         const int64_t idx_in_xcd = round0 + (((round0 / n_slots) & 1) ? (n_slots - 1 - slot) : slot);
         if (idx_in_xcd >= per_xcd) continue;
-        logical = (int64_t)(blockIdx.x & 7) * per_xcd + idx_in_xcd;
-        if (logical >= total) continue;
+        logical = order.unit(blockIdx.x & 7, idx_in_xcd);
+        if (logical < 0) continue;
     }
-    const int per_kvh = n_items_eff * p.group;
+    const int per_kvh = order.per_kvh;
     const int kvh = (int)(logical / per_kvh);
     const int rem = (int)(logical % per_kvh);
     const int item = rem / p.group;

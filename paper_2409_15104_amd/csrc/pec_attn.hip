@@ -15,6 +15,7 @@
 #include "decode_kernel.hpp"
 #include "fwd_kernel.hpp"
 #include "fwd_kernel_il.hpp"
+#include "fwd_split_kernel.hpp"
 #include "probes.hpp"
 
 namespace {
@@ -51,6 +52,72 @@ void launch_il(const FwdParams& p, unsigned grid, hipStream_t st) {
 constexpr int kBM = 256;
 static_assert(kSimpleBM == kBM, "the two kernels must agree on the query tile");
 
+// Query rows per workgroup of a launch: 256 (fwd_il_kernel, one workgroup per 64-key tile step) or, where that would
+// leave compute units idle, 64 or 32 (fwd_split_kernel<2 | 1>, 256 keys per step).  Estimated time of a choice =
+// base x rounds + step time x (steps of the longest workgroup, or of an average one times the rounds if that is more),
+// rounds = workgroups / compute units rounded up; the smallest wins.  Measured on 256 compute units (microseconds; step
+// time with few / with all of them busy, memory and power being shared):
+//     256 rows: 11.5 + 1.13 / 1.55 per 64 keys    64 rows: 8 + 1.68 / 2.15 per 256 keys    32 rows: 6 + 1.17 / 1.45
+// e.g. 8 q heads, 512 rows x 2048 keys: 47.5 / 22.6 / 16.5 us with 256 / 64 / 32 rows; 2048 x 8192: 158 / 80 / 87 us;
+// 32 q heads, 1024 x 8192: 164 / 144 / 178 us; 2048 x 8192: 212 / 264 / 323 us.
+struct RowChoice {
+    int rows, step_keys;
+    double base, t_few, t_all;
+    double estimate(double groups, double longest_keys, double average_keys) const {
+        const double cu = compute_units(), rounds = std::ceil(groups / cu);
+        const double longest = std::ceil(longest_keys / step_keys), average = std::ceil(average_keys / step_keys);
+        const double n = std::max(longest, rounds > 1 ? rounds * average : 0.0);
+        return base * rounds + n * (t_few + (t_all - t_few) * std::min(1.0, groups / cu));
+    }
+};
+constexpr RowChoice kRowChoices[] = {{256, 64, 11.5, 1.13, 1.55}, {64, 256, 8.0, 1.68, 2.15}, {32, 256, 6.0, 1.17, 1.45}};
+
+int rows_of_dense_call(const FwdParams& p) {
+    if (p.progress || p.kv_split_len || p.q_row_stride || p.q_head_stride) return kBM;
+    if ((double)((p.sq + kBM - 1) / kBM) * p.n_q_heads >= compute_units()) return kBM;   // an item for every compute unit
+    auto keys = [&](int64_t last_row) {   // that a query tile ending with this row sees
+        return (double)(p.causal ? std::max<int64_t>(0, std::min<int64_t>(p.sk, last_row + p.delta + 1)) : p.sk);
+    };
+    int best = kBM;
+    double best_t = 0;
+    for (const RowChoice& c : kRowChoices) {
+        const double longest = keys(p.sq - 1), shortest = keys(std::min(p.sq, c.rows) - 1);
+        const double t = c.estimate((double)((p.sq + c.rows - 1) / c.rows) * p.n_q_heads, longest, 0.5 * (longest + shortest));
+        if (c.rows == kBM || t < best_t) {
+            best = c.rows;
+            best_t = t;
+        }
+    }
+    return best;
+}
+
+// The same for a packed or colocated batch, of which the host knows only totals: estimated for `batch` sequences of
+// equal length, the longest as long as the caller's hint.  Keys beyond one per query are taken to be long caches, cut
+// into ranges of range_len keys per KV head.
+int rows_of_list_call(int n_q_heads, int n_kv_heads, int64_t batch, int64_t total_q, int64_t total_k, int64_t longest,
+                      int causal, int range_len) {
+    const double len = (double)total_q / batch;
+    // prompt lengths are spread wide (the log-normal mix of the tests has E[L^2] / E[L]^2 of about 3): a row sees 1.5
+    // times the average length, not half of it, and the longest prompt is several times the average
+    const double seen = std::min((double)total_q, 3 * len);
+    if (longest <= 0) longest = (int64_t)std::min((double)total_q, 4 * len);
+    const double range_units = range_len > 0 ? std::max(0.0, (double)(total_k - total_q) / range_len) * n_kv_heads : 0.0;
+    if ((double)batch * std::ceil(len / kBM) * n_q_heads + range_units >= compute_units()) return kBM;
+    int best = kBM;
+    double best_t = 0;
+    for (const RowChoice& c : kRowChoices) {
+        if (range_units > 0 && n_q_heads / n_kv_heads > c.rows) continue;   // a range item's rows are the heads of a group
+        const double groups = batch * std::ceil(len / c.rows) * n_q_heads + range_units;
+        const double t = c.estimate(groups, std::max({(double)longest, len, range_units > 0 ? (double)range_len : 0.0}),
+                                    causal ? 0.5 * seen : seen);
+        if (c.rows == kBM || t < best_t) {
+            best = c.rows;
+            best_t = t;
+        }
+    }
+    return best;
+}
+
 constexpr int64_t kMaxRows = (int64_t)1 << 30;
 
 inline bool misaligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) != 0; }
@@ -70,16 +137,26 @@ int check_shape(const pec_shape_t* s, float* scale_out) {
     return PEC_OK;
 }
 
-int launch_fwd(const FwdParams& p, bool simple, hipStream_t stream) {
+// `rows`: query rows per workgroup, which is what p.n_items counts.
+int launch_fwd(const FwdParams& p, bool simple, int rows, hipStream_t stream) {
     const int64_t total = (int64_t)p.n_items * p.n_q_heads;
     if (total <= 0) return PEC_OK;
     const int64_t per_xcd = (total + 7) / 8;
     const int64_t grid = per_xcd * 8;
     if (grid > 0x7fffffffLL) return PEC_ERR_UNSUPPORTED;
+    const dim3 blocks((unsigned)grid), threads(kSplitWaves * 64);
     if (simple)
-        hipLaunchKernelGGL(fwd_simple_kernel, dim3((unsigned)grid), dim3(kSimpleWaves * 64), 0, stream, p);
-    else
+        hipLaunchKernelGGL(fwd_simple_kernel, blocks, dim3(kSimpleWaves * 64), 0, stream, p);
+    else if (rows == kBM)
         launch_il(p, (unsigned)grid, stream);
+    else if (rows == 64 && p.cu_seqlens)
+        hipLaunchKernelGGL((fwd_split_kernel<2, true>), blocks, threads, 0, stream, p);
+    else if (rows == 64)
+        hipLaunchKernelGGL((fwd_split_kernel<2, false>), blocks, threads, 0, stream, p);
+    else if (p.cu_seqlens)
+        hipLaunchKernelGGL((fwd_split_kernel<1, true>), blocks, threads, 0, stream, p);
+    else
+        hipLaunchKernelGGL((fwd_split_kernel<1, false>), blocks, threads, 0, stream, p);
     return hipGetLastError() == hipSuccess ? PEC_OK : PEC_ERR_HIP;
 }
 
@@ -124,7 +201,6 @@ int chunk_impl(const pec_shape_t* shape, const void* q, const void* k, const voi
     p.n_q_heads = shape->n_q_heads;
     p.n_kv_heads = shape->n_kv_heads;
     p.group = shape->n_q_heads / shape->n_kv_heads;
-    p.n_items = (int32_t)((sq + kBM - 1) / kBM);
     p.out_f32 = out_f32;
     p.scale_log2 = scale * kLog2e;
     if (sweep) {
@@ -134,7 +210,10 @@ int chunk_impl(const pec_shape_t* shape, const void* q, const void* k, const voi
         p.stop = sweep->stop;
         p.seg_tiles = sweep->seg_tiles;
     }
-    return launch_fwd(p, (shape->flags & PEC_FLAG_SIMPLE_KERNEL) != 0, static_cast<hipStream_t>(stream));
+    const bool simple = (shape->flags & PEC_FLAG_SIMPLE_KERNEL) != 0;
+    const int rows = simple ? kBM : rows_of_dense_call(p);
+    p.n_items = (int32_t)((sq + rows - 1) / rows);
+    return launch_fwd(p, simple, rows, static_cast<hipStream_t>(stream));
 }
 
 // Ring schedule of one member: step t brings segment (r - t) mod P with r = q_off / chunk (own
@@ -580,8 +659,8 @@ int pec_sp_select_strategy(const pec_sp_model_t* m, pec_sp_choice_t* c) {
 
 size_t pec_varlen_workspace_bytes(int32_t batch, int64_t total_tokens) {
     if (batch < 0 || total_tokens < 0) return 0;
-    // every sequence contributes at most len / 256 + 1 items
-    const size_t cap = (size_t)(total_tokens / kBM) + (size_t)batch + 1;
+    // every sequence contributes at most len / rows + 1 items, rows >= 32 per item
+    const size_t cap = (size_t)(total_tokens / 32) + (size_t)batch + 1;
     // work list + counter (padded) + two int32 arrays indexed by query-tile number
     return cap * sizeof(WorkItem) + 256 + (2 * cap + 1) * sizeof(int32_t);
 }
@@ -599,9 +678,13 @@ int pec_attn_varlen(const pec_shape_t* shape, const void* q, const void* k, cons
         (reinterpret_cast<uintptr_t>(cu_seqlens) & 3u))
         return PEC_ERR_MISALIGNED;
     if (!workspace || workspace_bytes < pec_varlen_workspace_bytes(batch, total_tokens)) return PEC_ERR_WORKSPACE;
-    (void)max_seqlen;   // a hint only: the work list is sized from total_tokens, so an understated value costs nothing
-
-    const size_t cap = (size_t)(total_tokens / kBM) + (size_t)batch + 1;
+    // max_seqlen is a hint only (it weighs in the choice of the rows per work item): the work list is sized from
+    // total_tokens, so an understated value costs no result
+    const bool simple = (shape->flags & PEC_FLAG_SIMPLE_KERNEL) != 0;
+    const int rows = simple ? kBM
+                            : rows_of_list_call(shape->n_q_heads, shape->n_kv_heads, batch, total_tokens, total_tokens,
+                                                std::min<int64_t>(max_seqlen, total_tokens), causal, 0);
+    const size_t cap = (size_t)(total_tokens / rows) + (size_t)batch + 1;
     const int capacity = (int)std::min<size_t>(cap, 0x7fffffff);
     char* ws = static_cast<char*>(workspace);
     WorkItem* work = reinterpret_cast<WorkItem*>(ws);
@@ -609,7 +692,7 @@ int pec_attn_varlen(const pec_shape_t* shape, const void* q, const void* k, cons
     int32_t* bucket = reinterpret_cast<int32_t*>(ws + cap * sizeof(WorkItem) + 256);
     int32_t* cursor = bucket + cap + 1;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    hipLaunchKernelGGL(build_worklist_kernel, dim3(1), dim3(1024), 0, st, cu_seqlens, (int)batch, (int)total_tokens, kBM,
+    hipLaunchKernelGGL(build_worklist_kernel, dim3(1), dim3(1024), 0, st, cu_seqlens, (int)batch, (int)total_tokens, rows,
                        capacity, work, n_work, bucket, cursor);
     if (hipGetLastError() != hipSuccess) return PEC_ERR_HIP;
 
@@ -632,7 +715,7 @@ int pec_attn_varlen(const pec_shape_t* shape, const void* q, const void* k, cons
     p.n_work = n_work;
     p.sched = n_work + 8;   // same 256-byte block, zeroed by the builder
     p.total_tokens = (int32_t)total_tokens;
-    return launch_fwd(p, (shape->flags & PEC_FLAG_SIMPLE_KERNEL) != 0, st);
+    return launch_fwd(p, simple, rows, st);
 }
 
 namespace {
@@ -641,11 +724,11 @@ struct ColocLayout {
     size_t cap_items, n_buckets, slot_cap;
     size_t off_counters, off_bucket, off_cursor, off_slot0, off_split, off_part_lse, off_part_out, bytes;
 };
-ColocLayout coloc_layout(int n_q_heads, int32_t batch, int64_t total_q, int64_t total_k) {
+ColocLayout coloc_layout(int n_q_heads, int32_t batch, int64_t total_q, int64_t total_k, int rows) {
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
     ColocLayout L;
     L.slot_cap = (size_t)(total_k / kColocRange) + (size_t)batch;
-    L.cap_items = (size_t)(total_q / kBM) + (size_t)batch + L.slot_cap + 1;
+    L.cap_items = (size_t)(total_q / rows) + (size_t)batch + L.slot_cap + 1;
     L.n_buckets = (size_t)(total_k / 256) + 2;
     size_t o = up(L.cap_items * sizeof(WorkItem));
     L.off_counters = o;  o += 256;
@@ -662,7 +745,7 @@ ColocLayout coloc_layout(int n_q_heads, int32_t batch, int64_t total_q, int64_t 
 
 size_t pec_colocated_workspace_bytes(const pec_shape_t* shape, int32_t batch, int64_t total_q, int64_t total_k) {
     if (!shape || shape->n_q_heads <= 0 || batch < 0 || total_q < 0 || total_k < 0) return 0;
-    return coloc_layout(shape->n_q_heads, batch, total_q, total_k).bytes;
+    return coloc_layout(shape->n_q_heads, batch, total_q, total_k, 32).bytes;   // the most any choice of rows needs
 }
 
 int pec_attn_colocated(const pec_shape_t* shape, const void* q, const void* k, const void* v,
@@ -680,8 +763,9 @@ int pec_attn_colocated(const pec_shape_t* shape, const void* q, const void* k, c
     if (misaligned(q) || misaligned(k) || misaligned(v) || misaligned(out) || misaligned(workspace) ||
         (reinterpret_cast<uintptr_t>(cu_seqlens_q) & 3u) || (reinterpret_cast<uintptr_t>(cu_seqlens_k) & 3u))
         return PEC_ERR_MISALIGNED;
-    const ColocLayout L = coloc_layout(shape->n_q_heads, batch, total_q, total_k);
-    if (!workspace || workspace_bytes < L.bytes) return PEC_ERR_WORKSPACE;
+    const int rows = rows_of_list_call(shape->n_q_heads, shape->n_kv_heads, batch, total_q, total_k, 0, causal, kColocRange);
+    const ColocLayout L = coloc_layout(shape->n_q_heads, batch, total_q, total_k, rows);
+    if (!workspace || workspace_bytes < pec_colocated_workspace_bytes(shape, batch, total_q, total_k)) return PEC_ERR_WORKSPACE;
     if (L.cap_items > 0x7fffffff || L.n_buckets > 0x7fffffff) return PEC_ERR_UNSUPPORTED;
 
     char* ws = static_cast<char*>(workspace);
@@ -693,7 +777,7 @@ int pec_attn_colocated(const pec_shape_t* shape, const void* q, const void* k, c
     float* part_out = reinterpret_cast<float*>(ws + L.off_part_out);
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipLaunchKernelGGL(build_colocated_worklist_kernel, dim3(1), dim3(1024), 0, st, cu_seqlens_q, cu_seqlens_k, (int)batch,
-                       (int)total_q, (int)total_k, kBM, kColocRange, (int)L.cap_items, (int)L.slot_cap, (int)L.n_buckets,
+                       (int)total_q, (int)total_k, rows, kColocRange, (int)L.cap_items, (int)L.slot_cap, (int)L.n_buckets,
                        work, counters, reinterpret_cast<int32_t*>(ws + L.off_bucket),
                        reinterpret_cast<int32_t*>(ws + L.off_cursor), seq_slot0, split_seqs);
     if (hipGetLastError() != hipSuccess) return PEC_ERR_HIP;
@@ -723,7 +807,7 @@ int pec_attn_colocated(const pec_shape_t* shape, const void* q, const void* k, c
     p.part_lse = part_lse;
     p.total_k = (int32_t)total_k;
     p.coloc_range_len = kColocRange;
-    if (int rc = launch_fwd(p, false, st)) return rc;
+    if (int rc = launch_fwd(p, false, rows, st)) return rc;
 
     const dim3 grid((unsigned)shape->n_q_heads, (unsigned)std::min<int32_t>(batch, 1024));
     if (shape->out_dtype == PEC_F32)
