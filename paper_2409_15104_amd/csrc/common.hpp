@@ -59,6 +59,8 @@ struct FwdParams {
     int32_t delta;          // q_off - kv_off, clamped to [-sq-1, sk]
     int32_t causal;
     int32_t n_q_heads, n_kv_heads, group;
+    int32_t log_heads;      // fwd_il_kernel: 2^log_heads query heads of a KV group share a work item, (256 >> log_heads)
+                            // query positions of each; group is a multiple of 2^log_heads
     int32_t n_items;        // query tiles (dense) or work-list capacity (varlen)
     int32_t out_f32;
     float scale_log2;       // scale * log2(e)

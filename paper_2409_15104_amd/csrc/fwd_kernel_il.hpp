@@ -82,7 +82,10 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
     // used up; the heaviest items come first in the list, so the launch ends on the lightest ones.
     constexpr bool dynamic = kList;
     const int n_items_eff = dynamic ? min(*p.n_work, p.n_items) : p.n_items;
-    const WorkOrder order(n_items_eff, p.group, p.n_kv_heads);
+    const int log_heads = kSweep ? 0 : p.log_heads;
+    // work units per item and KV head: lists hold tiles of 256 positions, cut further inside this kernel
+    const int units = kList ? p.group : p.group >> log_heads;
+    const WorkOrder order(n_items_eff, units, p.n_kv_heads);
     const int64_t per_xcd = order.count;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n_slots = (int)(gridDim.x >> 3);
@@ -162,8 +165,17 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
     const int per_kvh = order.per_kvh;
     const int kvh = (int)(logical / per_kvh);
     const int rem = (int)(logical % per_kvh);
-    const int item = rem / p.group;
-    const int head = kvh * p.group + rem % p.group;
+    const int item = rem / units;
+    // The 256 query rows of a work unit are 2^log_heads heads x (256 >> log_heads) positions, 32 positions of one head
+    // per wavefront (see log_heads_per_item() on the host).  The units of a list item are its position sub-tiles, the
+    // longest first, for each such set of heads: they read the same keys and are drawn one after the other.  (With the
+    // sub-tiles as list items of their own, ordered by length over all sequences, neighbours shared no keys: 2 % slower
+    // than one head per item on a batch with a 65,536-token prompt.)
+    const int sub = kList ? (rem % units) >> log_heads : rem % units;
+    const int sub_tile = kList ? (1 << log_heads) - 1 - (rem & ((1 << log_heads) - 1)) : 0;
+    const int head = kvh * p.group + (sub << log_heads) + (wave >> (3 - log_heads));
+    int bm = BM >> log_heads;
+    int wave_row = (wave << 5) & (bm - 1);
 
     // Per-item geometry and addressing: rows sq x keys sk with diagonal offset delta; element offsets of
     // row 0 in q (q_off0), in out / acc (o_off0) and in lse (lse_off0), the row stride of q / out / acc.
@@ -190,13 +202,16 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
             sq = b1 - b0;
             sk = k1 - k0;
             delta = sk - sq;
-            qt = w.qtile;
+            qt = (w.qtile << log_heads) + sub_tile;
+            if ((qt << 8) >> log_heads >= sq) continue;   // the sequence ends before this sub-tile
             kv_tok0 = k0;
             q_off0 = b0 * q_stride + (int64_t)head * kHeadDim;
             o_off0 = q_off0;
             lse_off0 = (int64_t)head * p.lse_stride + b0;
         } else {              // a key range of a one-token sequence: the heads of a KV group are the rows
-            if (rem % p.group != 0) continue;   // one unit per KV head
+            if (rem % units != 0) continue;   // one unit per KV head
+            bm = BM;
+            wave_row = wave << 5;
             const int r = -1 - w.qtile;
             const int64_t slot_no = (int64_t)p.seq_slot0[w.seq] + r;
             sq = p.group;
@@ -241,10 +256,10 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
         }
     }
     const int causal = p.causal;
-    const int row0 = qt * BM;
-    const int rw0 = row0 + wave * 32;
+    const int row0 = qt * bm;
+    const int rw0 = row0 + wave_row;
     const int wave_last = rw0 + 31;
-    const int blk_last = min(sq, row0 + BM) - 1;
+    const int blk_last = min(sq, row0 + bm) - 1;
     int kv_end = sk;
     if (causal) kv_end = max(0, min(sk, blk_last + delta + 1));
     int n_tiles = (kv_end + kBN - 1) / kBN;

@@ -47,10 +47,21 @@ void launch_il(const FwdParams& p, unsigned grid, hipStream_t st) {
         hipLaunchKernelGGL(fwd_il_kernel<kFwdDense>, dim3(8 * slots), dim3(512), 0, st, p);
 }
 
-// Both kernels take 256 query rows per workgroup, so work lists and launch geometry do not depend
-// on which one a call selects.
-constexpr int kBM = 256;
-static_assert(kSimpleBM == kBM, "the two kernels must agree on the query tile");
+constexpr int kBM = 256;   // query rows per workgroup of fwd_il_kernel and fwd_simple_kernel
+static_assert(kSimpleBM == kBM, "rows == kBM stands for either");
+
+// The 256 rows of a fwd_il_kernel work item: as many heads of a KV group as divide it, up to 8, and 256 / heads query
+// positions of each.  All of them read the same keys, so the choice changes no traffic; fewer positions waste less at
+// the causal diagonal (a workgroup walks to the last key of its last row) and in the last, partly filled row tile.  256
+// prompts of the benchmark's length mix with 32 q / 8 kv heads take 1.56 M tile steps with one head per item, 1.48 M
+// with two, 1.44 M with four (1.40 M would be no waste).
+// Measured (one head per item -> up to eight): causal ring step of 4096 x 4096, 32 q / 8 kv heads, one of four in
+// 878 -> 859 us; the 256 prompts with a decode step 12.43 -> 12.17 ms: the chip is at its power limit, and wavefronts
+// that wait at the diagonal cost time but little power.
+int log_heads_per_item(int n_q_heads, int n_kv_heads) {
+    const int g = n_q_heads / n_kv_heads;
+    return g % 8 == 0 ? 3 : g % 4 == 0 ? 2 : g % 2 == 0 ? 1 : 0;
+}
 
 // Query rows per workgroup of a launch: 256 (fwd_il_kernel, one workgroup per 64-key tile step) or, where that would
 // leave compute units idle, 64 or 32 (fwd_split_kernel<2 | 1>, 256 keys per step).  Estimated time of a choice =
@@ -74,7 +85,11 @@ constexpr RowChoice kRowChoices[] = {{256, 64, 11.5, 1.13, 1.55}, {64, 256, 8.0,
 
 int rows_of_dense_call(const FwdParams& p) {
     if (p.progress || p.kv_split_len || p.q_row_stride || p.q_head_stride) return kBM;
-    if ((double)((p.sq + kBM - 1) / kBM) * p.n_q_heads >= compute_units()) return kBM;   // an item for every compute unit
+    auto groups_of = [&](int rows) {   // workgroups (of the persistent kernel: work items)
+        const int l = rows == kBM ? p.log_heads : 0, positions = rows >> l;
+        return (double)((p.sq + positions - 1) / positions) * (p.n_q_heads >> l);
+    };
+    if (groups_of(kBM) >= compute_units()) return kBM;   // an item for every compute unit
     auto keys = [&](int64_t last_row) {   // that a query tile ending with this row sees
         return (double)(p.causal ? std::max<int64_t>(0, std::min<int64_t>(p.sk, last_row + p.delta + 1)) : p.sk);
     };
@@ -82,7 +97,7 @@ int rows_of_dense_call(const FwdParams& p) {
     double best_t = 0;
     for (const RowChoice& c : kRowChoices) {
         const double longest = keys(p.sq - 1), shortest = keys(std::min(p.sq, c.rows) - 1);
-        const double t = c.estimate((double)((p.sq + c.rows - 1) / c.rows) * p.n_q_heads, longest, 0.5 * (longest + shortest));
+        const double t = c.estimate(groups_of(c.rows), longest, 0.5 * (longest + shortest));
         if (c.rows == kBM || t < best_t) {
             best = c.rows;
             best_t = t;
@@ -102,13 +117,16 @@ int rows_of_list_call(int n_q_heads, int n_kv_heads, int64_t batch, int64_t tota
     const double seen = std::min((double)total_q, 3 * len);
     if (longest <= 0) longest = (int64_t)std::min((double)total_q, 4 * len);
     const double range_units = range_len > 0 ? std::max(0.0, (double)(total_k - total_q) / range_len) * n_kv_heads : 0.0;
-    if ((double)batch * std::ceil(len / kBM) * n_q_heads + range_units >= compute_units()) return kBM;
+    auto groups_of = [&](int rows) {
+        const int l = rows == kBM ? log_heads_per_item(n_q_heads, n_kv_heads) : 0;
+        return batch * std::ceil(len / (rows >> l)) * (n_q_heads >> l) + range_units;
+    };
+    if (groups_of(kBM) >= compute_units()) return kBM;
     int best = kBM;
     double best_t = 0;
     for (const RowChoice& c : kRowChoices) {
         if (range_units > 0 && n_q_heads / n_kv_heads > c.rows) continue;   // a range item's rows are the heads of a group
-        const double groups = batch * std::ceil(len / c.rows) * n_q_heads + range_units;
-        const double t = c.estimate(groups, std::max({(double)longest, len, range_units > 0 ? (double)range_len : 0.0}),
+        const double t = c.estimate(groups_of(c.rows), std::max({(double)longest, len, range_units > 0 ? (double)range_len : 0.0}),
                                     causal ? 0.5 * seen : seen);
         if (c.rows == kBM || t < best_t) {
             best = c.rows;
@@ -137,9 +155,9 @@ int check_shape(const pec_shape_t* s, float* scale_out) {
     return PEC_OK;
 }
 
-// `rows`: query rows per workgroup, which is what p.n_items counts.
+// `rows`: query rows per workgroup; p.n_items counts tiles of `rows` positions (lists) or rows >> log_heads (dense).
 int launch_fwd(const FwdParams& p, bool simple, int rows, hipStream_t stream) {
-    const int64_t total = (int64_t)p.n_items * p.n_q_heads;
+    const int64_t total = (int64_t)p.n_items * (p.cu_seqlens ? p.n_q_heads : p.n_q_heads >> p.log_heads);
     if (total <= 0) return PEC_OK;
     const int64_t per_xcd = (total + 7) / 8;
     const int64_t grid = per_xcd * 8;
@@ -211,8 +229,12 @@ int chunk_impl(const pec_shape_t* shape, const void* q, const void* k, const voi
         p.seg_tiles = sweep->seg_tiles;
     }
     const bool simple = (shape->flags & PEC_FLAG_SIMPLE_KERNEL) != 0;
+    // (the progress table of the resumable sweep counts tiles of 256 rows of one head)
+    if (!simple && !sweep) p.log_heads = log_heads_per_item(p.n_q_heads, p.n_kv_heads);
     const int rows = simple ? kBM : rows_of_dense_call(p);
-    p.n_items = (int32_t)((sq + rows - 1) / rows);
+    if (rows != kBM) p.log_heads = 0;
+    const int positions = rows >> p.log_heads;
+    p.n_items = (int32_t)((sq + positions - 1) / positions);
     return launch_fwd(p, simple, rows, static_cast<hipStream_t>(stream));
 }
 
@@ -707,6 +729,7 @@ int pec_attn_varlen(const pec_shape_t* shape, const void* q, const void* k, cons
     p.n_q_heads = shape->n_q_heads;
     p.n_kv_heads = shape->n_kv_heads;
     p.group = shape->n_q_heads / shape->n_kv_heads;
+    p.log_heads = simple || rows != kBM ? 0 : log_heads_per_item(p.n_q_heads, p.n_kv_heads);
     p.n_items = capacity;
     p.out_f32 = shape->out_dtype == PEC_F32;
     p.scale_log2 = scale * kLog2e;
@@ -793,6 +816,7 @@ int pec_attn_colocated(const pec_shape_t* shape, const void* q, const void* k, c
     p.n_q_heads = shape->n_q_heads;
     p.n_kv_heads = shape->n_kv_heads;
     p.group = shape->n_q_heads / shape->n_kv_heads;
+    p.log_heads = rows != kBM ? 0 : log_heads_per_item(p.n_q_heads, p.n_kv_heads);
     p.n_items = (int32_t)L.cap_items;
     p.out_f32 = shape->out_dtype == PEC_F32;
     p.scale_log2 = scale * kLog2e;
