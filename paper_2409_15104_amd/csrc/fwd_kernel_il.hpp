@@ -41,9 +41,10 @@ typedef __attribute__((address_space(3))) unsigned char lds_byte;
 // inline asm, and the hardware does not interlock a VALU read of a register an MFMA is still writing,
 // so the wait states sit in ONE asm statement that takes all four accumulators as read-write operands:
 // every MFMA that produces them is ordered before it by the data dependence, and nothing can move
-// between the wait and the multiplications that follow it in the same statement sequence.
+// between the wait and the multiplications that follow it in the same statement sequence.  The factor is an operand of
+// the wait for the same reason: it comes from v_exp_f32, whose result the next instruction must not read.
 __device__ __forceinline__ void scale_acc_in_place(f32x16 (&o)[4], float a) {
-    asm volatile("s_nop 15\n\ts_nop 15" : "+v"(o[0]), "+v"(o[1]), "+v"(o[2]), "+v"(o[3]));
+    asm volatile("s_nop 15\n\ts_nop 15" : "+v"(o[0]), "+v"(o[1]), "+v"(o[2]), "+v"(o[3]), "+v"(a));
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
