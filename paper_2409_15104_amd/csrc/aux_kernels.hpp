@@ -258,8 +258,8 @@ __global__ __launch_bounds__(1024) void build_worklist_kernel(const int32_t* __r
         for (int t = lane; t < nq; t += 64) {
             const int pos = bucket[t] + atomicAdd(&cursor[t], 1);
             if (pos < capacity) {   // cannot overflow: capacity bounds the item count of any clamped cu_seqlens
-                work[pos].seq = b;
-                work[pos].qtile = t;
+                const int b0 = min(max(cu[b], 0), total_tokens), b1 = min(max(cu[b + 1], b0), total_tokens);
+                work[pos] = WorkItem{b0, b1 - b0, b0, b1 - b0, t, 0, {0, 0}};
             }
         }
     }
@@ -267,13 +267,13 @@ __global__ __launch_bounds__(1024) void build_worklist_kernel(const int32_t* __r
 
 // Work list of a colocated batch (separate query and key offsets per sequence).  A sequence with one
 // query token and more than range_len keys (the decode step of a long request) is cut into key ranges
-// of range_len keys, every other sequence into query tiles of bm rows; items are ordered by
+// of range_len keys, `group` of them per item (one for each of its work units), every other sequence into query tiles of bm rows; items are ordered by
 // descending number of 256-key blocks they have to read, so the long ones start first.
 // Single workgroup of 1024 threads.  counters: [0] number of items, [1] slots handed out, [2] number
 // of split sequences.  bucket is int32[n_buckets + 1], cursor int32[n_buckets], n_buckets >= total_k / 256 + 2.
 __global__ __launch_bounds__(1024) void build_colocated_worklist_kernel(
     const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k, int batch, int total_q, int total_k, int bm,
-    int range_len, int capacity, int slot_capacity, int n_buckets, WorkItem* __restrict__ work,
+    int range_len, int group, int capacity, int slot_capacity, int n_buckets, WorkItem* __restrict__ work,
     int32_t* __restrict__ counters, int32_t* __restrict__ bucket, int32_t* __restrict__ cursor,
     int32_t* __restrict__ seq_slot0, SplitSeq* __restrict__ split_seqs) {
     __shared__ int32_t red[1024];
@@ -283,22 +283,25 @@ __global__ __launch_bounds__(1024) void build_colocated_worklist_kernel(
     if (tid < 3) counters[tid] = 0;
     __syncthreads();
     struct Seq {
-        int len_q, len_k, n_items;
+        int q0, len_q, k0, len_k, n_items, n_ranges;
         bool split;
     };
     auto seq_of = [&](int b) {
         const int q0 = min(max(cu_q[b], 0), total_q), q1 = min(max(cu_q[b + 1], q0), total_q);
         const int k0 = min(max(cu_k[b], 0), total_k), k1 = min(max(cu_k[b + 1], k0), total_k);
         Seq s;
+        s.q0 = q0;
+        s.k0 = k0;
         s.len_q = q1 - q0;
         s.len_k = k1 - k0;
         s.split = s.len_q == 1 && s.len_k > range_len;
-        s.n_items = s.split ? (s.len_k + range_len - 1) / range_len : (s.len_q + bm - 1) / bm;
+        s.n_ranges = s.split ? (s.len_k + range_len - 1) / range_len : 0;
+        s.n_items = s.split ? (s.n_ranges + group - 1) / group : (s.len_q + bm - 1) / bm;
         return s;
     };
     auto weight_of = [&](const Seq& s, int i) {   // 256-key blocks item i of the sequence reads
         int keys;
-        if (s.split) keys = min(range_len, s.len_k - i * range_len);
+        if (s.split) keys = min(range_len, s.len_k - i * group * range_len);
         else keys = min(s.len_k, max(0, s.len_k - s.len_q + min(s.len_q, bm * (i + 1))));
         return min(n_buckets - 1, (keys + 255) / 256);
     };
@@ -308,10 +311,10 @@ __global__ __launch_bounds__(1024) void build_colocated_worklist_kernel(
         const Seq s = seq_of(b);
         int slot0 = -1;
         if (s.split) {
-            slot0 = atomicAdd(&counters[1], s.n_items);
-            if (slot0 + s.n_items <= slot_capacity) {
+            slot0 = atomicAdd(&counters[1], s.n_ranges);
+            if (slot0 + s.n_ranges <= slot_capacity) {
                 const int idx = atomicAdd(&counters[2], 1);
-                split_seqs[idx] = SplitSeq{b, slot0, s.n_items, 0};
+                split_seqs[idx] = SplitSeq{b, slot0, s.n_ranges, 0};
             } else {
                 slot0 = -2;
             }
@@ -337,8 +340,10 @@ __global__ __launch_bounds__(1024) void build_colocated_worklist_kernel(
             const int w = weight_of(s, i);
             const int pos = bucket[w] + atomicAdd(&cursor[w], 1);
             if (pos < capacity) {
-                work[pos].seq = b;
-                work[pos].qtile = s.split ? -1 - i : i;
+                const int r0 = i * group;   // first key range of a split sequence's item
+                work[pos] = s.split ? WorkItem{s.q0, 1, s.k0 + r0 * range_len, s.len_k - r0 * range_len, -1,
+                                               seq_slot0[b] + r0, {0, 0}}
+                                    : WorkItem{s.q0, s.len_q, s.k0, s.len_k, i, 0, {0, 0}};
             }
         }
     }

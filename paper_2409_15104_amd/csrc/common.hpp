@@ -38,10 +38,15 @@ constexpr int kTileBytes = kBN * kRowBytes;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
-struct WorkItem {   // one (sequence, query tile) of a packed batch; in a colocated batch a negative
-    int32_t seq;    // qtile stands for key range number -1 - qtile of a one-token (decode) sequence
-    int32_t qtile;
+struct WorkItem {        // one (sequence, query tile) of a packed or colocated batch, with all an attention kernel needs
+    int32_t q0, len_q;   // query rows of the sequence, in the packed arrays
+    int32_t k0, len_k;   // its keys; query i sits at position len_k - len_q + i
+    int32_t qtile;       // query tile; negative: keys k0 ... of a one-token (decode) sequence, one range for each of the
+                         // item's work units (as many per KV head as it has query heads)
+    int32_t slot;        // where the first range's partial result goes
+    int32_t pad[2];
 };
+static_assert(sizeof(WorkItem) == 32, "fwd_il_kernel fetches work items as eight words");
 
 constexpr int32_t kSweepDone = 0x7fffffff;
 
@@ -64,13 +69,11 @@ struct FwdParams {
     int32_t n_items;        // query tiles (dense) or work-list capacity (varlen)
     int32_t out_f32;
     float scale_log2;       // scale * log2(e)
-    // varlen mode (cu_seqlens != null): work list built on the device
-    const int32_t* cu_seqlens;
+    // packed or colocated batch (work != null): work list built on the device
     const WorkItem* work;
     const int32_t* n_work;  // number of valid work items
     int32_t* sched;         // eight zeroed counters (fwd_il_kernel only): work items are drawn from them, one
                             // counter per XCD's share of the work order, instead of being dealt in fixed rounds
-    int32_t total_tokens;   // rows of the packed arrays (bounds every index taken from cu_seqlens)
     // split-KV mode (kv_split_len > 0; fwd_il_kernel only): work item = key range
     // [item * kv_split_len, ...), partial results go to out / lse + item * split_*_stride
     int32_t kv_split_len;
@@ -78,16 +81,10 @@ struct FwdParams {
     // element strides of q / out / acc between rows and between heads (0 = the packed
     // [tokens, n_q_heads, 128] layout; fwd_il_kernel only)
     int64_t q_row_stride, q_head_stride;
-    // colocated batch (cu_seqlens_k != null; fwd_il_kernel only): sequence b has queries
-    // cu_seqlens[b] .. and keys cu_seqlens_k[b] ..; its query i sits at position len_k - len_q + i.
-    // One-token sequences with long caches are cut into key ranges of coloc_range_len keys whose
-    // partial results go to part_out / part_lse at slot seq_slot0[seq] + range.
-    const int32_t* cu_seqlens_k;
-    const int32_t* seq_slot0;
+    // colocated batch: partial results of the key ranges that one-token sequences with long caches are cut into
     float* part_out;            // [slots][n_q_heads][128] fp32
     float* part_lse;            // [slots][n_q_heads]
-    int32_t total_k;            // rows of the packed k / v arrays
-    int32_t coloc_range_len;    // keys per range, a multiple of 64
+    int32_t range_len;          // keys per range, a multiple of 64
     // resumable sweep (dense mode, progress != null; fwd_il_kernel only): work item i has finished its first
     // progress[i] key segments of seg_tiles tiles each (kSweepDone: all of them) and continues from there, its
     // running state in acc_in / lse_in / l_part.  A nonzero *stop makes a workgroup end the item in hand at the next

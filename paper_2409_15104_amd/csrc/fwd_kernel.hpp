@@ -45,15 +45,15 @@ __global__ __launch_bounds__(kSimpleWaves * 64) void fwd_simple_kernel(const Fwd
 
     int sq, sk, delta, qt;
     int64_t q_tok0, kv_tok0;
-    if (p.cu_seqlens) {
+    if (p.work) {
         if (item >= *p.n_work) return;
         const WorkItem w = p.work[item];
-        const int b0 = min(max(p.cu_seqlens[w.seq], 0), p.total_tokens);
-        const int b1 = min(max(p.cu_seqlens[w.seq + 1], b0), p.total_tokens);
-        sq = sk = b1 - b0;
-        delta = 0;
+        sq = w.len_q;
+        sk = w.len_k;
+        delta = sk - sq;
         qt = w.qtile;
-        q_tok0 = kv_tok0 = b0;
+        q_tok0 = w.q0;
+        kv_tok0 = w.k0;
     } else {
         sq = p.sq;
         sk = p.sk;

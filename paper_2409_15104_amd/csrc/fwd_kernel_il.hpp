@@ -68,7 +68,7 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
     // of the tile loop is then "lane offset + 16-bit immediate".  (Separate arrays are placed by the
     // compiler in an order of its own; a stage that lands above 64 KiB needs its address in a register,
     // and the tile loop has none to spare.)
-    __shared__ __attribute__((aligned(1024))) unsigned char lds_all[4 * kTileBytes + 256 + 64];
+    __shared__ __attribute__((aligned(1024))) unsigned char lds_all[4 * kTileBytes + 512 + (kList ? BM * kRowBytes : 0)];
     unsigned char* const lds_k0 = lds_all;
     unsigned char* const lds_k1 = lds_all + kTileBytes;
     unsigned char* const lds_v0 = lds_all + 2 * kTileBytes;
@@ -81,8 +81,7 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
     // (p.sched): items differ in length by orders of magnitude and the XCDs do not run at the same speed, so
     // every workgroup draws its next item from its XCD's counter, and from the next XCD's once that share is
     // used up; the heaviest items come first in the list, so the launch ends on the lightest ones.
-    constexpr bool dynamic = kList;
-    const int n_items_eff = dynamic ? min(*p.n_work, p.n_items) : p.n_items;
+    const int n_items_eff = kList ? min(*p.n_work, p.n_items) : p.n_items;
     const int log_heads = kSweep ? 0 : p.log_heads;
     // work units per item and KV head: lists hold tiles of 256 positions, cut further inside this kernel
     const int units = kList ? p.group : p.group >> log_heads;
@@ -107,82 +106,137 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
         return __builtin_amdgcn_readfirstlane(v);
     };
     bool first_item = true;   // of this workgroup in this launch: it is never abandoned before its first segment
-    // Drawing (work-list calls): lane 0 of wavefront 0 takes the next index and leaves it in one of two LDS
-    // words used in turn; everyone reads it after the next barrier.  The draw for item i + 1 is made while item
-    // i waits for its first tiles, so its latency is hidden; only the first draw, and the one after an index
-    // that turns out to hold no work, is waited for.  Words 2 and 3 (lane 0's own): the XCD share being drawn
-    // from and how many shares were found used up.
+    // Drawing (work-list calls; wavefront 0 only).  The item after the one in hand is known a whole item ahead: its unit
+    // number (-1: none left) and its WorkItem, brought in by a tile-style load, sit in one of two LDS slots used in turn.
+    // A number is drawn by request_item() and read behind the stores of an item's results, so nobody waits for the atomic.
     typedef __attribute__((address_space(3))) volatile int lds_int;
     lds_int* const lds_sched = (lds_int*)(lds_all + 4 * kTileBytes + 256);
-    int sched_par = 0;         // which of the two words holds the index to take next
-    bool have_next = false;
-    auto draw_next = [&](int into) {
-        if (wave == 0) {
-            int ln;
-            asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
-            if (ln == 0) {
-                int x = lds_sched[2], t = lds_sched[3], got = -1;
-                while (t < 8) {
-                    const int v = atomicAdd(&p.sched[x], 1);
-                    if (v < per_xcd && (got = (int)order.unit(x, v)) >= 0) break;
-                    x = (x + 1) & 7;
-                    ++t;
-                }
-                lds_sched[into] = got;
-                lds_sched[2] = x;
-                lds_sched[3] = t;
+    auto slot_of = [](int par) { return 16 * par; };    // word of the unit number; the WorkItem starts 8 words behind it
+    int par = 0;                      // slot of the item after the one in hand
+    auto lane_id = []() {
+        int ln;
+        asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
+        return ln;
+    };
+    auto uniform = [](const void* a) {   // a uniform address whose parts the compiler may have moved to vector registers
+        const uint64_t u = (uint64_t)a;
+        return reinterpret_cast<const unsigned char*>((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(u >> 32)) << 32 |
+                                                      (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)u));
+    };
+    auto count_up = [&](int x) {      // takes a number from XCD x's counter (valid in lane 0)
+        int v = 0;
+        if (lane_id() == 0) v = atomicAdd(&p.sched[x], 1);
+        return v;
+    };
+    int share = blockIdx.x & 7;       // the XCD share being drawn from
+    auto settle = [&](int v) {        // number taken from the share's counter -> unit, from other shares if need be
+        for (uint32_t used_up = 0;;) {
+            const int i = __builtin_amdgcn_readfirstlane(v);
+            if (i < per_xcd) {
+                const int got = (int)order.unit(share, i);
+                if (got >= 0) return got;
+            } else {                  // the next share with something left, all counters looked at together
+                used_up |= 1u << share;
+                const int ln = lane_id();
+                int c = 0x7fffffff;
+                if (ln < 8 && !(used_up >> ((share + ln) & 7) & 1)) c = __hip_atomic_load(&p.sched[(share + ln) & 7], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const uint64_t left = __ballot(c < per_xcd);
+                if (left == 0) return -1;
+                share = (share + __builtin_ctzll(left)) & 7;
             }
+            v = count_up(share);
         }
     };
-    if (dynamic && threadIdx.x == 0) {
-        lds_sched[2] = (int)(blockIdx.x & 7);
-        lds_sched[3] = 0;
+    auto take_next = [&](int v, int par) {     // leaves a unit and, soon, its WorkItem in LDS
+        const int got = settle(v);
+        const int ln = lane_id();
+        if (ln == 0) lds_sched[slot_of(par)] = got;
+        const unsigned char* const w = uniform(p.work + max(got, 0) % order.per_kvh / units);
+        const uint32_t lds_item = __builtin_amdgcn_readfirstlane(lds_stop + 256 + 4 * (slot_of(par) + 8));
+        if (got >= 0 && ln < 8) {
+            asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
+                         :
+                         : "v"(ln * 4), "s"(w), "s"(lds_item)
+                         : "memory", "m0");
+        }
+        __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt 0: the unit is in LDS before the next barrier
+    };
+
+    // Geometry of a work item: rows sq x keys sk with diagonal offset delta; rows row0 ... of the workgroup, rw0 ... of
+    // this wavefront; element offsets of row 0 in q (q_off0), in out / acc (o_off0) and in lse (lse_off0).
+    struct Geo {
+        int logical, sq, sk, delta, row0, rw0, blk_last, kvh;
+        int64_t kv_tok0, q_off0, q_stride, o_off0, lse_off0;
+        bool part;      // a key range whose result is a partial one
+    };
+    const int64_t packed_stride = (int64_t)p.n_q_heads * kHeadDim;
+    auto list_geometry = [&](int logical, const WorkItem& w) {
+        Geo g;
+        g.logical = logical;
+        g.kvh = logical / order.per_kvh;
+        const int rem = logical % order.per_kvh;
+        const int u = rem % units;
+        g.sk = w.len_k;
+        g.kv_tok0 = w.k0;
+        g.part = w.qtile < 0;
+        if (!g.part) {   // rows of a query tile.  The units of a list item are its position sub-tiles, the longest
+            // first, for each set of heads: they read the same keys and are drawn one after the other.  (With the
+            // sub-tiles as list items of their own, ordered by length over all sequences, neighbours shared no keys:
+            // 2 % slower than one head per item on a batch with a 65,536-token prompt.)
+            const int bm = BM >> log_heads;
+            const int head = g.kvh * p.group + (u >> log_heads << log_heads) + (wave >> (3 - log_heads));
+            g.sq = w.len_q;
+            g.delta = g.sk - g.sq;
+            g.row0 = ((w.qtile << log_heads) + (1 << log_heads) - 1 - (u & ((1 << log_heads) - 1))) * bm;
+            g.rw0 = g.row0 + ((wave << 5) & (bm - 1));
+            g.q_stride = packed_stride;
+            g.q_off0 = w.q0 * packed_stride + (int64_t)head * kHeadDim;
+            g.o_off0 = g.q_off0;
+            g.lse_off0 = (int64_t)head * p.lse_stride + w.q0;
+            g.blk_last = min(g.sq, g.row0 + bm) - 1;
+        } else {         // a key range of a one-token sequence: the heads of a KV group are the rows
+            const int64_t slot_head = (int64_t)(w.slot + u) * p.n_q_heads + (int64_t)g.kvh * p.group;
+            g.kv_tok0 += (int64_t)u * p.range_len;
+            g.sk = min(p.range_len, w.len_k - u * p.range_len);
+            g.sq = g.sk > 0 ? p.group : 0;
+            g.delta = g.sk;       // every key of the range is visible
+            g.row0 = 0;
+            g.rw0 = wave << 5;
+            g.q_stride = kHeadDim;
+            g.q_off0 = w.q0 * packed_stride + (int64_t)g.kvh * p.group * kHeadDim;
+            g.o_off0 = slot_head * kHeadDim;
+            g.lse_off0 = slot_head;
+            g.blk_last = g.sq - 1;
+        }
+        if (g.row0 >= g.sq) g.sq = g.sk = 0;   // nothing to do: the sequence ends before this sub-tile
+        return g;
+    };
+    auto tiles_of = [&](const Geo& g) {
+        int kv_end = g.sk;
+        if (p.causal) kv_end = max(0, min(g.sk, g.blk_last + g.delta + 1));
+        return (kv_end + kBN - 1) / kBN;
+    };
+    Geo next;
+    bool requested = false;    // Q and the first K tiles of the item in hand were asked for by the item before
+    if constexpr (kList) {
+        if (wave == 0) {
+            const int got = settle(count_up(share));
+            if (lane_id() == 0) lds_sched[1] = got;
+            __builtin_amdgcn_s_waitcnt(0xC07F);
+        }
+        __builtin_amdgcn_s_barrier();
+        const int got = __builtin_amdgcn_readfirstlane(lds_sched[1]);
+        if (got < 0) return;
+        next = list_geometry(got, p.work[got % order.per_kvh / units]);
     }
-    for (int64_t round0 = 0; dynamic || round0 < per_xcd; round0 += n_slots) {
+    for (int64_t round0 = 0; kList || round0 < per_xcd; round0 += n_slots) {
     // Lane-derived values are recomputed for every work item (the empty asm hides that they are
     // loop invariant): hoisted out of this loop they would stay live through the tile loop, which
     // has no register to spare -- a spill reload there waits on the tile loads just issued.
-    int lane;   // volatile asm: not hoisted, and no vector register carries it from item to item
-    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+    const int lane = lane_id();   // volatile asm: not hoisted, and no vector register carries it from item to item
     const int l32 = lane & 31;
     const int hl = lane >> 5;
-    int64_t logical;
-    if (dynamic) {
-        if (!have_next) {
-            draw_next(sched_par);
-            __builtin_amdgcn_s_barrier();
-        }
-        have_next = false;
-        const int got = __builtin_amdgcn_readfirstlane(lds_sched[sched_par]);
-        sched_par ^= 1;
-        if (got < 0) break;
-        logical = got;
-    } else {
-        const int64_t idx_in_xcd = round0 + (((round0 / n_slots) & 1) ? (n_slots - 1 - slot) : slot);
-        if (idx_in_xcd >= per_xcd) continue;
-        logical = order.unit(blockIdx.x & 7, idx_in_xcd);
-        if (logical < 0) continue;
-    }
-    const int per_kvh = order.per_kvh;
-    const int kvh = (int)(logical / per_kvh);
-    const int rem = (int)(logical % per_kvh);
-    const int item = rem / units;
-    // The 256 query rows of a work unit are 2^log_heads heads x (256 >> log_heads) positions, 32 positions of one head
-    // per wavefront (see log_heads_per_item() on the host).  The units of a list item are its position sub-tiles, the
-    // longest first, for each such set of heads: they read the same keys and are drawn one after the other.  (With the
-    // sub-tiles as list items of their own, ordered by length over all sequences, neighbours shared no keys: 2 % slower
-    // than one head per item on a batch with a 65,536-token prompt.)
-    const int sub = kList ? (rem % units) >> log_heads : rem % units;
-    const int sub_tile = kList ? (1 << log_heads) - 1 - (rem & ((1 << log_heads) - 1)) : 0;
-    const int head = kvh * p.group + (sub << log_heads) + (wave >> (3 - log_heads));
-    int bm = BM >> log_heads;
-    int wave_row = (wave << 5) & (bm - 1);
-
-    // Per-item geometry and addressing: rows sq x keys sk with diagonal offset delta; element offsets of
-    // row 0 in q (q_off0), in out / acc (o_off0) and in lse (lse_off0), the row stride of q / out / acc.
-    int sq, sk, delta, qt;
-    int64_t kv_tok0, q_off0, o_off0, lse_off0;
-    int64_t q_stride = p.q_row_stride ? p.q_row_stride : (int64_t)p.n_q_heads * kHeadDim;
+    Geo g;
     void* out_ptr = p.out;
     float* lse_ptr = p.lse;
     int out_f32 = p.out_f32;
@@ -190,80 +244,61 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
     float* acc_out = p.acc_out;
     int seg_done = 0;          // resumable sweep: key segments this item has behind it
     if constexpr (kList) {
-        if (item >= *p.n_work) continue;
-        const WorkItem w = p.work[item];
-        const int b0 = min(max(p.cu_seqlens[w.seq], 0), p.total_tokens);
-        const int b1 = min(max(p.cu_seqlens[w.seq + 1], b0), p.total_tokens);
-        int k0 = b0, k1 = b1;
-        if (p.cu_seqlens_k) {
-            k0 = min(max(p.cu_seqlens_k[w.seq], 0), p.total_k);
-            k1 = min(max(p.cu_seqlens_k[w.seq + 1], k0), p.total_k);
-        }
-        if (w.qtile >= 0) {   // a query tile of a prompt: its rows are the last b1 - b0 positions of k1 - k0
-            sq = b1 - b0;
-            sk = k1 - k0;
-            delta = sk - sq;
-            qt = (w.qtile << log_heads) + sub_tile;
-            if ((qt << 8) >> log_heads >= sq) continue;   // the sequence ends before this sub-tile
-            kv_tok0 = k0;
-            q_off0 = b0 * q_stride + (int64_t)head * kHeadDim;
-            o_off0 = q_off0;
-            lse_off0 = (int64_t)head * p.lse_stride + b0;
-        } else {              // a key range of a one-token sequence: the heads of a KV group are the rows
-            if (rem % units != 0) continue;   // one unit per KV head
-            bm = BM;
-            wave_row = wave << 5;
-            const int r = -1 - w.qtile;
-            const int64_t slot_no = (int64_t)p.seq_slot0[w.seq] + r;
-            sq = p.group;
-            kv_tok0 = (int64_t)k0 + (int64_t)r * p.coloc_range_len;
-            sk = (int)max((int64_t)0, min((int64_t)p.coloc_range_len, (int64_t)k1 - kv_tok0));
-            delta = sk;       // every key of the range is visible
-            qt = 0;
-            q_off0 = b0 * q_stride + (int64_t)kvh * p.group * kHeadDim;
-            q_stride = kHeadDim;
-            o_off0 = (slot_no * p.n_q_heads + (int64_t)kvh * p.group) * kHeadDim;
-            lse_off0 = slot_no * p.n_q_heads + (int64_t)kvh * p.group;
+        g = next;
+        if (g.part) {
             out_ptr = p.part_out;
             lse_ptr = p.part_lse;
             out_f32 = 1;
         }
     } else {
-        sq = p.sq;
-        sk = p.sk;
-        delta = p.delta;
-        qt = p.causal ? (p.n_items - 1 - item) : item;  // longest rows first
-        kv_tok0 = 0;
-        q_off0 = (int64_t)head * (p.q_head_stride ? p.q_head_stride : kHeadDim);
-        o_off0 = q_off0;
-        lse_off0 = (int64_t)head * p.lse_stride;
+        const int64_t idx_in_xcd = round0 + (((round0 / n_slots) & 1) ? (n_slots - 1 - slot) : slot);
+        if (idx_in_xcd >= per_xcd) continue;
+        const int64_t logical = order.unit(blockIdx.x & 7, idx_in_xcd);
+        if (logical < 0) continue;
+        g.logical = (int)logical;
+        g.kvh = (int)(logical / order.per_kvh);
+        const int rem = (int)(logical % order.per_kvh);
+        const int item = rem / units;
+        // the 256 query rows are 2^log_heads heads x (256 >> log_heads) positions, 32 positions of one head per wavefront
+        // (see log_heads_per_item() on the host)
+        const int bm = BM >> log_heads;
+        const int head = g.kvh * p.group + ((rem % units) << log_heads) + (wave >> (3 - log_heads));
+        int qt = p.causal ? (p.n_items - 1 - item) : item;  // longest rows first
+        g.sq = p.sq;
+        g.sk = p.sk;
+        g.delta = p.delta;
+        g.kv_tok0 = 0;
+        g.q_stride = p.q_row_stride ? p.q_row_stride : packed_stride;
+        g.q_off0 = (int64_t)head * (p.q_head_stride ? p.q_head_stride : kHeadDim);
+        g.o_off0 = g.q_off0;
+        g.lse_off0 = (int64_t)head * p.lse_stride;
         if constexpr (kSweep) {     // continue behind the segments already folded in
             seg_done = p.progress[logical];
             // (a table that was never initialised must not send the loads out of bounds: anything that is
             // not a count of segments inside the key range is taken as "through" or as "not started")
-            if (seg_done == kSweepDone || (seg_done > 0 && (int64_t)seg_done * p.seg_tiles * kBN >= (int64_t)sk)) continue;
+            if (seg_done == kSweepDone || (seg_done > 0 && (int64_t)seg_done * p.seg_tiles * kBN >= (int64_t)g.sk)) continue;
             seg_done = max(seg_done, 0);
             if (seg_done == 0) acc_in = nullptr;
-            kv_tok0 = (int64_t)seg_done * p.seg_tiles * kBN;
-            sk -= (int)kv_tok0;
-            delta -= (int)kv_tok0;
+            g.kv_tok0 = (int64_t)seg_done * p.seg_tiles * kBN;
+            g.sk -= (int)g.kv_tok0;
+            g.delta -= (int)g.kv_tok0;
         }
         if (!kSweep && p.kv_split_len > 0) {   // the work item is a key range; all of it is visible (decode)
             qt = 0;
-            kv_tok0 = (int64_t)item * p.kv_split_len;
-            sk = (int)max((int64_t)0, min((int64_t)p.kv_split_len, (int64_t)p.sk - kv_tok0));
-            o_off0 += item * p.split_out_stride;
-            lse_off0 += item * p.split_lse_stride;
+            g.kv_tok0 = (int64_t)item * p.kv_split_len;
+            g.sk = (int)max((int64_t)0, min((int64_t)p.kv_split_len, (int64_t)p.sk - g.kv_tok0));
+            g.o_off0 += item * p.split_out_stride;
+            g.lse_off0 += item * p.split_lse_stride;
         }
+        g.row0 = qt * bm;
+        g.rw0 = g.row0 + ((wave << 5) & (bm - 1));
+        g.blk_last = min(g.sq, g.row0 + bm) - 1;
     }
+    const int sq = g.sq, sk = g.sk, delta = g.delta, row0 = g.row0, rw0 = g.rw0;
+    const int64_t q_stride = g.q_stride, o_off0 = g.o_off0, lse_off0 = g.lse_off0;
     const int causal = p.causal;
-    const int row0 = qt * bm;
-    const int rw0 = row0 + wave_row;
     const int wave_last = rw0 + 31;
-    const int blk_last = min(sq, row0 + bm) - 1;
-    int kv_end = sk;
-    if (causal) kv_end = max(0, min(sk, blk_last + delta + 1));
-    int n_tiles = (kv_end + kBN - 1) / kBN;
+    int n_tiles = tiles_of(g);
 
     // runs of tiles for this wavefront: [0, n_full) need no mask, [n_full, n_act) do,
     // [n_act, n_tiles) lie wholly after its rows (causal only)
@@ -278,16 +313,17 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
     if (rw0 >= sq) n_full = n_act = 0;   // a wavefront without a valid row only helps loading tiles
 
     const uint32_t kv_stride_b = (uint32_t)p.n_kv_heads * kHeadDim * 2;   // bytes per token
-    const unsigned char* kbase =
-        reinterpret_cast<const unsigned char*>(p.k) + (kv_tok0 * p.n_kv_heads + kvh) * (int64_t)(kHeadDim * 2);
-    const unsigned char* vbase =
-        reinterpret_cast<const unsigned char*>(p.v) + (kv_tok0 * p.n_kv_heads + kvh) * (int64_t)(kHeadDim * 2);
+    auto kv_base = [&](const __bf16* kv, const Geo& of) {
+        return reinterpret_cast<const unsigned char*>(kv) + (of.kv_tok0 * p.n_kv_heads + of.kvh) * (int64_t)(kHeadDim * 2);
+    };
+    const unsigned char* kbase = kv_base(p.k, g);
+    const unsigned char* vbase = kv_base(p.v, g);
 
     // ---- Q fragments
     bf16x8 qf[8];
-    {
+    if constexpr (!kList) {
         const int row = rw0 + l32;
-        const __bf16* qrow = p.q + q_off0 + row * q_stride + 8 * hl;
+        const __bf16* qrow = p.q + g.q_off0 + row * q_stride + 8 * hl;
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
             u32x4 raw = {0u, 0u, 0u, 0u};
@@ -345,8 +381,7 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
                      : "v"(voff), "s"(sbase), "s"(lds_addr)
                      : "memory", "m0");
     };
-    auto issue_tile = [&](const unsigned char* base, bool is_v, uint32_t full_off0, int tile, unsigned char* stage) {
-        if (tile >= n_tiles) return;
+    auto issue_rows = [&](const unsigned char* base, bool is_v, uint32_t full_off0, int tile, unsigned char* stage, int sk) {
         const int key0 = tile * kBN;
         const unsigned char* tb = base + (int64_t)key0 * kv_stride_b;
         const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)stage + wave * 1024;
@@ -369,8 +404,55 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
             }
         }
     };
-    auto issue_k = [&](int tile, unsigned char* stage) { issue_tile(kbase, false, ldk_off0, tile, stage); };
-    auto issue_v = [&](int tile, unsigned char* stage) { issue_tile(vbase, true, ldv_off0, tile, stage); };
+    auto issue_k = [&](int tile, unsigned char* stage) {
+        if (tile < n_tiles) issue_rows(kbase, false, ldk_off0, tile, stage, sk);
+    };
+    auto issue_v = [&](int tile, unsigned char* stage) {
+        if (tile < n_tiles) issue_rows(vbase, true, ldv_off0, tile, stage, sk);
+    };
+    // Work-list calls take Q through LDS, a private 8 KiB per wavefront (registers that are filled while the last tile is
+    // worked on cost 140 spill instructions there); rows past the end re-read the last valid one, nothing of theirs is stored
+    unsigned char* const lds_q = lds_all + 4 * kTileBytes + 512 + wave * 32 * kRowBytes;
+    auto issue_q = [&](const Geo& of) {
+        if (of.rw0 >= of.sq) return;
+        const int ln = lane_id(), last = of.sq - 1 - of.rw0;
+        const unsigned char* qb = uniform(p.q + of.q_off0 + of.rw0 * of.q_stride);
+        const uint32_t l0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds_q;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int row = 4 * i + (ln >> 4);
+            dma16(qb, (uint32_t)min(row, last) * (uint32_t)(of.q_stride * 2) + (uint32_t)((ln & 15) ^ (row & 15)) * 16u, l0 + i * 1024);
+        }
+    };
+    // When the item's tiles are done, and both K stages free, everything the next item starts with is requested -- its Q,
+    // its first two K tiles, and the draw of the item behind it; the stores of this item's results go out behind them.
+    // An item of 32 tiles used to spend 6 of its 68 us on finding its geometry and waiting for 96 KiB of Q and K, the rate
+    // of one compute unit's memory path; requested one tile step earlier, that step waited for them instead.  8 prompts
+    // 294 -> 260 us, 256 prompts with a decode step 12.17 -> 11.51 ms, with a 65,536-token prompt 37.98 -> 37.30 ms.
+    bool more = false;       // there is a next item
+    int drawn = 0;
+    auto request_item = [&]() {
+        const lds_byte* const slot = (lds_byte*)lds_sched + 4 * slot_of(par);
+        const int unit = __builtin_amdgcn_readfirstlane(*(const __attribute__((address_space(3))) int*)slot);
+        more = unit >= 0;
+        if (!more) return;
+        if (wave == 0) drawn = count_up(share);
+        const u32x4 lo = *(const __attribute__((address_space(3))) u32x4*)(slot + 32);
+        const u32x2 hi = *(const __attribute__((address_space(3))) u32x2*)(slot + 48);
+        WorkItem w;
+        w.q0 = __builtin_amdgcn_readfirstlane(lo[0]);
+        w.len_q = __builtin_amdgcn_readfirstlane(lo[1]);
+        w.k0 = __builtin_amdgcn_readfirstlane(lo[2]);
+        w.len_k = __builtin_amdgcn_readfirstlane(lo[3]);
+        w.qtile = __builtin_amdgcn_readfirstlane(hi[0]);
+        w.slot = __builtin_amdgcn_readfirstlane(hi[1]);
+        next = list_geometry(unit, w);
+        const int n = tiles_of(next);
+        const unsigned char* const kb = uniform(kv_base(p.k, next));
+        if (n > 0) issue_rows(kb, false, ldk_off0, 0, lds_k0, next.sk);
+        if (n > 1) issue_rows(kb, false, ldk_off0, 1, lds_k1, next.sk);
+        issue_q(next);
+    };
 
     // ---- LDS operand offsets inside a stage
     uint32_t k_off[8];
@@ -620,19 +702,31 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
     using P0 = std::integral_constant<int, 0>;
     using P1 = std::integral_constant<int, 1>;
 
-    // ---- prologue: K(0), K(1); V(0) also into the stage iteration 0 reads with P = 0 (finite data)
-    issue_k(0, lds_k0);
-    issue_k(1, lds_k1);
-    issue_v(0, lds_v1);
+    // ---- prologue: K(0), K(1), and finite data in the V stage that iteration 0 reads with P = 0
     const bool may_stop = kSweep && p.stop != nullptr;
-    if (may_stop && !first_item) request_stop_word();
-    if (dynamic) {   // the next item's index, while this one waits for its first tiles
-        draw_next(sched_par);
-        have_next = true;
+    if constexpr (kList) {
+        if (!requested) {
+            issue_q(g);
+            issue_k(0, lds_k0);
+            issue_k(1, lds_k1);
+            if (wave == 0) take_next(count_up(share), par);
+            end_of_iteration();
+        }
+        const u32x4 z = {0u, 0u, 0u, 0u};
+        u32x4* const v1 = reinterpret_cast<u32x4*>(lds_v1 + wave * 2048 + lane * 16);
+        v1[0] = z;
+        v1[64] = z;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) qf[t] = *reinterpret_cast<const bf16x8*>(lds_q + k_off[t]);
+    } else {
+        issue_k(0, lds_k0);
+        issue_k(1, lds_k1);
+        issue_v(0, lds_v1);
+        if (may_stop && !first_item) request_stop_word();
+        end_of_iteration();
+        if (may_stop && !first_item && read_stop_word() != 0) return;   // nothing of this item has been touched
+        first_item = false;
     }
-    end_of_iteration();
-    if (may_stop && !first_item && read_stop_word() != 0) return;   // nothing of this item has been touched
-    first_item = false;
     if (n_act > 0) {
         qk_mfma(s_a, lds_k0);
         row_max(T{}, s_a, 0);
@@ -648,6 +742,11 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
         alpha = 1.f;
     }
     asm volatile("" : "+v"(s_a[0]), "+v"(s_a[1]), "+v"(m_run), "+v"(m_use), "+v"(alpha));
+    if constexpr (kList) {
+        __builtin_amdgcn_s_waitcnt(0xC07F);                       // lgkmcnt 0: the zeros are in LDS
+        if (n_tiles == 0) __builtin_amdgcn_s_waitcnt(0x0F70);     // and the next WorkItem, with no tile step in between
+        asm volatile("" ::: "memory");
+    }
     __builtin_amdgcn_s_barrier();     // K stage 0 may be overwritten from here on
 
     // ---- schedule: every wavefront passes one barrier per tile.  Iteration j needs the mask
@@ -723,6 +822,8 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
         end_of_iteration();
     }
 
+    if constexpr (kList) request_item();
+
     // ---- epilogue
     if constexpr (kSweep) {   // an item stopped short keeps its fp32 state; one that is through writes the result
         if (stopped) out_ptr = nullptr; else acc_out = nullptr;
@@ -757,10 +858,21 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
         }
     }
     if (kSweep && threadIdx.x == 0) {
-        p.progress[logical] = stopped ? seg_done + stop_b / p.seg_tiles : kSweepDone;
+        p.progress[g.logical] = stopped ? seg_done + stop_b / p.seg_tiles : kSweepDone;
         if (!stopped) atomicSub(p.pending, 1);
     }
     if (kSweep && stopped) return;  // a stop request: this workgroup takes no further item
+    if constexpr (kList) {
+        if (!more) return;
+        requested = true;
+        // This wavefront's requests for the next item have landed: only younger stores may be outstanding.  A wavefront
+        // with rows has issued at least eight of them since, 128 bytes of O per lane, at most 16 per instruction.
+        if (rw0 < sq) __builtin_amdgcn_s_waitcnt(0x0F78);   // vmcnt 8
+        else __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt 0
+        par ^= 1;
+        if (wave == 0) take_next(drawn, par);
+        asm volatile("" ::: "memory");
+    }
     __builtin_amdgcn_s_barrier();   // every wavefront is done with the LDS stages before the next item's loads
     }   // work items of this workgroup
 }

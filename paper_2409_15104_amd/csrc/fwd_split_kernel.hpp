@@ -68,32 +68,25 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void fwd_split_kernel(const Fw
     int out_f32 = p.out_f32;
     if constexpr (LIST) {
         const WorkItem w = p.work[item];
-        const int b0 = min(max(p.cu_seqlens[w.seq], 0), p.total_tokens);
-        const int b1 = min(max(p.cu_seqlens[w.seq + 1], b0), p.total_tokens);
-        int k0 = b0, k1 = b1;
-        if (p.cu_seqlens_k) {
-            k0 = min(max(p.cu_seqlens_k[w.seq], 0), p.total_k);
-            k1 = min(max(p.cu_seqlens_k[w.seq + 1], k0), p.total_k);
-        }
-        if (w.qtile >= 0) {   // a query tile: its rows are among the last b1 - b0 positions of k1 - k0
-            sq = b1 - b0;
-            sk = k1 - k0;
+        sk = w.len_k;
+        kv_tok0 = w.k0;
+        if (w.qtile >= 0) {
+            sq = w.len_q;
             delta = sk - sq;
             qt = w.qtile;
-            kv_tok0 = k0;
-            q_off0 = b0 * q_stride + (int64_t)head * kHeadDim;
+            q_off0 = w.q0 * q_stride + (int64_t)head * kHeadDim;
             o_off0 = q_off0;
-            lse_off0 = (int64_t)head * p.lse_stride + b0;
+            lse_off0 = (int64_t)head * p.lse_stride + w.q0;
         } else {              // a key range of a one-token sequence: the heads of a KV group are the rows
-            if (rem % p.group != 0) return;   // one unit per KV head
-            const int r = -1 - w.qtile;
-            const int64_t slot_no = (int64_t)p.seq_slot0[w.seq] + r;
+            const int r = rem % p.group;
+            const int64_t slot_no = (int64_t)w.slot + r;
             sq = p.group;
-            kv_tok0 = (int64_t)k0 + (int64_t)r * p.coloc_range_len;
-            sk = (int)max((int64_t)0, min((int64_t)p.coloc_range_len, (int64_t)k1 - kv_tok0));
+            sk = min(p.range_len, w.len_k - r * p.range_len);
+            if (sk <= 0) return;
+            kv_tok0 += (int64_t)r * p.range_len;
             delta = sk;       // every key of the range is visible
             qt = 0;
-            q_off0 = b0 * q_stride + (int64_t)kvh * p.group * kHeadDim;
+            q_off0 = w.q0 * q_stride + (int64_t)kvh * p.group * kHeadDim;
             q_stride = kHeadDim;
             o_off0 = (slot_no * p.n_q_heads + (int64_t)kvh * p.group) * kHeadDim;
             lse_off0 = slot_no * p.n_q_heads + (int64_t)kvh * p.group;

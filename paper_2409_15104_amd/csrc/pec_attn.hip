@@ -41,7 +41,7 @@ void launch_il(const FwdParams& p, unsigned grid, hipStream_t st) {
     const unsigned slots = std::max(1u, std::min(per_xcd, (unsigned)compute_units() / 8));
     if (p.progress)
         hipLaunchKernelGGL(fwd_il_kernel<kFwdSweep>, dim3(8 * slots), dim3(512), 0, st, p);
-    else if (p.cu_seqlens)
+    else if (p.work)
         hipLaunchKernelGGL(fwd_il_kernel<kFwdList>, dim3(8 * slots), dim3(512), 0, st, p);
     else
         hipLaunchKernelGGL(fwd_il_kernel<kFwdDense>, dim3(8 * slots), dim3(512), 0, st, p);
@@ -157,7 +157,7 @@ int check_shape(const pec_shape_t* s, float* scale_out) {
 
 // `rows`: query rows per workgroup; p.n_items counts tiles of `rows` positions (lists) or rows >> log_heads (dense).
 int launch_fwd(const FwdParams& p, bool simple, int rows, hipStream_t stream) {
-    const int64_t total = (int64_t)p.n_items * (p.cu_seqlens ? p.n_q_heads : p.n_q_heads >> p.log_heads);
+    const int64_t total = (int64_t)p.n_items * (p.work ? p.n_q_heads : p.n_q_heads >> p.log_heads);
     if (total <= 0) return PEC_OK;
     const int64_t per_xcd = (total + 7) / 8;
     const int64_t grid = per_xcd * 8;
@@ -167,11 +167,11 @@ int launch_fwd(const FwdParams& p, bool simple, int rows, hipStream_t stream) {
         hipLaunchKernelGGL(fwd_simple_kernel, blocks, dim3(kSimpleWaves * 64), 0, stream, p);
     else if (rows == kBM)
         launch_il(p, (unsigned)grid, stream);
-    else if (rows == 64 && p.cu_seqlens)
+    else if (rows == 64 && p.work)
         hipLaunchKernelGGL((fwd_split_kernel<2, true>), blocks, threads, 0, stream, p);
     else if (rows == 64)
         hipLaunchKernelGGL((fwd_split_kernel<2, false>), blocks, threads, 0, stream, p);
-    else if (p.cu_seqlens)
+    else if (p.work)
         hipLaunchKernelGGL((fwd_split_kernel<1, true>), blocks, threads, 0, stream, p);
     else
         hipLaunchKernelGGL((fwd_split_kernel<1, false>), blocks, threads, 0, stream, p);
@@ -733,11 +733,9 @@ int pec_attn_varlen(const pec_shape_t* shape, const void* q, const void* k, cons
     p.n_items = capacity;
     p.out_f32 = shape->out_dtype == PEC_F32;
     p.scale_log2 = scale * kLog2e;
-    p.cu_seqlens = cu_seqlens;
     p.work = work;
     p.n_work = n_work;
     p.sched = n_work + 8;   // same 256-byte block, zeroed by the builder
-    p.total_tokens = (int32_t)total_tokens;
     return launch_fwd(p, simple, rows, st);
 }
 
@@ -800,7 +798,8 @@ int pec_attn_colocated(const pec_shape_t* shape, const void* q, const void* k, c
     float* part_out = reinterpret_cast<float*>(ws + L.off_part_out);
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipLaunchKernelGGL(build_colocated_worklist_kernel, dim3(1), dim3(1024), 0, st, cu_seqlens_q, cu_seqlens_k, (int)batch,
-                       (int)total_q, (int)total_k, rows, kColocRange, (int)L.cap_items, (int)L.slot_cap, (int)L.n_buckets,
+                       (int)total_q, (int)total_k, rows, kColocRange,
+                       (int)(shape->n_q_heads / shape->n_kv_heads), (int)L.cap_items, (int)L.slot_cap, (int)L.n_buckets,
                        work, counters, reinterpret_cast<int32_t*>(ws + L.off_bucket),
                        reinterpret_cast<int32_t*>(ws + L.off_cursor), seq_slot0, split_seqs);
     if (hipGetLastError() != hipSuccess) return PEC_ERR_HIP;
@@ -820,17 +819,12 @@ int pec_attn_colocated(const pec_shape_t* shape, const void* q, const void* k, c
     p.n_items = (int32_t)L.cap_items;
     p.out_f32 = shape->out_dtype == PEC_F32;
     p.scale_log2 = scale * kLog2e;
-    p.cu_seqlens = cu_seqlens_q;
     p.work = work;
     p.n_work = counters;
     p.sched = counters + 8;   // same 256-byte block, zeroed by the builder
-    p.total_tokens = (int32_t)total_q;
-    p.cu_seqlens_k = cu_seqlens_k;
-    p.seq_slot0 = seq_slot0;
     p.part_out = part_out;
     p.part_lse = part_lse;
-    p.total_k = (int32_t)total_k;
-    p.coloc_range_len = kColocRange;
+    p.range_len = kColocRange;
     if (int rc = launch_fwd(p, false, rows, st)) return rc;
 
     const dim3 grid((unsigned)shape->n_q_heads, (unsigned)std::min<int32_t>(batch, 1024));
