@@ -837,22 +837,38 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
             const float lse = raw ? m_run : (l_tot > 0.f ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY);
             if (raw) p.l_part[(lse_off0 + row) * 2 + hl] = l_run;
             if (hl == 0) lse_ptr[lse_off0 + row] = lse;
-            const int64_t obase = o_off0 + row * q_stride + 4 * hl;
+            const int64_t obase = o_off0 + row * q_stride;
+            // bf16: a lane holds four consecutive dims of every eight, the other half of the wavefront the other four; two
+            // groups of eight are swapped into one whole group per lane, so that a store moves 16 bytes per lane.  (Every
+            // row is a line of its own to the store path: with 8 bytes per lane it takes twice as many of them.  8 prompts
+            // 260 -> 252 us, 256 prompts with a decode step 11.51 -> 11.19 ms.)
 #pragma unroll
             for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    f32x4 x;
+                for (int b = 0; b < 4; b += 2) {
+                    f32x4 x, y;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) x[i] = o[dt][4 * b + i] * inv;
+                    for (int i = 0; i < 4; ++i) {
+                        x[i] = o[dt][4 * b + i] * inv;
+                        y[i] = o[dt][4 * b + 4 + i] * inv;
+                    }
                     const int64_t idx = obase + 32 * dt + 8 * b;
-                    if (acc_out) *reinterpret_cast<f32x4*>(acc_out + idx) = x;
+                    if (acc_out) {
+                        *reinterpret_cast<f32x4*>(acc_out + idx + 4 * hl) = x;
+                        *reinterpret_cast<f32x4*>(acc_out + idx + 4 * hl + 8) = y;
+                    }
                     if (out_ptr) {
-                        if (out_f32)
-                            *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(out_ptr) + idx) = x;
-                        else
-                            *reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(out_ptr) + idx) =
-                                __builtin_convertvector(x, bf16x4);
+                        if (out_f32) {
+                            *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(out_ptr) + idx + 4 * hl) = x;
+                            *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(out_ptr) + idx + 4 * hl + 8) = y;
+                        } else {
+                            const u32x2 px = __builtin_bit_cast(u32x2, __builtin_convertvector(x, bf16x4));
+                            const u32x2 py = __builtin_bit_cast(u32x2, __builtin_convertvector(y, bf16x4));
+                            const auto s0 = __builtin_amdgcn_permlane32_swap(px[0], py[0], false, false);
+                            const auto s1 = __builtin_amdgcn_permlane32_swap(px[1], py[1], false, false);
+                            *reinterpret_cast<u32x4*>(reinterpret_cast<__bf16*>(out_ptr) + idx + 8 * hl) =
+                                u32x4{s0[0], s1[0], s0[1], s1[1]};
+                        }
                     }
                 }
         }
