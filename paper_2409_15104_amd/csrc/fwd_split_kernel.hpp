@@ -101,6 +101,15 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void fwd_split_kernel(const Fw
         qt = p.causal ? (n_items - 1 - item) : item;
         q_off0 = o_off0 = (int64_t)head * kHeadDim;
         lse_off0 = (int64_t)head * p.lse_stride;
+        if (p.kv_split_len > 0) {   // decode: the item is a key range, all of it visible; the heads of a KV group are the rows
+            qt = 0;
+            q_stride = p.q_row_stride;
+            q_off0 = o_off0 = (int64_t)head * p.q_head_stride;
+            kv_tok0 = (int64_t)item * p.kv_split_len;
+            sk = (int)max((int64_t)0, min((int64_t)p.kv_split_len, (int64_t)p.sk - kv_tok0));
+            o_off0 += item * p.split_out_stride;
+            lse_off0 += item * p.split_lse_stride;
+        }
     }
     const int causal = p.causal;
     const int row0 = qt * BM;

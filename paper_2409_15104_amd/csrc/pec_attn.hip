@@ -487,7 +487,10 @@ int32_t pec_decode_default_splits(const pec_shape_t* shape, int64_t sk) {
     if (!shape || shape->n_kv_heads <= 0 || sk <= 0) return 1;
     const int g = shape->n_q_heads / shape->n_kv_heads;
     const int64_t per_cu = std::max<int64_t>(1, compute_units() / shape->n_kv_heads);
-    if (g <= 32) {   // one workgroup (four KV heads of one range) per compute unit, at least 8 tiles of 32 keys each
+    if (g <= 32 && 4 * per_cu * shape->n_kv_heads >= 3 * compute_units())   // fwd_split_kernel: a workgroup per compute unit,
+        return (int32_t)std::max<int64_t>(1, std::min<int64_t>(per_cu, sk / 256));   // a tile of 32 keys per wavefront
+    if (g <= 32) {   // so many KV heads that this would leave compute units idle: one workgroup (four KV heads of one range)
+                     // per compute unit, at least 8 tiles of 32 keys each
         const int64_t head_groups = (shape->n_kv_heads + kDecWaves - 1) / kDecWaves;
         return (int32_t)std::max<int64_t>(1, std::min<int64_t>(compute_units() / head_groups, sk / 256));
     }
@@ -524,6 +527,24 @@ int static_scratch(void** out) {
     return PEC_OK;
 }
 
+// Keys per range when sk keys are cut into n_splits ranges of whole tiles.
+int64_t range_keys(int64_t sk, int32_t n_splits, int tile) {
+    return std::max<int64_t>(((sk + n_splits - 1) / n_splits + tile - 1) / tile * tile, tile);
+}
+
+// Whether a decode step with groups of up to 32 heads runs on fwd_split_kernel (a workgroup per range and KV head, its
+// wavefronts sharing the keys) or on decode_kernel (a wavefront per range and KV head).  Microseconds per step, with the
+// merge, fresh caches, 8 KV heads, (keys per range) in decode_kernel / fwd_split_kernel:
+//     4,096 keys     16 ranges 18.2 / 11.4      64 ranges (64) 11.6 / 15.1
+//     32,768 keys    32 ranges 60.9 / 31.8     128 ranges (256) 33.6 / 41.9
+//     524,288 keys   32 ranges 766 / 356       128 ranges 384 / 372
+// The workgroup kernel wins while all of its workgroups run at once and every wavefront has a tile; a second round of
+// workgroups costs it the latency that decode_kernel's deeper rings hide.
+bool decode_on_split_kernel(const pec_shape_t* shape, int64_t sk, int32_t n_splits) {
+    return shape->n_q_heads / shape->n_kv_heads <= 32 && (int64_t)n_splits * shape->n_kv_heads <= compute_units() &&
+           range_keys(sk, n_splits, 32) > 64;
+}
+
 // Common body of the two decode entry points; `workspace` holds pec_decode_workspace_bytes(shape, n_splits) bytes.
 int decode_impl(const pec_shape_t* shape, float scale, const void* q, const void* k, const void* v, int64_t sk,
                 int32_t n_splits, void* out, float* lse, void* workspace, void* stream) {
@@ -532,7 +553,8 @@ int decode_impl(const pec_shape_t* shape, float scale, const void* q, const void
     float* lse_part = o_part + (size_t)n_splits * shape->n_q_heads * kHeadDim;
     hipStream_t st = static_cast<hipStream_t>(stream);
 
-    if (g <= 32) {   // one key range per wavefront (decode_kernel.hpp)
+    const bool split = decode_on_split_kernel(shape, sk, n_splits);
+    if (g <= 32 && !split) {   // one key range per wavefront (decode_kernel.hpp)
         DecodeParams d{};
         d.q = static_cast<const __bf16*>(q);
         d.k = static_cast<const unsigned char*>(k);
@@ -544,8 +566,7 @@ int decode_impl(const pec_shape_t* shape, float scale, const void* q, const void
         d.n_kv_heads = shape->n_kv_heads;
         d.group = g;
         d.n_ranges = n_splits;
-        const int64_t per = ((sk + n_splits - 1) / n_splits + kDecTile - 1) / kDecTile * kDecTile;
-        d.range_len = (int32_t)std::max<int64_t>(per, kDecTile);
+        d.range_len = (int32_t)range_keys(sk, n_splits, kDecTile);
         d.scale_log2 = scale * kLog2e;
         const int64_t blocks = (int64_t)n_splits * ((shape->n_kv_heads + kDecWaves - 1) / kDecWaves);
         const int64_t grid = ((blocks + 7) / 8) * 8;
@@ -572,21 +593,23 @@ int decode_impl(const pec_shape_t* shape, float scale, const void* q, const void
     p.n_items = n_splits;
     p.out_f32 = 1;
     p.scale_log2 = scale * kLog2e;
-    const int64_t split_len = ((sk + n_splits - 1) / n_splits + kBN - 1) / kBN * kBN;   // whole tiles
-    p.kv_split_len = (int32_t)std::max<int64_t>(split_len, kBN);
+    p.kv_split_len = (int32_t)range_keys(sk, n_splits, kBN);
     p.split_out_stride = (int64_t)shape->n_q_heads * kHeadDim;
     p.split_lse_stride = shape->n_q_heads;
     p.q_row_stride = kHeadDim;
     p.q_head_stride = (int64_t)g * kHeadDim;
     const int64_t total = (int64_t)n_splits * shape->n_kv_heads;
-    launch_il(p, (unsigned)(((total + 7) / 8) * 8), st);
+    if (split)
+        hipLaunchKernelGGL((fwd_split_kernel<1, false>), dim3((unsigned)(((total + 7) / 8) * 8)), dim3(kSplitWaves * 64), 0, st, p);
+    else
+        launch_il(p, (unsigned)(((total + 7) / 8) * 8), st);
     if (hipGetLastError() != hipSuccess) return PEC_ERR_HIP;
     }
     if (shape->out_dtype == PEC_F32)
-        hipLaunchKernelGGL((combine_splits_kernel<true>), dim3(shape->n_q_heads), dim3(kCombineGroups * 128), 0, st, o_part, lse_part,
+        hipLaunchKernelGGL((combine_splits_kernel<true>), dim3(shape->n_q_heads), dim3(kCombineThreads), 0, st, o_part, lse_part,
                            (int)n_splits, (int)shape->n_q_heads, out, lse);
     else
-        hipLaunchKernelGGL((combine_splits_kernel<false>), dim3(shape->n_q_heads), dim3(kCombineGroups * 128), 0, st, o_part, lse_part,
+        hipLaunchKernelGGL((combine_splits_kernel<false>), dim3(shape->n_q_heads), dim3(kCombineThreads), 0, st, o_part, lse_part,
                            (int)n_splits, (int)shape->n_q_heads, out, lse);
     return hipGetLastError() == hipSuccess ? PEC_OK : PEC_ERR_HIP;
 }
@@ -829,10 +852,10 @@ int pec_attn_colocated(const pec_shape_t* shape, const void* q, const void* k, c
 
     const dim3 grid((unsigned)shape->n_q_heads, (unsigned)std::min<int32_t>(batch, 1024));
     if (shape->out_dtype == PEC_F32)
-        hipLaunchKernelGGL((combine_colocated_kernel<true>), grid, dim3(kCombineGroups * 128), 0, st, part_out, part_lse,
+        hipLaunchKernelGGL((combine_colocated_kernel<true>), grid, dim3(kCombineThreads), 0, st, part_out, part_lse,
                            split_seqs, counters + 2, cu_seqlens_q, (int)total_q, (int)shape->n_q_heads, out, lse);
     else
-        hipLaunchKernelGGL((combine_colocated_kernel<false>), grid, dim3(kCombineGroups * 128), 0, st, part_out, part_lse,
+        hipLaunchKernelGGL((combine_colocated_kernel<false>), grid, dim3(kCombineThreads), 0, st, part_out, part_lse,
                            split_seqs, counters + 2, cu_seqlens_q, (int)total_q, (int)shape->n_q_heads, out, lse);
     return hipGetLastError() == hipSuccess ? PEC_OK : PEC_ERR_HIP;
 }
