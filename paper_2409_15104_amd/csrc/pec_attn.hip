@@ -706,8 +706,8 @@ size_t pec_varlen_workspace_bytes(int32_t batch, int64_t total_tokens) {
     if (batch < 0 || total_tokens < 0) return 0;
     // every sequence contributes at most len / rows + 1 items, rows >= 32 per item
     const size_t cap = (size_t)(total_tokens / 32) + (size_t)batch + 1;
-    // work list + counter (padded) + two int32 arrays indexed by query-tile number
-    return cap * sizeof(WorkItem) + 256 + (2 * cap + 1) * sizeof(int32_t);
+    // work list + counters (padded) + an int32 array indexed by item weight
+    return cap * sizeof(WorkItem) + 256 + (cap + 1) * sizeof(int32_t);
 }
 
 int pec_attn_varlen(const pec_shape_t* shape, const void* q, const void* k, const void* v, const int32_t* cu_seqlens,
@@ -735,10 +735,10 @@ int pec_attn_varlen(const pec_shape_t* shape, const void* q, const void* k, cons
     WorkItem* work = reinterpret_cast<WorkItem*>(ws);
     int32_t* n_work = reinterpret_cast<int32_t*>(ws + cap * sizeof(WorkItem));
     int32_t* bucket = reinterpret_cast<int32_t*>(ws + cap * sizeof(WorkItem) + 256);
-    int32_t* cursor = bucket + cap + 1;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    hipLaunchKernelGGL(build_worklist_kernel, dim3(1), dim3(1024), 0, st, cu_seqlens, (int)batch, (int)total_tokens, rows,
-                       capacity, work, n_work, bucket, cursor);
+    hipLaunchKernelGGL(build_worklist_kernel, dim3(1), dim3(1024), 0, st, cu_seqlens, cu_seqlens, (int)batch,
+                       (int)total_tokens, (int)total_tokens, rows, rows, 0, 1, capacity, 0, capacity + 1, work, n_work, bucket,
+                       static_cast<SplitSeq*>(nullptr));
     if (hipGetLastError() != hipSuccess) return PEC_ERR_HIP;
 
     FwdParams p{};
@@ -766,7 +766,7 @@ namespace {
 constexpr int kColocRange = 4096;   // keys per range of a split one-token sequence (64 tiles)
 struct ColocLayout {
     size_t cap_items, n_buckets, slot_cap;
-    size_t off_counters, off_bucket, off_cursor, off_slot0, off_split, off_part_lse, off_part_out, bytes;
+    size_t off_counters, off_bucket, off_split, off_part_lse, off_part_out, bytes;
 };
 ColocLayout coloc_layout(int n_q_heads, int32_t batch, int64_t total_q, int64_t total_k, int rows) {
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
@@ -776,9 +776,7 @@ ColocLayout coloc_layout(int n_q_heads, int32_t batch, int64_t total_q, int64_t 
     L.n_buckets = (size_t)(total_k / 256) + 2;
     size_t o = up(L.cap_items * sizeof(WorkItem));
     L.off_counters = o;  o += 256;
-    L.off_bucket = o;    o = up(o + (L.n_buckets + 1) * sizeof(int32_t));
-    L.off_cursor = o;    o = up(o + L.n_buckets * sizeof(int32_t));
-    L.off_slot0 = o;     o = up(o + (size_t)batch * sizeof(int32_t));
+    L.off_bucket = o;    o = up(o + L.n_buckets * sizeof(int32_t));
     L.off_split = o;     o = up(o + (size_t)batch * sizeof(SplitSeq));
     L.off_part_lse = o;  o = up(o + L.slot_cap * n_q_heads * sizeof(float));
     L.off_part_out = o;  o = up(o + L.slot_cap * n_q_heads * kHeadDim * sizeof(float));
@@ -815,16 +813,14 @@ int pec_attn_colocated(const pec_shape_t* shape, const void* q, const void* k, c
     char* ws = static_cast<char*>(workspace);
     WorkItem* work = reinterpret_cast<WorkItem*>(ws);
     int32_t* counters = reinterpret_cast<int32_t*>(ws + L.off_counters);
-    int32_t* seq_slot0 = reinterpret_cast<int32_t*>(ws + L.off_slot0);
     SplitSeq* split_seqs = reinterpret_cast<SplitSeq*>(ws + L.off_split);
     float* part_lse = reinterpret_cast<float*>(ws + L.off_part_lse);
     float* part_out = reinterpret_cast<float*>(ws + L.off_part_out);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    hipLaunchKernelGGL(build_colocated_worklist_kernel, dim3(1), dim3(1024), 0, st, cu_seqlens_q, cu_seqlens_k, (int)batch,
-                       (int)total_q, (int)total_k, rows, kColocRange,
-                       (int)(shape->n_q_heads / shape->n_kv_heads), (int)L.cap_items, (int)L.slot_cap, (int)L.n_buckets,
-                       work, counters, reinterpret_cast<int32_t*>(ws + L.off_bucket),
-                       reinterpret_cast<int32_t*>(ws + L.off_cursor), seq_slot0, split_seqs);
+    hipLaunchKernelGGL(build_worklist_kernel, dim3(1), dim3(1024), 0, st, cu_seqlens_q, cu_seqlens_k, (int)batch,
+                       (int)total_q, (int)total_k, rows, 256, kColocRange, (int)(shape->n_q_heads / shape->n_kv_heads),
+                       (int)L.cap_items, (int)L.slot_cap, (int)L.n_buckets, work, counters,
+                       reinterpret_cast<int32_t*>(ws + L.off_bucket), split_seqs);
     if (hipGetLastError() != hipSuccess) return PEC_ERR_HIP;
 
     FwdParams p{};
