@@ -61,6 +61,7 @@ template <int MODE>
 __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
     constexpr bool kSweep = MODE == kFwdSweep;
     constexpr bool kList = MODE == kFwdList;
+    constexpr bool kAhead = !kSweep;   // the next item's first loads go out before this item's results
     constexpr int NWAVES = 8;
     constexpr int BM = NWAVES * 32;
 
@@ -68,7 +69,7 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
     // of the tile loop is then "lane offset + 16-bit immediate".  (Separate arrays are placed by the
     // compiler in an order of its own; a stage that lands above 64 KiB needs its address in a register,
     // and the tile loop has none to spare.)
-    __shared__ __attribute__((aligned(1024))) unsigned char lds_all[4 * kTileBytes + 512 + (kList ? BM * kRowBytes : 0)];
+    __shared__ __attribute__((aligned(1024))) unsigned char lds_all[4 * kTileBytes + 512 + (kAhead ? BM * kRowBytes : 0)];
     unsigned char* const lds_k0 = lds_all;
     unsigned char* const lds_k1 = lds_all + kTileBytes;
     unsigned char* const lds_v0 = lds_all + 2 * kTileBytes;
@@ -211,6 +212,43 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
         if (g.row0 >= g.sq) g.sq = g.sk = 0;   // nothing to do: the sequence ends before this sub-tile
         return g;
     };
+    auto dense_geometry = [&](int logical) {
+        Geo g;
+        g.logical = logical;
+        g.kvh = logical / order.per_kvh;
+        const int rem = logical % order.per_kvh;
+        const int item = rem / units;
+        // the 256 query rows are 2^log_heads heads x (256 >> log_heads) positions, 32 positions of one head per wavefront
+        // (see log_heads_per_item() on the host)
+        const int bm = BM >> log_heads;
+        const int head = g.kvh * p.group + ((rem % units) << log_heads) + (wave >> (3 - log_heads));
+        int qt = p.causal ? (p.n_items - 1 - item) : item;  // longest rows first
+        g.sq = p.sq;
+        g.sk = p.sk;
+        g.delta = p.delta;
+        g.kv_tok0 = 0;
+        g.q_stride = p.q_row_stride ? p.q_row_stride : packed_stride;
+        g.q_off0 = (int64_t)head * (p.q_head_stride ? p.q_head_stride : kHeadDim);
+        g.o_off0 = g.q_off0;
+        g.lse_off0 = (int64_t)head * p.lse_stride;
+        g.part = false;
+        if (!kSweep && p.kv_split_len > 0) {   // the work item is a key range; all of it is visible (decode)
+            qt = 0;
+            g.kv_tok0 = (int64_t)item * p.kv_split_len;
+            g.sk = (int)max((int64_t)0, min((int64_t)p.kv_split_len, (int64_t)p.sk - g.kv_tok0));
+            g.o_off0 += item * p.split_out_stride;
+            g.lse_off0 += item * p.split_lse_stride;
+        }
+        g.row0 = qt * bm;
+        g.rw0 = g.row0 + ((wave << 5) & (bm - 1));
+        g.blk_last = min(g.sq, g.row0 + bm) - 1;
+        return g;
+    };
+    // dense calls: the unit this workgroup works on in a round of n_slots per XCD (snake order), -1: none, nor in later rounds
+    auto dense_unit = [&](int64_t round0) {
+        const int64_t i = round0 + (((round0 / n_slots) & 1) ? (n_slots - 1 - slot) : slot);
+        return i < per_xcd ? (int)order.unit(blockIdx.x & 7, i) : -1;
+    };
     auto tiles_of = [&](const Geo& g) {
         int kv_end = g.sk;
         if (p.causal) kv_end = max(0, min(g.sk, g.blk_last + g.delta + 1));
@@ -228,8 +266,12 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
         const int got = __builtin_amdgcn_readfirstlane(lds_sched[1]);
         if (got < 0) return;
         next = list_geometry(got, p.work[got % order.per_kvh / units]);
+    } else if constexpr (kAhead) {
+        const int unit = dense_unit(0);
+        if (unit < 0) return;
+        next = dense_geometry(unit);
     }
-    for (int64_t round0 = 0; kList || round0 < per_xcd; round0 += n_slots) {
+    for (int64_t round0 = 0; kAhead || round0 < per_xcd; round0 += n_slots) {
     // Lane-derived values are recomputed for every work item (the empty asm hides that they are
     // loop invariant): hoisted out of this loop they would stay live through the tile loop, which
     // has no register to spare -- a spill reload there waits on the tile loads just issued.
@@ -243,56 +285,27 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
     const float* acc_in = p.acc_in;
     float* acc_out = p.acc_out;
     int seg_done = 0;          // resumable sweep: key segments this item has behind it
-    if constexpr (kList) {
+    if constexpr (kAhead) {
         g = next;
-        if (g.part) {
+        if (kList && g.part) {
             out_ptr = p.part_out;
             lse_ptr = p.part_lse;
             out_f32 = 1;
         }
     } else {
-        const int64_t idx_in_xcd = round0 + (((round0 / n_slots) & 1) ? (n_slots - 1 - slot) : slot);
-        if (idx_in_xcd >= per_xcd) continue;
-        const int64_t logical = order.unit(blockIdx.x & 7, idx_in_xcd);
-        if (logical < 0) continue;
-        g.logical = (int)logical;
-        g.kvh = (int)(logical / order.per_kvh);
-        const int rem = (int)(logical % order.per_kvh);
-        const int item = rem / units;
-        // the 256 query rows are 2^log_heads heads x (256 >> log_heads) positions, 32 positions of one head per wavefront
-        // (see log_heads_per_item() on the host)
-        const int bm = BM >> log_heads;
-        const int head = g.kvh * p.group + ((rem % units) << log_heads) + (wave >> (3 - log_heads));
-        int qt = p.causal ? (p.n_items - 1 - item) : item;  // longest rows first
-        g.sq = p.sq;
-        g.sk = p.sk;
-        g.delta = p.delta;
-        g.kv_tok0 = 0;
-        g.q_stride = p.q_row_stride ? p.q_row_stride : packed_stride;
-        g.q_off0 = (int64_t)head * (p.q_head_stride ? p.q_head_stride : kHeadDim);
-        g.o_off0 = g.q_off0;
-        g.lse_off0 = (int64_t)head * p.lse_stride;
-        if constexpr (kSweep) {     // continue behind the segments already folded in
-            seg_done = p.progress[logical];
-            // (a table that was never initialised must not send the loads out of bounds: anything that is
-            // not a count of segments inside the key range is taken as "through" or as "not started")
-            if (seg_done == kSweepDone || (seg_done > 0 && (int64_t)seg_done * p.seg_tiles * kBN >= (int64_t)g.sk)) continue;
-            seg_done = max(seg_done, 0);
-            if (seg_done == 0) acc_in = nullptr;
-            g.kv_tok0 = (int64_t)seg_done * p.seg_tiles * kBN;
-            g.sk -= (int)g.kv_tok0;
-            g.delta -= (int)g.kv_tok0;
-        }
-        if (!kSweep && p.kv_split_len > 0) {   // the work item is a key range; all of it is visible (decode)
-            qt = 0;
-            g.kv_tok0 = (int64_t)item * p.kv_split_len;
-            g.sk = (int)max((int64_t)0, min((int64_t)p.kv_split_len, (int64_t)p.sk - g.kv_tok0));
-            g.o_off0 += item * p.split_out_stride;
-            g.lse_off0 += item * p.split_lse_stride;
-        }
-        g.row0 = qt * bm;
-        g.rw0 = g.row0 + ((wave << 5) & (bm - 1));
-        g.blk_last = min(g.sq, g.row0 + bm) - 1;
+        const int unit = dense_unit(round0);
+        if (unit < 0) return;
+        // continue behind the segments already folded in
+        seg_done = p.progress[unit];
+        // (a table that was never initialised must not send the loads out of bounds: anything that is
+        // not a count of segments inside the key range is taken as "through" or as "not started")
+        if (seg_done == kSweepDone || (seg_done > 0 && (int64_t)seg_done * p.seg_tiles * kBN >= (int64_t)p.sk)) continue;
+        seg_done = max(seg_done, 0);
+        if (seg_done == 0) acc_in = nullptr;
+        g = dense_geometry(unit);
+        g.kv_tok0 = (int64_t)seg_done * p.seg_tiles * kBN;
+        g.sk -= (int)g.kv_tok0;
+        g.delta -= (int)g.kv_tok0;
     }
     const int sq = g.sq, sk = g.sk, delta = g.delta, row0 = g.row0, rw0 = g.rw0;
     const int64_t q_stride = g.q_stride, o_off0 = g.o_off0, lse_off0 = g.lse_off0;
@@ -321,7 +334,7 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
 
     // ---- Q fragments
     bf16x8 qf[8];
-    if constexpr (!kList) {
+    if constexpr (!kAhead) {
         const int row = rw0 + l32;
         const __bf16* qrow = p.q + g.q_off0 + row * q_stride + 8 * hl;
 #pragma unroll
@@ -410,7 +423,7 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
     auto issue_v = [&](int tile, unsigned char* stage) {
         if (tile < n_tiles) issue_rows(vbase, true, ldv_off0, tile, stage, sk);
     };
-    // Work-list calls take Q through LDS, a private 8 KiB per wavefront (registers that are filled while the last tile is
+    // All calls but the resumable sweep take Q through LDS, a private 8 KiB per wavefront (registers that are filled while the last tile is
     // worked on cost 140 spill instructions there); rows past the end re-read the last valid one, nothing of theirs is stored
     unsigned char* const lds_q = lds_all + 4 * kTileBytes + 512 + wave * 32 * kRowBytes;
     auto issue_q = [&](const Geo& of) {
@@ -432,21 +445,28 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
     bool more = false;       // there is a next item
     int drawn = 0;
     auto request_item = [&]() {
-        const lds_byte* const slot = (lds_byte*)lds_sched + 4 * slot_of(par);
-        const int unit = __builtin_amdgcn_readfirstlane(*(const __attribute__((address_space(3))) int*)slot);
-        more = unit >= 0;
-        if (!more) return;
-        if (wave == 0) drawn = count_up(share);
-        const u32x4 lo = *(const __attribute__((address_space(3))) u32x4*)(slot + 32);
-        const u32x2 hi = *(const __attribute__((address_space(3))) u32x2*)(slot + 48);
-        WorkItem w;
-        w.q0 = __builtin_amdgcn_readfirstlane(lo[0]);
-        w.len_q = __builtin_amdgcn_readfirstlane(lo[1]);
-        w.k0 = __builtin_amdgcn_readfirstlane(lo[2]);
-        w.len_k = __builtin_amdgcn_readfirstlane(lo[3]);
-        w.qtile = __builtin_amdgcn_readfirstlane(hi[0]);
-        w.slot = __builtin_amdgcn_readfirstlane(hi[1]);
-        next = list_geometry(unit, w);
+        if constexpr (kList) {
+            const lds_byte* const slot = (lds_byte*)lds_sched + 4 * slot_of(par);
+            const int unit = __builtin_amdgcn_readfirstlane(*(const __attribute__((address_space(3))) int*)slot);
+            more = unit >= 0;
+            if (!more) return;
+            if (wave == 0) drawn = count_up(share);
+            const u32x4 lo = *(const __attribute__((address_space(3))) u32x4*)(slot + 32);
+            const u32x2 hi = *(const __attribute__((address_space(3))) u32x2*)(slot + 48);
+            WorkItem w;
+            w.q0 = __builtin_amdgcn_readfirstlane(lo[0]);
+            w.len_q = __builtin_amdgcn_readfirstlane(lo[1]);
+            w.k0 = __builtin_amdgcn_readfirstlane(lo[2]);
+            w.len_k = __builtin_amdgcn_readfirstlane(lo[3]);
+            w.qtile = __builtin_amdgcn_readfirstlane(hi[0]);
+            w.slot = __builtin_amdgcn_readfirstlane(hi[1]);
+            next = list_geometry(unit, w);
+        } else {
+            const int unit = round0 + n_slots < per_xcd ? dense_unit(round0 + n_slots) : -1;
+            more = unit >= 0;
+            if (!more) return;
+            next = dense_geometry(unit);
+        }
         const int n = tiles_of(next);
         const unsigned char* const kb = uniform(kv_base(p.k, next));
         if (n > 0) issue_rows(kb, false, ldk_off0, 0, lds_k0, next.sk);
@@ -704,12 +724,12 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
 
     // ---- prologue: K(0), K(1), and finite data in the V stage that iteration 0 reads with P = 0
     const bool may_stop = kSweep && p.stop != nullptr;
-    if constexpr (kList) {
+    if constexpr (kAhead) {
         if (!requested) {
             issue_q(g);
             issue_k(0, lds_k0);
             issue_k(1, lds_k1);
-            if (wave == 0) take_next(count_up(share), par);
+            if (kList && wave == 0) take_next(count_up(share), par);
             end_of_iteration();
         }
         const u32x4 z = {0u, 0u, 0u, 0u};
@@ -742,9 +762,10 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
         alpha = 1.f;
     }
     asm volatile("" : "+v"(s_a[0]), "+v"(s_a[1]), "+v"(m_run), "+v"(m_use), "+v"(alpha));
-    if constexpr (kList) {
+    if constexpr (kAhead) {
         __builtin_amdgcn_s_waitcnt(0xC07F);                       // lgkmcnt 0: the zeros are in LDS
-        if (n_tiles == 0) __builtin_amdgcn_s_waitcnt(0x0F70);     // and the next WorkItem, with no tile step in between
+        // and, in a list, the next WorkItem, if no tile step comes in between; in a dense call the running state
+        if (!kList || n_tiles == 0) __builtin_amdgcn_s_waitcnt(0x0F70);
         asm volatile("" ::: "memory");
     }
     __builtin_amdgcn_s_barrier();     // K stage 0 may be overwritten from here on
@@ -822,7 +843,7 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
         end_of_iteration();
     }
 
-    if constexpr (kList) request_item();
+    if constexpr (kAhead) request_item();
 
     // ---- epilogue
     if constexpr (kSweep) {   // an item stopped short keeps its fp32 state; one that is through writes the result
@@ -878,7 +899,7 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
         if (!stopped) atomicSub(p.pending, 1);
     }
     if (kSweep && stopped) return;  // a stop request: this workgroup takes no further item
-    if constexpr (kList) {
+    if constexpr (kAhead) {
         if (!more) return;
         requested = true;
         // This wavefront's requests for the next item have landed: only younger stores may be outstanding.  A wavefront
@@ -886,7 +907,7 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
         if (rw0 < sq) __builtin_amdgcn_s_waitcnt(0x0F78);   // vmcnt 8
         else __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt 0
         par ^= 1;
-        if (wave == 0) take_next(drawn, par);
+        if (kList && wave == 0) take_next(drawn, par);
         asm volatile("" ::: "memory");
     }
     __builtin_amdgcn_s_barrier();   // every wavefront is done with the LDS stages before the next item's loads
