@@ -598,7 +598,7 @@ def bench_decode(args, torch, np, pec, synth, dev):
                                % n_splits},
         "ms_per_step_stats": step_stats(ev_list),
         "roofline": {"bound": "hbm", "achieved": round(gbs, 1), "peak": 8000.0, "unit": "GB/s",
-                     "frac": round(gbs / 8000.0, 4), "traffic": None, "kernel": "pec::decode_kernel + pec::combine_splits_kernel"},
+                     "frac": round(gbs / 8000.0, 4), "traffic": None, "kernel": "pec::fwd_split_kernel + pec::combine_splits_kernel"},
     }
     probe = hbm_read_probe(torch, pec, dev)
     result["hbm_read_probe"] = probe

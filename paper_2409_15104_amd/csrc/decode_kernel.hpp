@@ -9,6 +9,9 @@
 // transposed-score MFMA scheme as the prefill kernels (columns >= g carry zeros): the matrix
 // pipe is mostly idle and does not matter here.
 //
+// Used where a workgroup per key range and KV head (fwd_split_kernel.hpp) would not be resident all at once, or would have
+// fewer tiles than wavefronts: see decode_on_split_kernel() on the host for where the line lies.
+//
 // Each wavefront writes a normalised partial O and its LSE for its key range; the ranges are
 // merged by combine_splits_kernel.
 #pragma once
