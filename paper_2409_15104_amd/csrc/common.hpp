@@ -130,6 +130,27 @@ struct WorkOrder {
     }
 };
 
+// One tile-load instruction: 16 bytes per lane from sbase + voff to LDS, lane i at lds_addr + 16 i (M0 holds the address,
+// and needs one wait state before the load).
+// A load may read its scalar base five wait states after a vector instruction (v_readlane, v_readfirstlane) wrote it at the
+// earliest, and the compiler does not look inside asm.  In the tile loops (IN_LOOP) the base is the sum that a scalar add
+// has just made.  Everywhere else it may have come out of a spill or a readfirstlane the instruction before: s_mov_b64 is
+// interlocked and leaves it written by a scalar instruction.  (In the loops as well it costs 0.3 % of long calls and 1.2 %
+// of a 512 x 2048 one; tests/test_sgpr_wait_states.py looks every load of the built library over.)
+template <bool IN_LOOP>
+__device__ __forceinline__ void dma16(const unsigned char* sbase, uint32_t voff, uint32_t lds_addr) {
+    if constexpr (IN_LOOP)
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0"
+                     :
+                     : "s"(sbase), "v"(voff), "s"(lds_addr)
+                     : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %2\n\ts_mov_b64 %0, %0\n\tglobal_load_lds_dwordx4 %1, %0"
+                     : "+s"(sbase)
+                     : "v"(voff), "s"(lds_addr)
+                     : "memory", "m0");
+}
+
 __device__ __forceinline__ uint32_t k_lds_off(int key, int chunk16) {
     return (uint32_t)(key * kRowBytes + ((chunk16 ^ (key & 15)) << 4));
 }

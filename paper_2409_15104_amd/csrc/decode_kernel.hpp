@@ -83,12 +83,6 @@ __global__ __launch_bounds__(kDecWaves * 64) void decode_kernel(const DecodePara
     const unsigned char* kbase = p.k + (key_begin * p.n_kv_heads + kvh) * (int64_t)(kHeadDim * 2);
     const unsigned char* vbase = p.v + (key_begin * p.n_kv_heads + kvh) * (int64_t)(kHeadDim * 2);
     const int ld_row = lane >> 4, ld_pos = lane & 15;
-    auto dma16 = [](const unsigned char* sbase, uint32_t voff, uint32_t lds_addr) {
-        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                     :
-                     : "v"(voff), "s"(sbase), "s"(lds_addr)
-                     : "memory", "m0");
-    };
     auto issue_half = [&](const unsigned char* base, bool is_v, int tile, unsigned char* stage) {
         if (tile >= n_tiles) return;
         const int key0 = tile * kDecTile;
@@ -101,7 +95,7 @@ __global__ __launch_bounds__(kDecWaves * 64) void decode_kernel(const DecodePara
             const uint32_t row_off = (uint32_t)min(key, last) * kv_stride_b;
             const uint32_t col = is_v ? (uint32_t)((((ld_pos >> 2) ^ (key & 3)) << 2) | (ld_pos & 3)) * 16u
                                       : (uint32_t)(ld_pos ^ (key & 15)) * 16u;
-            dma16(tb, row_off + col, l0 + i * 1024);
+            dma16<false>(tb, row_off + col, l0 + i * 1024);
         }
     };
     auto issue_k = [&](int tile) { issue_half(kbase, false, tile, lds_k[wave][tile % kDecKStages]); };

@@ -95,10 +95,11 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
     const uint32_t lds_stop = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds_all + 4 * kTileBytes;
     auto request_stop_word = [&]() {   // lands with the tile loads; visible to everyone after the next barrier
         if (wave == 0) {
+            const int32_t* word = p.stop;
             uint32_t zero;
-            asm volatile("v_mov_b32 %0, 0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1 sc0 sc1"
-                         : "=&v"(zero)
-                         : "s"(p.stop), "s"(lds_stop)
+            asm volatile("v_mov_b32 %0, 0\n\ts_mov_b32 m0, %2\n\ts_mov_b64 %1, %1\n\tglobal_load_lds_dword %0, %1 sc0 sc1"
+                         : "=&v"(zero), "+s"(word)     // (s_mov_b64: as in dma16)
+                         : "s"(lds_stop)
                          : "memory", "m0");
         }
     };
@@ -152,12 +153,12 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
         const int got = settle(v);
         const int ln = lane_id();
         if (ln == 0) lds_sched[slot_of(par)] = got;
-        const unsigned char* const w = uniform(p.work + max(got, 0) % order.per_kvh / units);
+        const unsigned char* w = uniform(p.work + max(got, 0) % order.per_kvh / units);
         const uint32_t lds_item = __builtin_amdgcn_readfirstlane(lds_stop + 256 + 4 * (slot_of(par) + 8));
         if (got >= 0 && ln < 8) {
-            asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
-                         :
-                         : "v"(ln * 4), "s"(w), "s"(lds_item)
+            asm volatile("s_mov_b32 m0, %2\n\ts_mov_b64 %0, %0\n\tglobal_load_lds_dword %1, %0"
+                         : "+s"(w)                     // (s_mov_b64: as in dma16)
+                         : "v"(ln * 4), "s"(lds_item)
                          : "memory", "m0");
         }
         __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt 0: the unit is in LDS before the next barrier
@@ -388,19 +389,13 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
         ldv_off0 = (uint32_t)key * kv_stride_b + (uint32_t)((((ld_pos >> 2) ^ (key & 3)) << 2) | (ld_pos & 3)) * 16u;
     }
     const uint32_t block_stride_b = 4u * NWAVES * kv_stride_b;
-    auto dma16 = [](const unsigned char* sbase, uint32_t voff, uint32_t lds_addr) {
-        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                     :
-                     : "v"(voff), "s"(sbase), "s"(lds_addr)
-                     : "memory", "m0");
-    };
-    auto issue_rows = [&](const unsigned char* base, bool is_v, uint32_t full_off0, int tile, unsigned char* stage, int sk) {
+    auto issue_rows = [&](auto in_loop, const unsigned char* base, bool is_v, uint32_t full_off0, int tile, unsigned char* stage, int sk) {
         const int key0 = tile * kBN;
         const unsigned char* tb = base + (int64_t)key0 * kv_stride_b;
         const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)stage + wave * 1024;
         if (key0 + kBN <= sk) {
 #pragma unroll
-            for (int it = 0; it < 2; ++it) dma16(tb + it * block_stride_b, full_off0, lds0 + it * NWAVES * 1024);
+            for (int it = 0; it < 2; ++it) dma16<decltype(in_loop)::value>(tb + it * block_stride_b, full_off0, lds0 + it * NWAVES * 1024);
         } else {   // rows past the end re-read the last valid row: finite data, weight zero
             // (at most once per work item: everything is rebuilt from the lane id here, so that the
             // tile loop carries no register for this path)
@@ -413,15 +408,15 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
                 const int key = 4 * (it * NWAVES + wave) + r_row;
                 const uint32_t col = is_v ? (uint32_t)((((r_pos >> 2) ^ (key & 3)) << 2) | (r_pos & 3)) * 16u
                                           : (uint32_t)(r_pos ^ (key & 15)) * 16u;
-                dma16(tb, (uint32_t)min(key, last) * kv_stride_b + col, lds0 + it * NWAVES * 1024);
+                dma16<false>(tb, (uint32_t)min(key, last) * kv_stride_b + col, lds0 + it * NWAVES * 1024);
             }
         }
     };
-    auto issue_k = [&](int tile, unsigned char* stage) {
-        if (tile < n_tiles) issue_rows(kbase, false, ldk_off0, tile, stage, sk);
+    auto issue_k = [&](auto in_loop, int tile, unsigned char* stage) {
+        if (tile < n_tiles) issue_rows(in_loop, kbase, false, ldk_off0, tile, stage, sk);
     };
-    auto issue_v = [&](int tile, unsigned char* stage) {
-        if (tile < n_tiles) issue_rows(vbase, true, ldv_off0, tile, stage, sk);
+    auto issue_v = [&](auto in_loop, int tile, unsigned char* stage) {
+        if (tile < n_tiles) issue_rows(in_loop, vbase, true, ldv_off0, tile, stage, sk);
     };
     // All calls but the resumable sweep take Q through LDS, a private 8 KiB per wavefront (registers that are filled while the last tile is
     // worked on cost 140 spill instructions there); rows past the end re-read the last valid one, nothing of theirs is stored
@@ -434,7 +429,7 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int row = 4 * i + (ln >> 4);
-            dma16(qb, (uint32_t)min(row, last) * (uint32_t)(of.q_stride * 2) + (uint32_t)((ln & 15) ^ (row & 15)) * 16u, l0 + i * 1024);
+            dma16<false>(qb, (uint32_t)min(row, last) * (uint32_t)(of.q_stride * 2) + (uint32_t)((ln & 15) ^ (row & 15)) * 16u, l0 + i * 1024);
         }
     };
     // When the item's tiles are done, and both K stages free, everything the next item starts with is requested -- its Q,
@@ -469,8 +464,8 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
         }
         const int n = tiles_of(next);
         const unsigned char* const kb = uniform(kv_base(p.k, next));
-        if (n > 0) issue_rows(kb, false, ldk_off0, 0, lds_k0, next.sk);
-        if (n > 1) issue_rows(kb, false, ldk_off0, 1, lds_k1, next.sk);
+        if (n > 0) issue_rows(std::false_type{}, kb, false, ldk_off0, 0, lds_k0, next.sk);
+        if (n > 1) issue_rows(std::false_type{}, kb, false, ldk_off0, 1, lds_k1, next.sk);
         issue_q(next);
     };
 
@@ -617,8 +612,8 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
         unsigned char* v_wr = PAR ? lds_v1 : lds_v0;
         const unsigned char* k_rd = PAR ? lds_k0 : lds_k1;
         const unsigned char* v_rd = PAR ? lds_v0 : lds_v1;
-        issue_k(j + 2, k_wr);
-        issue_v(j, v_wr);
+        issue_k(std::true_type{}, j + 2, k_wr);
+        issue_v(std::true_type{}, j, v_wr);
         // An iteration whose next tile needs no mask skips the row maximum altogether: the weights of
         // tile j are taken against the reference as it stands, and only a row sum above kSumLimit
         // (some score far ahead of the reference) sends the wavefront through row_max() and a second
@@ -727,8 +722,8 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
     if constexpr (kAhead) {
         if (!requested) {
             issue_q(g);
-            issue_k(0, lds_k0);
-            issue_k(1, lds_k1);
+            issue_k(std::false_type{}, 0, lds_k0);
+            issue_k(std::false_type{}, 1, lds_k1);
             if (kList && wave == 0) take_next(count_up(share), par);
             end_of_iteration();
         }
@@ -739,9 +734,9 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
 #pragma unroll
         for (int t = 0; t < 8; ++t) qf[t] = *reinterpret_cast<const bf16x8*>(lds_q + k_off[t]);
     } else {
-        issue_k(0, lds_k0);
-        issue_k(1, lds_k1);
-        issue_v(0, lds_v1);
+        issue_k(std::false_type{}, 0, lds_k0);
+        issue_k(std::false_type{}, 1, lds_k1);
+        issue_v(std::false_type{}, 0, lds_v1);
         if (may_stop && !first_item) request_stop_word();
         end_of_iteration();
         if (may_stop && !first_item && read_stop_word() != 0) return;   // nothing of this item has been touched
@@ -838,8 +833,8 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
         ++j;
     }
     for (; j < n_tiles; ++j) {   // keep the workgroup's load / barrier cadence
-        issue_k(j + 2, (j & 1) ? lds_k1 : lds_k0);
-        issue_v(j, (j & 1) ? lds_v1 : lds_v0);
+        issue_k(std::true_type{}, j + 2, (j & 1) ? lds_k1 : lds_k0);
+        issue_v(std::true_type{}, j, (j & 1) ? lds_v1 : lds_v0);
         end_of_iteration();
     }
 

@@ -27,6 +27,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace pec {
@@ -177,20 +179,14 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void fwd_split_kernel(const Fw
     const int ld_row = lane >> 4, ld_pos = lane & 15;
     const uint32_t ldk_off = (uint32_t)ld_row * kv_stride_b + (uint32_t)(ld_pos ^ ld_row) * 16u;
     const uint32_t ldv_off = (uint32_t)ld_row * kv_stride_b + (uint32_t)((((ld_pos >> 2) ^ ld_row) << 2) | (ld_pos & 3)) * 16u;
-    auto dma16 = [](const unsigned char* sbase, uint32_t voff, uint32_t lds_addr) {
-        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                     :
-                     : "v"(voff), "s"(sbase), "s"(lds_addr)
-                     : "memory", "m0");
-    };
-    auto issue = [&](const unsigned char* base, bool is_v, int tile, unsigned char* stage) {
+    auto issue = [&](auto in_loop, const unsigned char* base, bool is_v, int tile, unsigned char* stage) {
         const int key0 = tile * kSplitTile;
         const unsigned char* tb = base + (int64_t)key0 * kv_stride_b;
         const uint32_t l0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)stage;
         if (key0 + kSplitTile <= sk) {
 #pragma unroll
             for (int i = 0; i < LOADS; ++i)
-                dma16(tb + (uint32_t)(4 * i) * kv_stride_b, is_v ? ldv_off : ldk_off ^ ((i & 3) << 6), l0 + i * 1024);
+                dma16<decltype(in_loop)::value>(tb + (uint32_t)(4 * i) * kv_stride_b, is_v ? ldv_off : ldk_off ^ ((i & 3) << 6), l0 + i * 1024);
         } else {   // rows past the end re-read the last valid one: finite data, weight zero
             int ln;     // rebuilt from the lane id: the loop carries no register for this path
             asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
@@ -201,7 +197,7 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void fwd_split_kernel(const Fw
                 const int key = 4 * i + r_row;
                 const uint32_t col = is_v ? (uint32_t)((((r_pos >> 2) ^ (key & 3)) << 2) | (r_pos & 3)) * 16u
                                           : (uint32_t)(r_pos ^ (key & 15)) * 16u;
-                dma16(tb, (uint32_t)min(key, last) * kv_stride_b + col, l0 + i * 1024);
+                dma16<false>(tb, (uint32_t)min(key, last) * kv_stride_b + col, l0 + i * 1024);
             }
         }
     };
@@ -222,14 +218,14 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void fwd_split_kernel(const Fw
 #pragma unroll
         for (int i = 0; i < BM / 4 / KS; ++i) {
             const int blk = wave + i * KS, row = 4 * blk + ld_row;
-            dma16(qb, (uint32_t)min(row, sq - 1 - row0) * (uint32_t)(q_stride * 2) + (uint32_t)(ld_pos ^ (row & 15)) * 16u, l0 + blk * 1024);
+            dma16<false>(qb, (uint32_t)min(row, sq - 1 - row0) * (uint32_t)(q_stride * 2) + (uint32_t)(ld_pos ^ (row & 15)) * 16u, l0 + blk * 1024);
         }
     }
     unsigned char* const kst = lds + wave * 2 * kSplitTileBytes;
     unsigned char* const vst = kst + kSplitTileBytes;
     if (wave < n_tiles) {
-        issue(kbase, false, wave, kst);
-        issue(vbase, true, wave, vst);
+        issue(std::false_type{}, kbase, false, wave, kst);
+        issue(std::false_type{}, vbase, true, wave, vst);
     }
     static_assert(LOADS == 8, "the vmcnt immediates below assume eight loads per matrix and tile");
     if constexpr (kQLds) {
@@ -257,7 +253,7 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void fwd_split_kernel(const Fw
             }
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the K stage has been read
-        if (more) issue(kbase, false, tile + KS, kst);
+        if (more) issue(std::true_type{}, kbase, false, tile + KS, kst);
 
         // mask, softmax reference (kept lazily: it moves only for a score more than 2^8 ahead of it), weights
         const bool need_mask = key0 + kSplitTile > sk || (causal && key0 + kSplitTile - 1 > row0 + delta);
@@ -323,7 +319,7 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void fwd_split_kernel(const Fw
                     o[nt][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pp[nt][k2], o[nt][dt], 0, 0, 0);
             }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the V stage has been read
-        if (more) issue(vbase, true, tile + KS, vst);
+        if (more) issue(std::true_type{}, vbase, true, tile + KS, vst);
     }
 
     // ---- merge of the eight partial results of every row, 32 rows at a time.  O goes to LDS in 16-byte chunks of 4
