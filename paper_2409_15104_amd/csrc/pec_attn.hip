@@ -260,6 +260,24 @@ int64_t ring_visit(int64_t s_q, int64_t q_off, int64_t s_kv, int64_t chunk, int 
     return visited;
 }
 
+// Keys per range when sk keys are cut into n_splits ranges of whole tiles.
+int64_t range_keys(int64_t sk, int32_t n_splits, int tile) {
+    return std::max<int64_t>(((sk + n_splits - 1) / n_splits + tile - 1) / tile * tile, tile);
+}
+
+// Whether a decode step with groups of up to 32 heads runs on fwd_split_kernel (a workgroup per range and KV head, its
+// wavefronts sharing the keys) or on decode_kernel (a wavefront per range and KV head).  Microseconds per step, with the
+// merge, fresh caches, 8 KV heads, (keys per range) in decode_kernel / fwd_split_kernel:
+//     4,096 keys     16 ranges 18.2 / 11.4      64 ranges (64) 11.6 / 15.1
+//     32,768 keys    32 ranges 60.9 / 31.8     128 ranges (256) 33.6 / 41.9
+//     524,288 keys   32 ranges 766 / 356       128 ranges 384 / 372
+// The workgroup kernel wins while all of its workgroups run at once and every wavefront has a tile; a second round of
+// workgroups costs it the latency that decode_kernel's deeper rings hide.
+bool decode_on_split_kernel(const pec_shape_t* shape, int64_t sk, int32_t n_splits) {
+    return shape->n_q_heads / shape->n_kv_heads <= 32 && (int64_t)n_splits * shape->n_kv_heads <= compute_units() &&
+           range_keys(sk, n_splits, 32) > 64;
+}
+
 int grid_for(int64_t n_groups) { return (int)std::min<int64_t>((n_groups + 255) / 256, 256 * 32); }
 
 }  // namespace
@@ -486,11 +504,13 @@ int pec_sp_prefill_step(const pec_shape_t* shape, const void* q, const void* k, 
 int32_t pec_decode_default_splits(const pec_shape_t* shape, int64_t sk) {
     if (!shape || shape->n_kv_heads <= 0 || sk <= 0) return 1;
     const int g = shape->n_q_heads / shape->n_kv_heads;
-    const int64_t per_cu = std::max<int64_t>(1, compute_units() / shape->n_kv_heads);
-    if (g <= 32 && 4 * per_cu * shape->n_kv_heads >= 3 * compute_units())   // fwd_split_kernel: a workgroup per compute unit,
-        return (int32_t)std::max<int64_t>(1, std::min<int64_t>(per_cu, sk / 256));   // a tile of 32 keys per wavefront
-    if (g <= 32) {   // so many KV heads that this would leave compute units idle: one workgroup (four KV heads of one range)
-                     // per compute unit, at least 8 tiles of 32 keys each
+    const int64_t per_cu = compute_units() / shape->n_kv_heads;   // ranges if every compute unit takes one KV head of one
+    const int64_t n = std::max<int64_t>(1, std::min<int64_t>(per_cu, sk / 256));   // ... and 256 keys at least: a tile of
+                                                                                  // 32 for each of eight wavefronts
+    // fwd_split_kernel, unless there are so many KV heads that it would leave a quarter of the compute units idle, or
+    // would not be the kernel that runs n ranges (more KV heads than compute units)
+    if (4 * per_cu * shape->n_kv_heads >= 3 * compute_units() && decode_on_split_kernel(shape, sk, (int32_t)n)) return (int32_t)n;
+    if (g <= 32) {   // decode_kernel: one workgroup (four KV heads of one range) per compute unit, at least 8 tiles of 32 keys
         const int64_t head_groups = (shape->n_kv_heads + kDecWaves - 1) / kDecWaves;
         return (int32_t)std::max<int64_t>(1, std::min<int64_t>(compute_units() / head_groups, sk / 256));
     }
@@ -525,24 +545,6 @@ int static_scratch(void** out) {
     }
     *out = ptr[dev];
     return PEC_OK;
-}
-
-// Keys per range when sk keys are cut into n_splits ranges of whole tiles.
-int64_t range_keys(int64_t sk, int32_t n_splits, int tile) {
-    return std::max<int64_t>(((sk + n_splits - 1) / n_splits + tile - 1) / tile * tile, tile);
-}
-
-// Whether a decode step with groups of up to 32 heads runs on fwd_split_kernel (a workgroup per range and KV head, its
-// wavefronts sharing the keys) or on decode_kernel (a wavefront per range and KV head).  Microseconds per step, with the
-// merge, fresh caches, 8 KV heads, (keys per range) in decode_kernel / fwd_split_kernel:
-//     4,096 keys     16 ranges 18.2 / 11.4      64 ranges (64) 11.6 / 15.1
-//     32,768 keys    32 ranges 60.9 / 31.8     128 ranges (256) 33.6 / 41.9
-//     524,288 keys   32 ranges 766 / 356       128 ranges 384 / 372
-// The workgroup kernel wins while all of its workgroups run at once and every wavefront has a tile; a second round of
-// workgroups costs it the latency that decode_kernel's deeper rings hide.
-bool decode_on_split_kernel(const pec_shape_t* shape, int64_t sk, int32_t n_splits) {
-    return shape->n_q_heads / shape->n_kv_heads <= 32 && (int64_t)n_splits * shape->n_kv_heads <= compute_units() &&
-           range_keys(sk, n_splits, 32) > 64;
 }
 
 // Common body of the two decode entry points; `workspace` holds pec_decode_workspace_bytes(shape, n_splits) bytes.

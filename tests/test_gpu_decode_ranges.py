@@ -20,7 +20,9 @@ pytestmark = pytest.mark.gpu
     (500, 6, 3, 4),                        # last range empty
     (8192, 32, 8, 32), (8192, 32, 8, 33),  # as many workgroups as compute units, and one round more
     (300, 32, 1, 0), (300, 33, 1, 0),      # widest group of this kernel, next one
-    (700, 100, 100, 0),                    # too many KV heads for a workgroup each per compute unit
+    (700, 100, 100, 0),                    # 200 workgroups of one KV head
+    (1500, 90, 90, 0), (1100, 150, 150, 0),    # a workgroup per KV head and range would leave compute units idle: a wavefront each
+    (1100, 300, 300, 0), (600, 600, 300, 1),   # more KV heads than compute units
     (40000, 8, 1, 1100),                   # more ranges than the merge has threads, many of them empty
 ])
 def test_decode_ranges_match_oracle(sk, hq, hkv, n_splits):

@@ -111,3 +111,14 @@ def test_binding_refuses_cpu_tensors(lib):
     q = torch.zeros(4, 2, 128, dtype=torch.bfloat16)
     with pytest.raises(ValueError):
         binding.pec_attn_chunk(q, q, q, 0, 0)
+
+
+@pytest.mark.parametrize("hkv,sk,n", [
+    (8, 524288, 32), (8, 4096, 16), (1, 100000, 256), (256, 100000, 1),   # a workgroup per compute unit, 256 keys at least
+    (90, 100000, 11), (150, 100000, 6),      # a workgroup each would leave a quarter of 256 compute units idle
+    (257, 100000, 3), (300, 100000, 3),      # more KV heads than compute units: four of a range in a workgroup
+    (300, 500, 1), (8, 64, 1), (8, 0, 1),
+])
+def test_default_ranges_of_a_decode_step(lib, hkv, sk, n):
+    shape = binding.PecShape(hkv, hkv, 128, binding.PEC_F32, 0.0, 0)
+    assert lib.pec_decode_default_splits(ctypes.byref(shape), sk) == n
