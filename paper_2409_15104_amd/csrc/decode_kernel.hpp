@@ -19,6 +19,7 @@
 #include <stdint.h>
 
 #include "common.hpp"
+#include "kernel_choice.hpp"
 
 namespace pec {
 
@@ -37,7 +38,6 @@ struct DecodeParams {
 
 constexpr int kDecTile = 32;                          // keys per tile
 constexpr int kDecTileBytes = kDecTile * kRowBytes;   // 8 KiB for K, 8 KiB for V
-constexpr int kDecWaves = 4;
 constexpr int kDecKStages = 2, kDecVStages = 3;      // ring depths: K(j) is requested two tiles ahead, V(j) three
 
 __global__ __launch_bounds__(kDecWaves * 64) void decode_kernel(const DecodeParams p) {

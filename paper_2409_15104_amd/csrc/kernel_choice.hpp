@@ -1,0 +1,133 @@
+// Which kernel a call runs on and how its work is cut, as functions of the call's sizes and the number of compute units.
+// Plain C++ without HIP, so that a test can ask what a call of given sizes runs on.
+#pragma once
+#include <stdint.h>
+
+#include <algorithm>
+#include <cmath>
+
+namespace pec {
+
+constexpr int kBM = 256;       // query rows per workgroup of fwd_il_kernel and fwd_simple_kernel
+constexpr int kDecWaves = 4;   // KV heads per workgroup of decode_kernel
+
+// The 256 rows of a fwd_il_kernel work item: as many heads of a KV group as divide it, up to 8, and 256 / heads query
+// positions of each.  All of them read the same keys, so the choice changes no traffic; fewer positions waste less at
+// the causal diagonal (a workgroup walks to the last key of its last row) and in the last, partly filled row tile.  256
+// prompts of the benchmark's length mix with 32 q / 8 kv heads take 1.56 M tile steps with one head per item, 1.48 M
+// with two, 1.44 M with four (1.40 M would be no waste).
+// Measured (one head per item -> up to eight): causal ring step of 4096 x 4096, 32 q / 8 kv heads, one of four in
+// 878 -> 859 us; the 256 prompts with a decode step 12.43 -> 12.17 ms: the chip is at its power limit, and wavefronts
+// that wait at the diagonal cost time but little power.
+inline int log_heads_per_item(int n_q_heads, int n_kv_heads) {
+    const int g = n_q_heads / n_kv_heads;
+    return g % 8 == 0 ? 3 : g % 4 == 0 ? 2 : g % 2 == 0 ? 1 : 0;
+}
+
+// Query rows per workgroup of a launch: 256 (fwd_il_kernel, one workgroup per 64-key tile step) or, where that would
+// leave compute units idle, 64 or 32 (fwd_split_kernel<2 | 1>, 256 keys per step).  Estimated time of a choice =
+// base x rounds + step time x (steps of the longest workgroup, or of an average one times the rounds if that is more),
+// rounds = workgroups / compute units rounded up; the smallest wins.  Measured on 256 compute units (microseconds; step
+// time with few / with all of them busy, memory and power being shared):
+//     256 rows: 11.5 + 1.13 / 1.55 per 64 keys    64 rows: 8 + 1.68 / 2.15 per 256 keys    32 rows: 6 + 1.17 / 1.45
+// e.g. 8 q heads, 512 rows x 2048 keys: 47.5 / 22.6 / 16.5 us with 256 / 64 / 32 rows; 2048 x 8192: 158 / 80 / 87 us;
+// 32 q heads, 1024 x 8192: 164 / 144 / 178 us; 2048 x 8192: 212 / 264 / 323 us.
+struct RowChoice {
+    int rows, step_keys;
+    double base, t_few, t_all;
+    double estimate(double cu, double groups, double longest_keys, double average_keys) const {
+        const double rounds = std::ceil(groups / cu);
+        const double longest = std::ceil(longest_keys / step_keys), average = std::ceil(average_keys / step_keys);
+        const double n = std::max(longest, rounds > 1 ? rounds * average : 0.0);
+        return base * rounds + n * (t_few + (t_all - t_few) * std::min(1.0, groups / cu));
+    }
+};
+constexpr RowChoice kRowChoices[] = {{256, 64, 11.5, 1.13, 1.55}, {64, 256, 8.0, 1.68, 2.15}, {32, 256, 6.0, 1.17, 1.45}};
+
+inline int rows_of_dense_call(int cu, int n_q_heads, int n_kv_heads, int64_t sq, int64_t sk, int64_t delta, bool causal) {
+    auto groups_of = [&](int rows) {   // workgroups (of the persistent kernel: work items)
+        const int l = rows == kBM ? log_heads_per_item(n_q_heads, n_kv_heads) : 0, positions = rows >> l;
+        return (double)((sq + positions - 1) / positions) * (n_q_heads >> l);
+    };
+    if (groups_of(kBM) >= cu) return kBM;   // an item for every compute unit
+    auto keys = [&](int64_t last_row) {   // that a query tile ending with this row sees
+        return (double)(causal ? std::max<int64_t>(0, std::min<int64_t>(sk, last_row + delta + 1)) : sk);
+    };
+    int best = kBM;
+    double best_t = 0;
+    for (const RowChoice& c : kRowChoices) {
+        const double longest = keys(sq - 1), shortest = keys(std::min<int64_t>(sq, c.rows) - 1);
+        const double t = c.estimate(cu, groups_of(c.rows), longest, 0.5 * (longest + shortest));
+        if (c.rows == kBM || t < best_t) {
+            best = c.rows;
+            best_t = t;
+        }
+    }
+    return best;
+}
+
+// The same for a packed or colocated batch, of which the host knows only totals: estimated for `batch` sequences of
+// equal length, the longest as long as the caller's hint.  Keys beyond one per query are taken to be long caches, cut
+// into ranges of range_len keys per KV head.
+inline int rows_of_list_call(int cu, int n_q_heads, int n_kv_heads, int64_t batch, int64_t total_q, int64_t total_k,
+                             int64_t longest, bool causal, int range_len) {
+    const double len = (double)total_q / batch;
+    // prompt lengths are spread wide (the log-normal mix of the tests has E[L^2] / E[L]^2 of about 3): a row sees 1.5
+    // times the average length, not half of it, and the longest prompt is several times the average
+    const double seen = std::min((double)total_q, 3 * len);
+    if (longest <= 0) longest = (int64_t)std::min((double)total_q, 4 * len);
+    const double range_units = range_len > 0 ? std::max(0.0, (double)(total_k - total_q) / range_len) * n_kv_heads : 0.0;
+    auto groups_of = [&](int rows) {
+        const int l = rows == kBM ? log_heads_per_item(n_q_heads, n_kv_heads) : 0;
+        return batch * std::ceil(len / (rows >> l)) * (n_q_heads >> l) + range_units;
+    };
+    if (groups_of(kBM) >= cu) return kBM;
+    int best = kBM;
+    double best_t = 0;
+    for (const RowChoice& c : kRowChoices) {
+        if (range_units > 0 && n_q_heads / n_kv_heads > c.rows) continue;   // a range item's rows are the heads of a group
+        const double t = c.estimate(cu, groups_of(c.rows), std::max({(double)longest, len, range_units > 0 ? (double)range_len : 0.0}),
+                                    causal ? 0.5 * seen : seen);
+        if (c.rows == kBM || t < best_t) {
+            best = c.rows;
+            best_t = t;
+        }
+    }
+    return best;
+}
+
+// Keys per range when sk keys are cut into n_splits ranges of whole tiles.
+inline int64_t range_keys(int64_t sk, int64_t n_splits, int tile) {
+    return std::max<int64_t>(((sk + n_splits - 1) / n_splits + tile - 1) / tile * tile, tile);
+}
+
+// Whether a decode step with groups of up to 32 heads runs on fwd_split_kernel (a workgroup per range and KV head, its
+// wavefronts sharing the keys) or on decode_kernel (a wavefront per range and KV head).  Microseconds per step, with the
+// merge, fresh caches, 8 KV heads, (keys per range) in decode_kernel / fwd_split_kernel:
+//     4,096 keys     16 ranges 18.2 / 11.4      64 ranges (64) 11.6 / 15.1
+//     32,768 keys    32 ranges 60.9 / 31.8     128 ranges (256) 33.6 / 41.9
+//     524,288 keys   32 ranges 766 / 356       128 ranges 384 / 372
+// The workgroup kernel wins while all of its workgroups run at once and every wavefront has a tile; a second round of
+// workgroups costs it the latency that decode_kernel's deeper rings hide.
+inline bool decode_on_split_kernel(int cu, int n_q_heads, int n_kv_heads, int64_t sk, int64_t n_splits) {
+    return n_q_heads / n_kv_heads <= 32 && n_splits * n_kv_heads <= cu && range_keys(sk, n_splits, 32) > 64;
+}
+
+// Key ranges of a decode step whose caller leaves the number to the library.
+inline int64_t decode_default_ranges(int cu, int n_q_heads, int n_kv_heads, int64_t sk) {
+    const int g = n_q_heads / n_kv_heads;
+    const int64_t per_cu = cu / n_kv_heads;   // ranges if every compute unit takes one KV head of one
+    const int64_t n = std::max<int64_t>(1, std::min<int64_t>(per_cu, sk / 256));   // ... and 256 keys at least: a tile of
+                                                                                  // 32 for each of eight wavefronts
+    // fwd_split_kernel, unless there are so many KV heads that it would leave a quarter of the compute units idle, or
+    // would not be the kernel that runs n ranges (more KV heads than compute units)
+    if (4 * per_cu * n_kv_heads >= 3 * cu && decode_on_split_kernel(cu, n_q_heads, n_kv_heads, sk, n)) return n;
+    if (g <= 32) {   // decode_kernel: one workgroup (four KV heads of one range) per compute unit, at least 8 tiles of 32 keys
+        const int64_t head_groups = (n_kv_heads + kDecWaves - 1) / kDecWaves;
+        return std::max<int64_t>(1, std::min<int64_t>(cu / head_groups, sk / 256));
+    }
+    // wide groups run on the prefill kernel: one workgroup per compute unit, at least 16 tiles of 64 keys each
+    return std::max<int64_t>(1, std::min<int64_t>(per_cu, sk / 1024));
+}
+
+}  // namespace pec

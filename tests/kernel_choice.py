@@ -1,0 +1,61 @@
+"""The library's own choice of kernel (csrc/kernel_choice.hpp, plain C++) for a call of given sizes, so that a test can make
+sure that its cases run on the kernel that they are about."""
+import ctypes
+import functools
+import os
+import subprocess
+import tempfile
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2409_15104_amd", "csrc")
+COMPUTE_UNITS = 256
+COLOC_RANGE = 4096
+SOURCE = """
+#include "kernel_choice.hpp"
+extern "C" int dense(int cu, int hq, int hkv, int64_t sq, int64_t sk, int64_t delta, int causal) {
+    return pec::rows_of_dense_call(cu, hq, hkv, sq, sk, delta, causal);
+}
+extern "C" int list(int cu, int hq, int hkv, int64_t batch, int64_t tq, int64_t tk, int64_t longest, int causal, int range) {
+    return pec::rows_of_list_call(cu, hq, hkv, batch, tq, tk, longest, causal, range);
+}
+extern "C" int64_t ranges(int cu, int hq, int hkv, int64_t sk) { return pec::decode_default_ranges(cu, hq, hkv, sk); }
+extern "C" int split(int cu, int hq, int hkv, int64_t sk, int64_t n) { return pec::decode_on_split_kernel(cu, hq, hkv, sk, n); }
+"""
+
+
+@functools.lru_cache(maxsize=None)
+def _lib():
+    with tempfile.TemporaryDirectory() as d:
+        src, lib = os.path.join(d, "choice.cpp"), os.path.join(d, "choice.so")
+        with open(src, "w") as f:
+            f.write(SOURCE)
+        subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, "-o", lib, src], check=True)
+        L = ctypes.CDLL(lib)
+    i64 = ctypes.c_int64
+    L.dense.argtypes = [ctypes.c_int] * 3 + [i64] * 3 + [ctypes.c_int]
+    L.list.argtypes = [ctypes.c_int] * 3 + [i64] * 4 + [ctypes.c_int] * 2
+    L.ranges.argtypes, L.ranges.restype = [ctypes.c_int] * 3 + [i64], i64
+    L.split.argtypes = [ctypes.c_int] * 3 + [i64] * 2
+    return L
+
+
+def dense_rows(hq, hkv, sq, sk, q_off=0, kv_off=0, causal=True):
+    """Query rows per workgroup: 256 is fwd_il_kernel, 64 and 32 are fwd_split_kernel<2> and <1>."""
+    delta = max(-sq - 1, min(q_off - kv_off, sk))
+    return _lib().dense(COMPUTE_UNITS, hq, hkv, sq, sk, delta, int(causal))
+
+
+def packed_rows(hq, hkv, lengths, hint=None, causal=True):
+    total = int(sum(lengths))
+    return _lib().list(COMPUTE_UNITS, hq, hkv, len(lengths), total, total, min(hint or max(lengths), total), int(causal), 0)
+
+
+def mixed_rows(hq, hkv, len_q, len_k, causal=True):
+    return _lib().list(COMPUTE_UNITS, hq, hkv, len(len_q), int(sum(len_q)), int(sum(len_k)), 0, int(causal), COLOC_RANGE)
+
+
+def decode_kernel_of(hq, hkv, sk, n_splits):
+    """(key ranges, kernel) of a decode step; n_splits 0 is the library's choice."""
+    n = n_splits or _lib().ranges(COMPUTE_UNITS, hq, hkv, sk)
+    if _lib().split(COMPUTE_UNITS, hq, hkv, sk, n):
+        return n, "fwd_split_kernel"
+    return n, "decode_kernel" if hq // hkv <= 32 else "fwd_il_kernel"

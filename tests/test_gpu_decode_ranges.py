@@ -14,12 +14,12 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("sk,hq,hkv,n_splits", [
     (65, 8, 8, 1), (64, 8, 8, 1),          # just over and just at the range length that changes kernels
-    (255, 32, 8, 0), (257, 32, 8, 1),      # a tile per wavefront, the ninth tile with one key
+    (255, 32, 8, 0), (257, 32, 8, 1),      # a tile per wavefront, the last one key short; the ninth tile with one key
     (4097, 32, 8, 0), (1000, 64, 2, 7),    # last range short
     (9 * 128 + 1, 16, 4, 10),              # last range with one key
     (500, 6, 3, 4),                        # last range empty
     (8192, 32, 8, 32), (8192, 32, 8, 33),  # as many workgroups as compute units, and one round more
-    (300, 32, 1, 0), (300, 33, 1, 0),      # widest group of this kernel, next one
+    (300, 32, 1, 0), (300, 33, 1, 0),      # widest group of either kernel; the next one runs on the prefill kernel
     (700, 100, 100, 0),                    # 200 workgroups of one KV head
     (1500, 90, 90, 0), (1100, 150, 150, 0),    # a workgroup per KV head and range would leave compute units idle: a wavefront each
     (1100, 300, 300, 0), (600, 600, 300, 1),   # more KV heads than compute units

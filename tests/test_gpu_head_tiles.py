@@ -37,11 +37,15 @@ def test_items_of_several_heads_match_oracle(hq, hkv, sq, sk, q_off, causal):
     assert_close(o_acc, l_acc, o_ref, l_ref, "two segments")
 
 
-@pytest.mark.parametrize("hq,hkv", [(64, 8), (32, 8), (24, 2), (16, 8), (36, 6), (8, 8)])
-def test_mixed_batches_with_items_of_several_heads(hq, hkv):
-    """Prompts at the edges of 32, 64, 128 and 256 positions, a chunk behind a prefix, whole and cut caches."""
-    len_q = [32, 1, 33, 64, 0, 65, 127, 1, 128, 129, 255, 1, 256, 257, 31, 63, 5, 700, 40]
-    len_k = [32, 5000, 33, 64, 7, 65, 127, 4097, 128, 129, 255, 9, 256, 257, 31, 63, 300, 700, 1000]
+# prompts at the edges of 32, 64, 128 and 256 positions, a chunk behind a prefix, whole and cut caches
+LEN_Q = [32, 1, 33, 64, 0, 65, 127, 1, 128, 129, 255, 1, 256, 257, 31, 63, 5, 700, 40]
+LEN_K = [32, 5000, 33, 64, 7, 65, 127, 4097, 128, 129, 255, 9, 256, 257, 31, 63, 300, 700, 1000]
+
+
+@pytest.mark.parametrize("hq,hkv,times", [(64, 8, 1), (32, 8, 1), (24, 2, 2), (16, 8, 2), (36, 6, 1), (8, 8, 2)])
+def test_mixed_batches_with_items_of_several_heads(hq, hkv, times):
+    """The batch above, as often as it takes for an item per compute unit (tests/test_kernel_choice.py)."""
+    len_q, len_k = LEN_Q * times, LEN_K * times
     cq, ck = synth.cu_seqlens_of(len_q), synth.cu_seqlens_of(len_k)
     tq, tk = int(cq[-1]), int(ck[-1])
     q, _, _ = synth.qkv(7200 + hq, tq, 1, hq, hkv)

@@ -19,7 +19,8 @@ pytestmark = pytest.mark.gpu
 O_ATOL = 2e-2
 LSE_RTOL = 1e-3
 DEV = "cuda:0"
-# per-call kernel selection: the default pipelined kernel and the plain cross-check kernel
+# per-call kernel selection: the library's choice (at the sizes of most small cases here fwd_split_kernel; the pipelined
+# kernel's own cases are in test_gpu_pipelined_kernel.py and test_gpu_head_tiles.py) and the plain cross-check kernel
 KERNELS = [0, pec.PEC_FLAG_SIMPLE_KERNEL]
 # pec_sp_prefill: the default single sweep, and the two modes that launch once per ring step
 SP_MODES = [0, pec.PEC_FLAG_SP_SEPARATE_MERGE, pec.PEC_FLAG_SP_STEP_LAUNCHES]

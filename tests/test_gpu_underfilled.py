@@ -37,9 +37,10 @@ def assert_close(out, lse, o_ref, l_ref, what):
     (256, 300, 44, 0, True, 64, 4),        # 64-row workgroups, one per compute unit
     (193, 543, 350, 0, True, 64, 8),       # 64-row workgroups, the last one with a single row
     (224, 256, 0, 0, False, 64, 64),       # 64-row workgroups, half a row tile at the end, no mask
-    (130, 200, 70, 0, True, 256, 64),      # enough heads for the pipelined kernel: ragged single row tile
+    (40, 100, 0, 0, False, 256, 1),        # 64-row workgroups on one KV head, no mask
+    (130, 200, 70, 0, True, 256, 64),      # enough heads for the pipelined kernel: ragged last row tile
     (257, 321, 64, 0, True, 128, 128),     # the same, second row tile with one row
-    (40, 100, 0, 0, False, 256, 1),        # the same on one KV head, no mask
+    (300, 100, 0, 0, False, 256, 1),       # the same on one KV head, no mask
 ])
 def test_underfilled_calls_match_oracle_alone_and_merged(sq, sk, q_off, kv_off, causal, hq, hkv):
     q, k, v = synth.qkv(6000 + 7 * sq + sk, sq, max(sk, 1), hq, hkv)

@@ -1,0 +1,50 @@
+"""The GPU tests that are about one kernel run on it: the library's own choice, asked for the sizes that they use."""
+import pytest
+
+import kernel_choice as choice
+import test_gpu_decode_ranges as decode
+import test_gpu_head_tiles as head_tiles
+import test_gpu_pipelined_kernel as pipelined
+import test_gpu_underfilled as underfilled
+
+
+def cases(test):
+    (mark,) = [m for m in test.pytestmark if m.name == "parametrize"]
+    return [tuple(c) for c in mark.args[1]]
+
+
+@pytest.mark.parametrize("hkv", pipelined.KV_HEADS)
+def test_pipelined_kernel_cases(hkv):
+    for (sq, sk, q_off, causal), _ in pipelined.JUMPS:
+        cut = sk // 2
+        for n, kv_off in ((sk, 0), (cut, 0), (sk - cut, cut)):
+            assert choice.dense_rows(pipelined.HQ, hkv, sq, n, q_off, kv_off, causal) == 256
+    for q_off, kv_off, sq, sk in pipelined.MASKS:
+        assert choice.dense_rows(pipelined.HQ, hkv, sq, sk, q_off, kv_off) == 256
+    assert choice.packed_rows(pipelined.HQ, hkv, pipelined.BATCH_Q) == 256
+    assert choice.mixed_rows(pipelined.HQ, hkv, pipelined.BATCH_Q, pipelined.BATCH_K) == 256
+
+
+def test_head_tile_cases_run_on_the_pipelined_kernel():
+    for hq, hkv, sq, sk, q_off, causal in cases(head_tiles.test_items_of_several_heads_match_oracle):
+        assert choice.dense_rows(hq, hkv, sq, sk, q_off, 0, causal) == 256
+    got = {choice.mixed_rows(hq, hkv, head_tiles.LEN_Q * times, head_tiles.LEN_K * times): (hq, hkv, times)
+           for hq, hkv, times in cases(head_tiles.test_mixed_batches_with_items_of_several_heads)}
+    assert set(got) == {256}, got
+
+
+def test_underfilled_cases_cover_all_three_workgroups():
+    rows = [choice.dense_rows(hq, hkv, sq, sk, q_off, kv_off, causal) for sq, sk, q_off, kv_off, causal, hq, hkv in
+            cases(underfilled.test_underfilled_calls_match_oracle_alone_and_merged)]
+    assert rows == [32] * 10 + [64] * 4 + [256] * 3
+    batch = ([32, 1, 33, 1, 0, 64, 1, 65, 5], [32, 4096, 33, 4097, 7, 64, 9000, 65, 300])
+    assert {hq // hkv: choice.mixed_rows(hq, hkv, *batch) for hq, hkv in
+            cases(underfilled.test_small_mixed_batches_for_every_deal_of_kv_heads_to_xcds)} == {8: 32, 4: 32, 1: 32, 2: 32, 40: 64}
+
+
+def test_decode_cases_run_on_all_kernels():
+    kernels = {c: choice.decode_kernel_of(c[1], c[2], c[0], c[3])[1] for c in cases(decode.test_decode_ranges_match_oracle)}
+    others = {(64, 8, 8, 1), (8192, 32, 8, 33), (1500, 90, 90, 0), (1100, 150, 150, 0), (1100, 300, 300, 0), (600, 600, 300, 1),
+              (40000, 8, 1, 1100)}
+    for c, kernel in kernels.items():
+        assert kernel == ("fwd_il_kernel" if c == (300, 33, 1, 0) else "decode_kernel" if c in others else "fwd_split_kernel"), c
