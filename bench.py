@@ -254,7 +254,7 @@ def main():
     achieved = (flops / launches) / (avg_launch_ms * 1e-3) / 1e12
     roofline = {"bound": "mfma", "achieved": round(achieved, 2), "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(achieved / PEAK_BF16_TFLOPS, 4), "traffic": measured_traffic(args.workload),
-                "kernel": pec.KERNEL_NAMES[args.kernel_flag], "launches_per_step": launches,
+                "kernel": attention_kernel(torch, pec, args, dev, Hq, C), "launches_per_step": launches,
                 "avg_launch_ms": round(avg_launch_ms, 4), "flop_per_launch_avg": flops / launches}
 
     result = {
@@ -265,7 +265,7 @@ def main():
         "config": {"workload": "%s: causal prefill, %d q heads / %d kv heads, d 128, seq %d as %d segments of %d, "
                                "full ring sweep with LSE merge (%s)" % (w.name, Hq, Hkv, S, P, C, how),
                    "seq_len": S, "chunk": C, "n_q_heads": Hq, "n_kv_heads": Hkv, "sp_mode": args.sp_mode,
-                   "kernel": pec.KERNEL_NAMES[args.kernel_flag]},
+                   "kernel": attention_kernel(torch, pec, args, dev, Hq, C)},
         "tokens_per_s": round(S / (ms_step * 1e-3), 1),
         "pct_of_bf16_mfma_peak": round(100.0 * tflops / PEAK_BF16_TFLOPS, 2),
         "causal_useful_tflop_per_step": round(flops / 1e12, 3),
@@ -280,6 +280,14 @@ def main():
         result["cpu_baseline"] = cpu_baseline(args, np, torch, synth, q, k, v, w)
     print(json.dumps(result), flush=True)
     return 0
+
+
+def attention_kernel(torch, pec, args, dev, n_q_heads, rows):
+    """Kernel of one ring member's launches.  Of the workloads here only the 512-row members have fewer than 256 rows per
+    compute unit; as calls that cannot be stopped they run on the kernel that shares the keys out among wavefronts."""
+    underfilled = rows * n_q_heads < 256 * torch.cuda.get_device_properties(dev).multi_processor_count
+    return "pec::fwd_split_kernel" if underfilled and args.kernel_flag == 0 and args.sp_mode != "resumable" else \
+        pec.KERNEL_NAMES[args.kernel_flag]
 
 
 def bench_share(args, torch, pec, synth, dev, w, mode):
@@ -322,7 +330,7 @@ def bench_share(args, torch, pec, synth, dev, w, mode):
         "ms_per_step_stats": step_stats(ev_list),
         "roofline": {"bound": "mfma", "achieved": round(achieved, 2), "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(achieved / PEAK_BF16_TFLOPS, 4), "traffic": None,
-                     "kernel": pec.KERNEL_NAMES[args.kernel_flag],
+                     "kernel": attention_kernel(torch, pec, args, dev, Hq, C),
                      "launches_per_step": launches, "avg_launch_ms": round(avg_launch_ms, 4)},
     }
     print(json.dumps(result), flush=True)
@@ -581,6 +589,8 @@ def bench_decode(args, torch, np, pec, synth, dev):
     lse = torch.empty((Hq,), dtype=torch.float32, device=dev)
     ws = torch.empty(n_splits * Hq * 129 * 4, dtype=torch.uint8, device=dev)
     algo_bytes = 2.0 * sk * Hkv * 128 * 2 + 2 * Hq * 128 * 2 + Hq * 4      # K + V once, q, out, lse
+    one_round = n_splits * Hkv <= torch.cuda.get_device_properties(dev).multi_processor_count    # a workgroup per range and KV head
+    kernel = "pec::fwd_split_kernel" if one_round else "pec::decode_kernel"
 
     def step():
         pec.pec_decode_splitkv(q, k, v, n_splits=n_splits, out=out, lse=lse, workspace=ws)
@@ -598,7 +608,7 @@ def bench_decode(args, torch, np, pec, synth, dev):
                                % n_splits},
         "ms_per_step_stats": step_stats(ev_list),
         "roofline": {"bound": "hbm", "achieved": round(gbs, 1), "peak": 8000.0, "unit": "GB/s",
-                     "frac": round(gbs / 8000.0, 4), "traffic": None, "kernel": "pec::fwd_split_kernel + pec::combine_splits_kernel"},
+                     "frac": round(gbs / 8000.0, 4), "traffic": None, "kernel": kernel + " + pec::combine_splits_kernel"},
     }
     probe = hbm_read_probe(torch, pec, dev)
     result["hbm_read_probe"] = probe

@@ -197,7 +197,8 @@ int pec_sp_prefill_step(const pec_shape_t* shape, const void* q, const void* k, 
  *               device, so malformed values can misplace results but never index out of bounds.
  *   max_seqlen: the caller's bound on the sequence lengths (host value); a HINT only -- the work
  *               list is sized from total_tokens, so a sequence longer than max_seqlen is still
- *               processed in full, never cut short.
+ *               processed in full, never cut short.  It weighs in the choice of the query rows per
+ *               workgroup, so results for different hints may differ in rounding.
  *   lse [Hq, total_tokens].  Zero-length sequences are legal.
  * workspace: at least pec_varlen_workspace_bytes() bytes (the device-built work list).
  */
@@ -235,7 +236,9 @@ size_t pec_colocated_workspace_bytes(const pec_shape_t* shape, int32_t batch, in
  * (section "Coordinated Prefill-Decode Colocation and Disaggregation"): ONE new token, q [1, Hq, 128],
  * against this GPU's shard of the KV cache, k/v [sk, Hkv, 128]; every key is visible.  The shard is
  * cut into n_splits key ranges (0 = pick a default: one workgroup per compute unit), each KV head of
- * a range is streamed by one wavefront on its own, the partial (O, LSE) pairs are combined exactly
+ * a range is streamed by one workgroup, its eight wavefronts sharing the keys (by one wavefront on its
+ * own where that would be more workgroups than compute units, or ranges of up to 64 keys; groups of
+ * more than 32 query heads run on the prefill kernel), the partial (O, LSE) pairs are combined exactly
  * by log-sum-exp.  out [1, Hq, 128] in shape->out_dtype and
  * lse [Hq] form a partial pair over this shard: results of several shards / GPUs (the paper's
  * example merges the outputs of two GPUs) combine with pec_attn_merge (use out_dtype PEC_F32).

@@ -18,6 +18,7 @@ LIB_PATH = os.path.join(_HERE, "libpec_attn.so")
 
 PEC_BF16, PEC_F32 = 0, 1
 PEC_FLAG_SIMPLE_KERNEL, PEC_FLAG_SP_SEPARATE_MERGE, PEC_FLAG_SP_STEP_LAUNCHES = 1, 2, 4
+# by flags: the kernel of calls that fill the chip (smaller ones run on pec::fwd_split_kernel), and the plain one
 KERNEL_NAMES = {0: "pec::fwd_il_kernel", PEC_FLAG_SIMPLE_KERNEL: "pec::fwd_simple_kernel"}
 
 EXPORTS = (

@@ -65,7 +65,7 @@ __global__ __launch_bounds__(256) void finalize_kernel(const float* __restrict__
 // grp, grp + kCombineGroups, ...; every range's weight is taken once and handed round through LDS.  Partials are fp32
 // [n_splits][n_heads][128] and [n_splits][n_heads]; out_row points at the 128 outputs.
 // A few KB per head: latency is all there is to it, so the first kCombineAhead ranges of every thread are requested
-// together with the LSEs.128 ranges of 64 heads: 9.0 -> 5.1 us.
+// together with the LSEs.  128 ranges of 64 heads: 9.0 -> 5.1 us.
 constexpr int kCombineThreads = 1024, kCombineGroups = kCombineThreads / 32, kCombineAhead = 4;
 template <bool OUT_F32>
 __device__ __forceinline__ void combine_one_head(const float* __restrict__ o_part, const float* __restrict__ lse_part,

@@ -74,12 +74,12 @@ struct FwdParams {
     const int32_t* n_work;  // number of valid work items
     int32_t* sched;         // eight zeroed counters (fwd_il_kernel only): work items are drawn from them, one
                             // counter per XCD's share of the work order, instead of being dealt in fixed rounds
-    // split-KV mode (kv_split_len > 0; fwd_il_kernel only): work item = key range
+    // split-KV mode (kv_split_len > 0; not in fwd_simple_kernel): work item = key range
     // [item * kv_split_len, ...), partial results go to out / lse + item * split_*_stride
     int32_t kv_split_len;
     int64_t split_out_stride, split_lse_stride;   // elements
     // element strides of q / out / acc between rows and between heads (0 = the packed
-    // [tokens, n_q_heads, 128] layout; fwd_il_kernel only)
+    // [tokens, n_q_heads, 128] layout; not in fwd_simple_kernel, and fwd_split_kernel reads them in split-KV mode only)
     int64_t q_row_stride, q_head_stride;
     // colocated batch: partial results of the key ranges that one-token sequences with long caches are cut into
     float* part_out;            // [slots][n_q_heads][128] fp32

@@ -9,8 +9,8 @@
 // transposed-score MFMA scheme as the prefill kernels (columns >= g carry zeros): the matrix
 // pipe is mostly idle and does not matter here.
 //
-// Used where a workgroup per key range and KV head (fwd_split_kernel.hpp) would not be resident all at once, or would have
-// fewer tiles than wavefronts: see decode_on_split_kernel() on the host for where the line lies.
+// Used where the workgroups per key range and KV head of fwd_split_kernel.hpp would not be resident all at once, or would
+// have no more than two tiles: decode_on_split_kernel() in kernel_choice.hpp says where the line lies and what it measured.
 //
 // Each wavefront writes a normalised partial O and its LSE for its key range; the ranges are
 // merged by combine_splits_kernel.
