@@ -491,12 +491,11 @@ int decode_impl(const pec_shape_t* shape, float scale, const void* q, const void
         launch_il(p, (unsigned)(((total + 7) / 8) * 8), st);
     if (hipGetLastError() != hipSuccess) return PEC_ERR_HIP;
     }
-    if (shape->out_dtype == PEC_F32)
-        hipLaunchKernelGGL((combine_splits_kernel<true>), dim3(shape->n_q_heads), dim3(kCombineThreads), 0, st, o_part, lse_part,
-                           (int)n_splits, (int)shape->n_q_heads, out, lse);
-    else
-        hipLaunchKernelGGL((combine_splits_kernel<false>), dim3(shape->n_q_heads), dim3(kCombineThreads), 0, st, o_part, lse_part,
-                           (int)n_splits, (int)shape->n_q_heads, out, lse);
+    const bool few = n_splits <= kCombineFew, f32 = shape->out_dtype == PEC_F32;
+    auto* const merge = few ? (f32 ? combine_few_kernel<true> : combine_few_kernel<false>)
+                            : (f32 ? combine_splits_kernel<true> : combine_splits_kernel<false>);
+    hipLaunchKernelGGL(merge, dim3(shape->n_q_heads), dim3(few ? 64 : kCombineThreads), 0, st, o_part, lse_part, (int)n_splits,
+                       (int)shape->n_q_heads, out, lse);
     return hipGetLastError() == hipSuccess ? PEC_OK : PEC_ERR_HIP;
 }
 

@@ -23,6 +23,8 @@ pytestmark = pytest.mark.gpu
     (700, 100, 100, 0),                    # 200 workgroups of one KV head
     (1500, 90, 90, 0), (1100, 150, 150, 0),    # a workgroup per KV head and range would leave compute units idle: a wavefront each
     (1100, 300, 300, 0), (600, 600, 300, 1),   # more KV heads than compute units
+    (24 * 96, 6, 2, 24), (25 * 96, 6, 2, 25),   # as many ranges as one wavefront merges per head, and one more
+    (96 * 23 - 95, 4, 4, 24),              # ... the last but one with one key, the last empty
     (40000, 8, 1, 1100),                   # more ranges than the merge has threads, many of them empty
 ])
 def test_decode_ranges_match_oracle(sk, hq, hkv, n_splits):
