@@ -10,6 +10,8 @@ namespace pec {
 
 constexpr int kBM = 256;       // query rows per workgroup of fwd_il_kernel and fwd_simple_kernel
 constexpr int kDecWaves = 4;   // KV heads per workgroup of decode_kernel
+constexpr int64_t kStaticScratchBytes = 8 << 20;                        // of pec_decode_splitkv_static
+constexpr int64_t kStaticPartials = kStaticScratchBytes / (129 * 4);    // (range, query head) pairs that fit: O and LSE in fp32
 
 // The 256 rows of a fwd_il_kernel work item: as many heads of a KV group as divide it, up to 8, and 256 / heads query
 // positions of each.  All of them read the same keys, so the choice changes no traffic; fewer positions waste less at
@@ -115,19 +117,28 @@ inline bool decode_on_split_kernel(int cu, int n_q_heads, int n_kv_heads, int64_
     return n_q_heads / n_kv_heads <= 32 && n_splits * n_kv_heads <= cu && range_keys(sk, n_splits, 32) > 64;
 }
 
-// Key ranges of a decode step whose caller leaves the number to the library.
+// Key ranges of a decode step whose caller leaves the number to the library: as many as give every compute unit a workgroup
+// of fwd_split_kernel, of 256 keys at least (a tile of 32 for each of eight wavefronts) -- or, with more than 11 KV heads
+// and 768 keys per compute unit in all, of decode_kernel, whose workgroups read four neighbouring KV heads of a token.
+// Microseconds per step on 256 compute units, decode_kernel / fwd_split_kernel, each with these many ranges:
+//     16,384 keys    8 heads 26.8 / 21.3   12 heads 29.0 / 26.5   16 heads 33.1 / 34.5   40 heads 64.0 / 64.5   128 heads 190 / 201
+//     4,096 keys     40 heads 27.3 / 24.1   48 heads 28.0 / 26.6   64 heads 33.5 / 34.7   128 heads 55.7 / 56.5
+//     65,536 keys    7 heads 51.6 / 49.0   10 heads 66.8 / 60.4   36 heads 216 / 227   100 heads 562 / 627
+//     524,288 keys   1 head 100 / 54   8 heads 377 / 369   11 heads 507 / 504
+// Up to 11 heads the first is behind everywhere but for 1.6 % at 8 heads and 65,536 keys and 3 % at 4 heads and 524,288.
+// At the line itself (16 heads x 12,288 keys ... 256 x 768) the two differ by 0 ... 17 % in favour of fwd_split_kernel.
+// Ranges of decode_kernel whose partial results would not fit pec_decode_splitkv_static's buffer (16 KV heads with groups of
+// 16, say) stay with fwd_split_kernel too: its ranges, a quarter as many, always fit there where they did before.
 inline int64_t decode_default_ranges(int cu, int n_q_heads, int n_kv_heads, int64_t sk) {
     const int g = n_q_heads / n_kv_heads;
-    const int64_t per_cu = cu / n_kv_heads;   // ranges if every compute unit takes one KV head of one
-    const int64_t n = std::max<int64_t>(1, std::min<int64_t>(per_cu, sk / 256));   // ... and 256 keys at least: a tile of
-                                                                                  // 32 for each of eight wavefronts
-    // fwd_split_kernel, unless there are so many KV heads that it would leave a quarter of the compute units idle, or
-    // would not be the kernel that runs n ranges (more KV heads than compute units)
-    if (4 * per_cu * n_kv_heads >= 3 * cu && decode_on_split_kernel(cu, n_q_heads, n_kv_heads, sk, n)) return n;
-    if (g <= 32) {   // decode_kernel: one workgroup (four KV heads of one range) per compute unit, at least 8 tiles of 32 keys
-        const int64_t head_groups = (n_kv_heads + kDecWaves - 1) / kDecWaves;
-        return std::max<int64_t>(1, std::min<int64_t>(cu / head_groups, sk / 256));
-    }
+    const int64_t per_cu = cu / n_kv_heads;      // 0: more KV heads than compute units
+    const int64_t n = std::max<int64_t>(1, std::min<int64_t>(per_cu, sk / 256));
+    const int64_t head_groups = (n_kv_heads + kDecWaves - 1) / kDecWaves;
+    const int64_t n_waves = std::max<int64_t>(1, std::min<int64_t>(cu / head_groups, sk / 256));
+    if ((n_kv_heads <= 11 || sk * n_kv_heads <= 768 * (int64_t)cu || n_waves * n_q_heads > kStaticPartials) &&
+        decode_on_split_kernel(cu, n_q_heads, n_kv_heads, sk, n))
+        return n;
+    if (g <= 32) return std::min<int64_t>(n_waves, std::max<int64_t>(1, kStaticPartials / n_q_heads));
     // wide groups run on the prefill kernel: one workgroup per compute unit, at least 16 tiles of 64 keys each
     return std::max<int64_t>(1, std::min<int64_t>(per_cu, sk / 1024));
 }

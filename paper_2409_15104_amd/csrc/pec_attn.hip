@@ -413,7 +413,7 @@ namespace {
 
 // Scratch of pec_decode_splitkv_static: the fp32 partial (O, LSE) of every (key range, query head).
 // One copy per GPU, held until the process ends; its device address is looked up once per device.
-constexpr size_t kStaticScratchBytes = PEC_DECODE_STATIC_SCRATCH_BYTES;
+static_assert(PEC_DECODE_STATIC_SCRATCH_BYTES == (size_t)kStaticScratchBytes, "the default range count reckons with it");
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 int static_scratch(void** out) {

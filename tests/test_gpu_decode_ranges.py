@@ -20,8 +20,10 @@ pytestmark = pytest.mark.gpu
     (500, 6, 3, 4),                        # last range empty
     (8192, 32, 8, 32), (8192, 32, 8, 33),  # as many workgroups as compute units, and one round more
     (300, 32, 1, 0), (300, 33, 1, 0),      # widest group of either kernel; the next one runs on the prefill kernel
-    (700, 100, 100, 0),                    # 200 workgroups of one KV head
-    (1500, 90, 90, 0), (1100, 150, 150, 0),    # a workgroup per KV head and range would leave compute units idle: a wavefront each
+    (700, 100, 100, 0),                    # 200 workgroups of one range and KV head
+    (1500, 90, 90, 0), (1100, 150, 150, 0),    # 180 and 150 of them
+    (2500, 90, 90, 0), (1400, 150, 150, 0),    # more than 768 keys per compute unit in all: a wavefront each
+    (6145, 64, 32, 0), (6144, 64, 32, 0),      # on either side of that line
     (1100, 300, 300, 0), (600, 600, 300, 1),   # more KV heads than compute units
     (24 * 96, 6, 2, 24), (25 * 96, 6, 2, 25),   # as many ranges as one wavefront merges per head, and one more
     (96 * 23 - 95, 4, 4, 24),              # ... the last but one with one key, the last empty

@@ -44,7 +44,7 @@ def test_underfilled_cases_cover_all_three_workgroups():
 
 def test_decode_cases_run_on_all_kernels():
     kernels = {c: choice.decode_kernel_of(c[1], c[2], c[0], c[3])[1] for c in cases(decode.test_decode_ranges_match_oracle)}
-    others = {(64, 8, 8, 1), (8192, 32, 8, 33), (1500, 90, 90, 0), (1100, 150, 150, 0), (1100, 300, 300, 0), (600, 600, 300, 1),
-              (40000, 8, 1, 1100)}
+    others = {(64, 8, 8, 1), (8192, 32, 8, 33), (2500, 90, 90, 0), (1400, 150, 150, 0), (6145, 64, 32, 0), (1100, 300, 300, 0),
+              (600, 600, 300, 1), (40000, 8, 1, 1100)}
     for c, kernel in kernels.items():
         assert kernel == ("fwd_il_kernel" if c == (300, 33, 1, 0) else "decode_kernel" if c in others else "fwd_split_kernel"), c

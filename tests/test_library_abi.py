@@ -114,11 +114,19 @@ def test_binding_refuses_cpu_tensors(lib):
 
 
 @pytest.mark.parametrize("hkv,sk,n", [
-    (8, 524288, 32), (8, 4096, 16), (1, 100000, 256), (256, 100000, 1),   # a workgroup per compute unit, 256 keys at least
-    (90, 100000, 11), (150, 100000, 6),      # a workgroup each would leave a quarter of 256 compute units idle
-    (257, 100000, 3), (300, 100000, 3),      # more KV heads than compute units: four of a range in a workgroup
+    (8, 524288, 32), (8, 4096, 16), (1, 100000, 256), (11, 100000, 23),   # a workgroup per compute unit, 256 keys at least
+    (12, 16384, 21), (64, 3072, 4), (200, 900, 1), (256, 768, 1),         # the same, up to 768 keys per compute unit
+    (12, 16385, 64), (64, 3073, 12), (40, 65536, 25), (128, 65536, 8),    # beyond: four KV heads of a range in a workgroup
+    (90, 100000, 11), (150, 100000, 6), (257, 100000, 3), (300, 100000, 3),
     (300, 500, 1), (8, 64, 1), (8, 0, 1),
 ])
 def test_default_ranges_of_a_decode_step(lib, hkv, sk, n):
     shape = binding.PecShape(hkv, hkv, 128, binding.PEC_F32, 0.0, 0)
     assert lib.pec_decode_default_splits(ctypes.byref(shape), sk) == n
+
+
+@pytest.mark.parametrize("hq,hkv,sk", [(256, 16, 100000), (512, 16, 65536), (384, 12, 65536), (1024, 32, 32768), (255, 15, 100000)])
+def test_default_ranges_of_wide_groups_fit_the_static_buffer(lib, hq, hkv, sk):
+    shape = binding.PecShape(hq, hkv, 128, binding.PEC_F32, 0.0, 0)
+    n = lib.pec_decode_default_splits(ctypes.byref(shape), sk)
+    assert lib.pec_decode_workspace_bytes(ctypes.byref(shape), n) <= 8 << 20
