@@ -18,6 +18,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "common.hpp"
 #include "kernel_choice.hpp"
 
@@ -83,7 +85,7 @@ __global__ __launch_bounds__(kDecWaves * 64) void decode_kernel(const DecodePara
     const unsigned char* kbase = p.k + (key_begin * p.n_kv_heads + kvh) * (int64_t)(kHeadDim * 2);
     const unsigned char* vbase = p.v + (key_begin * p.n_kv_heads + kvh) * (int64_t)(kHeadDim * 2);
     const int ld_row = lane >> 4, ld_pos = lane & 15;
-    auto issue_half = [&](const unsigned char* base, bool is_v, int tile, unsigned char* stage) {
+    auto issue_half = [&](auto in_loop, const unsigned char* base, bool is_v, int tile, unsigned char* stage) {
         if (tile >= n_tiles) return;
         const int key0 = tile * kDecTile;
         const int last = len - 1 - key0;   // last valid row of this tile (>= 0)
@@ -95,11 +97,11 @@ __global__ __launch_bounds__(kDecWaves * 64) void decode_kernel(const DecodePara
             const uint32_t row_off = (uint32_t)min(key, last) * kv_stride_b;
             const uint32_t col = is_v ? (uint32_t)((((ld_pos >> 2) ^ (key & 3)) << 2) | (ld_pos & 3)) * 16u
                                       : (uint32_t)(ld_pos ^ (key & 15)) * 16u;
-            dma16<false>(tb, row_off + col, l0 + i * 1024);
+            dma16<decltype(in_loop)::value>(tb, row_off + col, l0 + i * 1024);
         }
     };
-    auto issue_k = [&](int tile) { issue_half(kbase, false, tile, lds_k[wave][tile % kDecKStages]); };
-    auto issue_v = [&](int tile) { issue_half(vbase, true, tile, lds_v[wave][tile % kDecVStages]); };
+    auto issue_k = [&](auto in_loop, int tile) { issue_half(in_loop, kbase, false, tile, lds_k[wave][tile % kDecKStages]); };
+    auto issue_v = [&](auto in_loop, int tile) { issue_half(in_loop, vbase, true, tile, lds_v[wave][tile % kDecVStages]); };
     constexpr int kLoadsPerHalf = kDecTile / 4;   // 8 load instructions per K or V tile and wavefront
 
     // ---- LDS operand offsets
@@ -124,11 +126,12 @@ __global__ __launch_bounds__(kDecWaves * 64) void decode_kernel(const DecodePara
     // Issue order: K(0) V(0) K(1) V(1) V(2), then per tile j: K(j+2) V(j+3).  Loads retire in order, so
     // when tile j starts the requests younger than K(j) and V(j) are V(j+1) | K(j+1) V(j+2): 24 of them
     // in the steady state, fewer at the end of the range (tiles past the end are not requested).
-    issue_k(0);
-    issue_v(0);
-    issue_k(1);
-    issue_v(1);
-    issue_v(2);
+    constexpr std::false_type ahead{};
+    issue_k(ahead, 0);
+    issue_v(ahead, 0);
+    issue_k(ahead, 1);
+    issue_v(ahead, 1);
+    issue_v(ahead, 2);
     static_assert(kLoadsPerHalf == 8 && kDecKStages == 2 && kDecVStages == 3, "the vmcnt immediates below assume this");
     for (int j = 0; j < n_tiles; ++j) {
         const int left = n_tiles - 1 - j;   // tiles after this one
@@ -200,8 +203,8 @@ __global__ __launch_bounds__(kDecWaves * 64) void decode_kernel(const DecodePara
             }
         // the LDS reads of this tile's stages are consumed (the MFMAs above needed them): refill them
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        issue_k(j + 2);
-        issue_v(j + 3);
+        issue_k(std::true_type{}, j + 2);
+        issue_v(std::true_type{}, j + 3);
     }
 
     // ---- partial result of this range
