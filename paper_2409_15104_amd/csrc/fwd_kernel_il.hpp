@@ -125,6 +125,11 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
         return reinterpret_cast<const unsigned char*>((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(u >> 32)) << 32 |
                                                       (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)u));
     };
+    auto settled = [&](const void* a) {   // the same, as the base of several loads: moved once for all of them (see dma16)
+        const unsigned char* u = uniform(a);
+        asm volatile("s_mov_b64 %0, %0" : "+s"(u));
+        return u;
+    };
     auto count_up = [&](int x) {      // takes a number from XCD x's counter (valid in lane 0)
         int v = 0;
         if (lane_id() == 0) v = atomicAdd(&p.sched[x], 1);
@@ -408,7 +413,7 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
                 const int key = 4 * (it * NWAVES + wave) + r_row;
                 const uint32_t col = is_v ? (uint32_t)((((r_pos >> 2) ^ (key & 3)) << 2) | (r_pos & 3)) * 16u
                                           : (uint32_t)(r_pos ^ (key & 15)) * 16u;
-                dma16<false>(tb, (uint32_t)min(key, last) * kv_stride_b + col, lds0 + it * NWAVES * 1024);
+                dma16<decltype(in_loop)::value>(tb, (uint32_t)min(key, last) * kv_stride_b + col, lds0 + it * NWAVES * 1024);
             }
         }
     };
@@ -424,12 +429,12 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
     auto issue_q = [&](const Geo& of) {
         if (of.rw0 >= of.sq) return;
         const int ln = lane_id(), last = of.sq - 1 - of.rw0;
-        const unsigned char* qb = uniform(p.q + of.q_off0 + of.rw0 * of.q_stride);
+        const unsigned char* const qb = settled(p.q + of.q_off0 + of.rw0 * of.q_stride);
         const uint32_t l0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds_q;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int row = 4 * i + (ln >> 4);
-            dma16<false>(qb, (uint32_t)min(row, last) * (uint32_t)(of.q_stride * 2) + (uint32_t)((ln & 15) ^ (row & 15)) * 16u, l0 + i * 1024);
+            dma16<true>(qb, (uint32_t)min(row, last) * (uint32_t)(of.q_stride * 2) + (uint32_t)((ln & 15) ^ (row & 15)) * 16u, l0 + i * 1024);
         }
     };
     // When the item's tiles are done, and both K stages free, everything the next item starts with is requested -- its Q,
@@ -463,9 +468,9 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
             next = dense_geometry(unit);
         }
         const int n = tiles_of(next);
-        const unsigned char* const kb = uniform(kv_base(p.k, next));
-        if (n > 0) issue_rows(std::false_type{}, kb, false, ldk_off0, 0, lds_k0, next.sk);
-        if (n > 1) issue_rows(std::false_type{}, kb, false, ldk_off0, 1, lds_k1, next.sk);
+        const unsigned char* const kb = settled(kv_base(p.k, next));
+        if (n > 0) issue_rows(std::true_type{}, kb, false, ldk_off0, 0, lds_k0, next.sk);
+        if (n > 1) issue_rows(std::true_type{}, kb, false, ldk_off0, 1, lds_k1, next.sk);
         issue_q(next);
     };
 

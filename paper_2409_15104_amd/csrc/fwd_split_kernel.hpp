@@ -197,7 +197,7 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void fwd_split_kernel(const Fw
                 const int key = 4 * i + r_row;
                 const uint32_t col = is_v ? (uint32_t)((((r_pos >> 2) ^ (key & 3)) << 2) | (r_pos & 3)) * 16u
                                           : (uint32_t)(r_pos ^ (key & 15)) * 16u;
-                dma16<false>(tb, (uint32_t)min(key, last) * kv_stride_b + col, l0 + i * 1024);
+                dma16<decltype(in_loop)::value>(tb, (uint32_t)min(key, last) * kv_stride_b + col, l0 + i * 1024);
             }
         }
     };
