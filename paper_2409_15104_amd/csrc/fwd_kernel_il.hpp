@@ -225,7 +225,7 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
         const int rem = logical % order.per_kvh;
         const int item = rem / units;
         // the 256 query rows are 2^log_heads heads x (256 >> log_heads) positions, 32 positions of one head per wavefront
-        // (see log_heads_per_item() on the host)
+        // (see most_log_heads_per_item() on the host)
         const int bm = BM >> log_heads;
         const int head = g.kvh * p.group + ((rem % units) << log_heads) + (wave >> (3 - log_heads));
         int qt = p.causal ? (p.n_items - 1 - item) : item;  // longest rows first

@@ -21,9 +21,39 @@ constexpr int64_t kStaticPartials = kStaticScratchBytes / (129 * 4);    // (rang
 // Measured (one head per item -> up to eight): causal ring step of 4096 x 4096, 32 q / 8 kv heads, one of four in
 // 878 -> 859 us; the 256 prompts with a decode step 12.43 -> 12.17 ms: the chip is at its power limit, and wavefronts
 // that wait at the diagonal cost time but little power.
-inline int log_heads_per_item(int n_q_heads, int n_kv_heads) {
+inline int most_log_heads_per_item(int n_q_heads, int n_kv_heads) {
     const int g = n_q_heads / n_kv_heads;
     return g % 8 == 0 ? 3 : g % 4 == 0 ? 2 : g % 2 == 0 ? 1 : 0;
+}
+
+// One head per item where that is faster.
+//  * Fewer items than compute units and fewer than 768 keys: such a call is its first loads and its results, at the rate of
+//    one compute unit's memory path, and one head per item spreads them over more of them: 64 q / 8 kv heads, 322 x 322 rows
+//    and keys 17.1 -> 14.2 us; 16 / 4, 1900 x 205 folded into a running state 20.6 -> 17.7; at worst 381 x 381 without
+//    mask 19.5 -> 20.1.  From 2,000 keys on several heads are 0 ... 5 % ahead.
+//  * Items of nearly equal length that come out at a little more than a whole number per compute unit: a few compute units
+//    take one more, at full length, while the partly filled row tiles of one head per item are a light last round.  64 / 8,
+//    1047 x 11729 without mask 522 -> 442 us, 2073 x 7188 442 -> 384, 128 / 8, 1560 x 16985 1546 -> 1448, 1055 x 1055
+//    without mask 97.7 -> 89.4; at worst 2317 x 5543 317 -> 321.  With a mask and between one and two items per compute unit
+//    the heavy items of both rounds meet, which pays only for long calls: 598 x 1680 73 -> 79, 532 x 2922 125 -> 118.
+inline int log_heads_of_dense_call(int cu, int n_q_heads, int n_kv_heads, int64_t sq, int64_t sk, int64_t delta, bool causal) {
+    const int l = most_log_heads_per_item(n_q_heads, n_kv_heads);
+    auto items_of = [&](int lh) { return ((sq + (kBM >> lh) - 1) / (kBM >> lh)) * (n_q_heads >> lh); };
+    auto keys = [&](int64_t last_row) { return causal ? std::max<int64_t>(0, std::min(sk, last_row + delta + 1)) : sk; };
+    const int64_t longest = keys(sq - 1), shortest = keys(std::min<int64_t>(sq, kBM >> l) - 1);
+    const int64_t items = items_of(l), items1 = items_of(0);
+    if (items < cu) return longest < 768 ? 0 : l;
+    const int64_t whole = items / cu, left = items % cu;
+    const bool cliff = left > 0 && 20 * left <= 7 * cu && (items1 + cu - 1) / cu == whole + 1 && 10 * (items1 - items) >= cu;
+    return cliff && 2 * shortest >= longest && (!causal || whole > 1 || longest >= 2048) ? 0 : l;
+}
+
+// The same for a packed or colocated batch, of which the host knows only totals: several heads from 2.5 items per compute
+// unit on.  Over 118 random batches, time with one head per item over time with the most, by items per compute unit:
+// up to 0.5 0.87, up to 1 0.97, up to 1.5 0.975 (0.73 ... 1.10), up to 2.5 0.986 (0.82 ... 1.03), up to 5 1.014, beyond 1.032.
+inline int log_heads_of_list_call(int cu, int n_q_heads, int n_kv_heads, int64_t batch, int64_t total_q) {
+    const int l = most_log_heads_per_item(n_q_heads, n_kv_heads);
+    return 2 * batch * std::ceil((double)total_q / batch / (kBM >> l)) * (n_q_heads >> l) >= 5.0 * cu ? l : 0;
 }
 
 // Query rows per workgroup of a launch: 256 (fwd_il_kernel, one workgroup per 64-key tile step) or, where that would
@@ -48,7 +78,7 @@ constexpr RowChoice kRowChoices[] = {{256, 64, 11.5, 1.13, 1.55}, {64, 256, 8.0,
 
 inline int rows_of_dense_call(int cu, int n_q_heads, int n_kv_heads, int64_t sq, int64_t sk, int64_t delta, bool causal) {
     auto groups_of = [&](int rows) {   // workgroups (of the persistent kernel: work items)
-        const int l = rows == kBM ? log_heads_per_item(n_q_heads, n_kv_heads) : 0, positions = rows >> l;
+        const int l = rows == kBM ? most_log_heads_per_item(n_q_heads, n_kv_heads) : 0, positions = rows >> l;
         return (double)((sq + positions - 1) / positions) * (n_q_heads >> l);
     };
     if (groups_of(kBM) >= cu) return kBM;   // an item for every compute unit
@@ -80,7 +110,7 @@ inline int rows_of_list_call(int cu, int n_q_heads, int n_kv_heads, int64_t batc
     if (longest <= 0) longest = (int64_t)std::min((double)total_q, 4 * len);
     const double range_units = range_len > 0 ? std::max(0.0, (double)(total_k - total_q) / range_len) * n_kv_heads : 0.0;
     auto groups_of = [&](int rows) {
-        const int l = rows == kBM ? log_heads_per_item(n_q_heads, n_kv_heads) : 0;
+        const int l = rows == kBM ? most_log_heads_per_item(n_q_heads, n_kv_heads) : 0;
         return batch * std::ceil(len / (rows >> l)) * (n_q_heads >> l) + range_units;
     };
     if (groups_of(kBM) >= cu) return kBM;

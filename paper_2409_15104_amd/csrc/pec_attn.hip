@@ -144,9 +144,9 @@ int chunk_impl(const pec_shape_t* shape, const void* q, const void* k, const voi
     }
     const bool simple = (shape->flags & PEC_FLAG_SIMPLE_KERNEL) != 0;
     // (the progress table of the resumable sweep counts tiles of 256 rows of one head)
-    if (!simple && !sweep) p.log_heads = log_heads_per_item(p.n_q_heads, p.n_kv_heads);
     const int rows = simple || sweep ? kBM : rows_of_dense_call(compute_units(), p.n_q_heads, p.n_kv_heads, sq, sk, p.delta, p.causal);
-    if (rows != kBM) p.log_heads = 0;
+    if (!simple && !sweep && rows == kBM)
+        p.log_heads = log_heads_of_dense_call(compute_units(), p.n_q_heads, p.n_kv_heads, sq, sk, p.delta, p.causal);
     const int positions = rows >> p.log_heads;
     p.n_items = (int32_t)((sq + positions - 1) / positions);
     return launch_fwd(p, simple, rows, static_cast<hipStream_t>(stream));
@@ -637,7 +637,7 @@ int pec_attn_varlen(const pec_shape_t* shape, const void* q, const void* k, cons
     p.n_q_heads = shape->n_q_heads;
     p.n_kv_heads = shape->n_kv_heads;
     p.group = shape->n_q_heads / shape->n_kv_heads;
-    p.log_heads = simple || rows != kBM ? 0 : log_heads_per_item(p.n_q_heads, p.n_kv_heads);
+    if (!simple && rows == kBM) p.log_heads = log_heads_of_list_call(compute_units(), p.n_q_heads, p.n_kv_heads, batch, total_tokens);
     p.n_items = capacity;
     p.out_f32 = shape->out_dtype == PEC_F32;
     p.scale_log2 = scale * kLog2e;
@@ -719,7 +719,7 @@ int pec_attn_colocated(const pec_shape_t* shape, const void* q, const void* k, c
     p.n_q_heads = shape->n_q_heads;
     p.n_kv_heads = shape->n_kv_heads;
     p.group = shape->n_q_heads / shape->n_kv_heads;
-    p.log_heads = rows != kBM ? 0 : log_heads_per_item(p.n_q_heads, p.n_kv_heads);
+    if (rows == kBM) p.log_heads = log_heads_of_list_call(compute_units(), p.n_q_heads, p.n_kv_heads, batch, total_q);
     p.n_items = (int32_t)L.cap_items;
     p.out_f32 = shape->out_dtype == PEC_F32;
     p.scale_log2 = scale * kLog2e;

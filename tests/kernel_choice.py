@@ -17,6 +17,12 @@ extern "C" int dense(int cu, int hq, int hkv, int64_t sq, int64_t sk, int64_t de
 extern "C" int list(int cu, int hq, int hkv, int64_t batch, int64_t tq, int64_t tk, int64_t longest, int causal, int range) {
     return pec::rows_of_list_call(cu, hq, hkv, batch, tq, tk, longest, causal, range);
 }
+extern "C" int dense_heads(int cu, int hq, int hkv, int64_t sq, int64_t sk, int64_t delta, int causal) {
+    return 1 << pec::log_heads_of_dense_call(cu, hq, hkv, sq, sk, delta, causal);
+}
+extern "C" int list_heads(int cu, int hq, int hkv, int64_t batch, int64_t tq) {
+    return 1 << pec::log_heads_of_list_call(cu, hq, hkv, batch, tq);
+}
 extern "C" int64_t ranges(int cu, int hq, int hkv, int64_t sk) { return pec::decode_default_ranges(cu, hq, hkv, sk); }
 extern "C" int split(int cu, int hq, int hkv, int64_t sk, int64_t n) { return pec::decode_on_split_kernel(cu, hq, hkv, sk, n); }
 """
@@ -32,6 +38,8 @@ def _lib():
         L = ctypes.CDLL(lib)
     i64 = ctypes.c_int64
     L.dense.argtypes = [ctypes.c_int] * 3 + [i64] * 3 + [ctypes.c_int]
+    L.dense_heads.argtypes = L.dense.argtypes
+    L.list_heads.argtypes = [ctypes.c_int] * 3 + [i64] * 2
     L.list.argtypes = [ctypes.c_int] * 3 + [i64] * 4 + [ctypes.c_int] * 2
     L.ranges.argtypes, L.ranges.restype = [ctypes.c_int] * 3 + [i64], i64
     L.split.argtypes = [ctypes.c_int] * 3 + [i64] * 2
@@ -42,6 +50,16 @@ def dense_rows(hq, hkv, sq, sk, q_off=0, kv_off=0, causal=True):
     """Query rows per workgroup: 256 is fwd_il_kernel, 64 and 32 are fwd_split_kernel<2> and <1>."""
     delta = max(-sq - 1, min(q_off - kv_off, sk))
     return _lib().dense(COMPUTE_UNITS, hq, hkv, sq, sk, delta, int(causal))
+
+
+def dense_heads(hq, hkv, sq, sk, q_off=0, kv_off=0, causal=True):
+    """Query heads per work item of a call that runs on fwd_il_kernel."""
+    return _lib().dense_heads(COMPUTE_UNITS, hq, hkv, sq, sk, max(-sq - 1, min(q_off - kv_off, sk)), int(causal))
+
+
+def batch_heads(hq, hkv, len_q):
+    """The same for a packed or mixed batch."""
+    return _lib().list_heads(COMPUTE_UNITS, hq, hkv, len(len_q), int(sum(len_q)))
 
 
 def packed_rows(hq, hkv, lengths, hint=None, causal=True):

@@ -16,10 +16,13 @@ pytestmark = pytest.mark.gpu
     (512, 64, 127, 260, 133, True),      # 8 heads x 32 positions: last tile one position short
     (512, 64, 97, 65, 0, True),          # ... last tile with one position, rows past the last key
     (512, 128, 129, 190, 61, True),      # 4 heads x 64 positions: last tile with one position
-    (512, 128, 63, 100, 0, False),       # ... no mask, one tile one position short
+    (512, 128, 63, 100, 0, False),       # ... no mask; so few items and keys that a head has an item of its own
+    (512, 128, 127, 100, 0, False),      # ... no mask, last tile one position short
     (384, 32, 130, 130, 0, True),        # 12 heads per KV head: three work units of 4
     (256, 128, 257, 257, 0, True),       # 2 heads x 128 positions: last tile with one position
-    (192, 32, 200, 70, 200, True),       # 6 heads per KV head: three work units of 2, every key visible
+    (192, 32, 200, 70, 200, True),       # 6 heads per KV head, every key visible; a head has an item of its own
+    (192, 32, 300, 70, 300, True),       # ... three work units of 2
+    (512, 64, 130, 100, 0, False),       # a little more than one item of 8 heads per compute unit: one head each
     (264, 88, 90, 150, 20, True),        # 3 heads per KV head: one head x 256 positions, KV heads not a power of two
 ])
 def test_items_of_several_heads_match_oracle(hq, hkv, sq, sk, q_off, causal):
@@ -42,9 +45,10 @@ LEN_Q = [32, 1, 33, 64, 0, 65, 127, 1, 128, 129, 255, 1, 256, 257, 31, 63, 5, 70
 LEN_K = [32, 5000, 33, 64, 7, 65, 127, 4097, 128, 129, 255, 9, 256, 257, 31, 63, 300, 700, 1000]
 
 
-@pytest.mark.parametrize("hq,hkv,times", [(64, 8, 1), (32, 8, 1), (24, 2, 2), (16, 8, 2), (36, 6, 1), (8, 8, 2)])
+@pytest.mark.parametrize("hq,hkv,times", [(64, 8, 1), (32, 8, 1), (24, 2, 2), (16, 8, 2), (36, 6, 1), (8, 8, 2),   # one head
+                                         (64, 8, 2), (32, 8, 3), (24, 2, 3), (16, 8, 5), (36, 6, 2)])
 def test_mixed_batches_with_items_of_several_heads(hq, hkv, times):
-    """The batch above, as often as it takes for an item per compute unit (tests/test_kernel_choice.py)."""
+    """The batch above, as often as it takes for an item per compute unit, and for 2.5 of them (tests/test_kernel_choice.py)."""
     len_q, len_k = LEN_Q * times, LEN_K * times
     cq, ck = synth.cu_seqlens_of(len_q), synth.cu_seqlens_of(len_k)
     tq, tk = int(cq[-1]), int(ck[-1])

@@ -53,21 +53,23 @@ def test_jumps_of_the_row_maximum(sizes, outliers, hkv):
             assert_close(o_acc[:, heads], l_acc[heads], o_ref, l_ref, "two segments")
 
 
+@pytest.mark.parametrize("times", [1, 2])      # one head and several heads per work item
 @pytest.mark.parametrize("hkv", KV_HEADS)
-def test_jumps_of_the_row_maximum_in_batches(hkv):
-    for len_k in (BATCH_Q, BATCH_K):
-        cq, ck = synth.cu_seqlens_of(BATCH_Q), synth.cu_seqlens_of(len_k)
+def test_jumps_of_the_row_maximum_in_batches(hkv, times):
+    len_q = BATCH_Q * times
+    for len_k in (len_q, BATCH_K * times):
+        cq, ck = synth.cu_seqlens_of(len_q), synth.cu_seqlens_of(len_k)
         tq, tk = int(cq[-1]), int(ck[-1])
         q1, k1, q2, k2 = int(cq[1]), int(ck[1]), int(cq[2]), int(ck[2])
         outliers = [(10, 150, 8), (k1 + 70, q1 + 950, 2), (k1 + 640, q1 + 700, 8), (k1 + 900, q1 + 901, 4), (k1 + 1023, q1 + 1023, 8)]
-        if len_k is BATCH_K:     # the decode step: in the first key range, around its end and in the last, short one
+        if len_k is not len_q:   # the decode step: in the first key range, around its end and in the last, short one
             outliers += [(k2 + 100, q2, 1), (k2 + 4095, q2, 1), (k2 + 4100, q2, 2), (k2 + 8999, q2, 1)]
         q, k, v = synth.qkv_with_outlier_keys(5200 + hkv, tq, tk, HQ, hkv, outliers)
         cqd, ckd = torch.from_numpy(cq).to(DEV), torch.from_numpy(ck).to(DEV)
         out = torch.full((tq, HQ, 128), float("nan"), dtype=torch.float32, device=DEV)
         lse = torch.full((HQ, tq), float("nan"), dtype=torch.float32, device=DEV)
-        if len_k is BATCH_Q:
-            pec.pec_attn_varlen(q.to(DEV), k.to(DEV), v.to(DEV), cqd, max(BATCH_Q), True, out_dtype=torch.float32, out=out, lse=lse)
+        if len_k is len_q:
+            pec.pec_attn_varlen(q.to(DEV), k.to(DEV), v.to(DEV), cqd, max(len_q), True, out_dtype=torch.float32, out=out, lse=lse)
         else:
             pec.pec_attn_colocated(q.to(DEV), k.to(DEV), v.to(DEV), cqd, ckd, True, out_dtype=torch.float32, out=out, lse=lse)
         for heads, qh, kh, vh in some_groups(hkv, q, k, v):

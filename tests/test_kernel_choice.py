@@ -15,22 +15,47 @@ def cases(test):
 
 @pytest.mark.parametrize("hkv", pipelined.KV_HEADS)
 def test_pipelined_kernel_cases(hkv):
+    hq = pipelined.HQ
     for (sq, sk, q_off, causal), _ in pipelined.JUMPS:
         cut = sk // 2
         for n, kv_off in ((sk, 0), (cut, 0), (sk - cut, cut)):
-            assert choice.dense_rows(pipelined.HQ, hkv, sq, n, q_off, kv_off, causal) == 256
+            assert choice.dense_rows(hq, hkv, sq, n, q_off, kv_off, causal) == 256
+            assert choice.dense_heads(hq, hkv, sq, n, q_off, kv_off, causal) == hq // hkv
     for q_off, kv_off, sq, sk in pipelined.MASKS:
-        assert choice.dense_rows(pipelined.HQ, hkv, sq, sk, q_off, kv_off) == 256
-    assert choice.packed_rows(pipelined.HQ, hkv, pipelined.BATCH_Q) == 256
-    assert choice.mixed_rows(pipelined.HQ, hkv, pipelined.BATCH_Q, pipelined.BATCH_K) == 256
+        assert choice.dense_rows(hq, hkv, sq, sk, q_off, kv_off) == 256
+        assert choice.dense_heads(hq, hkv, sq, sk, q_off, kv_off) == hq // hkv
+    for times, heads in ((1, 1), (2, hq // hkv)):
+        assert choice.packed_rows(hq, hkv, pipelined.BATCH_Q * times) == 256
+        assert choice.mixed_rows(hq, hkv, pipelined.BATCH_Q * times, pipelined.BATCH_K * times) == 256
+        assert choice.batch_heads(hq, hkv, pipelined.BATCH_Q * times) == heads
 
 
 def test_head_tile_cases_run_on_the_pipelined_kernel():
+    heads = []
     for hq, hkv, sq, sk, q_off, causal in cases(head_tiles.test_items_of_several_heads_match_oracle):
         assert choice.dense_rows(hq, hkv, sq, sk, q_off, 0, causal) == 256
-    got = {choice.mixed_rows(hq, hkv, head_tiles.LEN_Q * times, head_tiles.LEN_K * times): (hq, hkv, times)
-           for hq, hkv, times in cases(head_tiles.test_mixed_batches_with_items_of_several_heads)}
-    assert set(got) == {256}, got
+        heads.append(choice.dense_heads(hq, hkv, sq, sk, q_off, 0, causal))
+    assert heads == [8, 8, 4, 1, 4, 4, 2, 1, 2, 1, 1]
+    heads = []
+    for hq, hkv, times in cases(head_tiles.test_mixed_batches_with_items_of_several_heads):
+        assert choice.mixed_rows(hq, hkv, head_tiles.LEN_Q * times, head_tiles.LEN_K * times) == 256
+        heads.append(choice.batch_heads(hq, hkv, head_tiles.LEN_Q * times))
+    assert heads == [1] * 6 + [8, 4, 4, 2, 2]
+
+
+@pytest.mark.parametrize("case,heads", [
+    # fewer items than compute units: by the keys
+    ((64, 8, 322, 767), 1), ((64, 8, 322, 768, 446), 8), ((64, 8, 322, 768, 445), 1), ((16, 4, 700, 700, 0, 0, False), 1),
+    # a little more than a whole number of items per compute unit and nearly equal lengths
+    ((64, 8, 1047, 11729, 0, 0, False), 1), ((64, 8, 2073, 7188, 5115), 1), ((128, 8, 1560, 16985, 15425), 1),
+    # ... exactly a whole number; more than 0.35 above it
+    ((64, 8, 1024, 11729, 0, 0, False), 8), ((64, 8, 1409, 11729, 0, 0, False), 8), ((64, 8, 1400, 11729, 0, 0, False), 8),
+    # ... lengths from one to all keys, a short call with a mask
+    ((64, 8, 2118, 2118), 8), ((128, 8, 598, 1680, 1082), 8), ((128, 8, 598, 2048, 1450), 1),
+    ((40, 8, 1047, 11729, 0, 0, False), 1),   # groups of five
+])
+def test_heads_per_work_item_of_dense_calls(case, heads):
+    assert choice.dense_heads(*case) == heads
 
 
 def test_underfilled_cases_cover_all_three_workgroups():
