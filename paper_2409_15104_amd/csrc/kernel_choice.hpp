@@ -160,7 +160,8 @@ inline bool decode_on_split_kernel(int cu, int n_q_heads, int n_kv_heads, int64_
 //     4,096 keys     40 heads 27.3 / 24.1   48 heads 28.0 / 26.6   64 heads 33.5 / 34.7   128 heads 55.7 / 56.5
 //     65,536 keys    7 heads 51.6 / 49.0   10 heads 66.8 / 60.4   36 heads 216 / 227   100 heads 562 / 627
 //     524,288 keys   1 head 100 / 54   8 heads 377 / 369   11 heads 507 / 504
-// Up to 11 heads the first is behind everywhere but for 1.6 % at 8 heads and 65,536 keys and 3 % at 4 heads and 524,288.
+// Up to 11 heads the first is behind everywhere but for 1.6 % at 8 heads and 65,536 keys and 3 % at 4 heads and 524,288 on one
+// card, where it is 3 % and 1.5 % behind on another.
 // At the line itself (16 heads x 12,288 keys ... 256 x 768) the two differ by 0 ... 17 % in favour of fwd_split_kernel.
 // Ranges of decode_kernel whose partial results would not fit pec_decode_splitkv_static's buffer (16 KV heads with groups of
 // 16, say) stay with fwd_split_kernel too: its ranges, a quarter as many, always fit there where they did before.
