@@ -307,8 +307,11 @@ __device__ __forceinline__ int block_suffix_sum_1024(T* a, int n, int32_t* red) 
 
 // Work list of a packed or colocated batch.  A sequence with one query token and more than range_len keys (the decode
 // step of a long request; range_len > 0 only in a colocated batch) is cut into key ranges of range_len keys, `group` of
-// them per item (one for each of its work units), every other sequence into query tiles of bm rows; items are ordered by
-// descending number of blocks of block_keys keys they have to read, so that the long ones start first.
+// them per item (one for each of its work units), every other sequence into query tiles of bm rows.  Items are ordered by
+// descending number of blocks of block_keys keys they have to read, so that the long ones start first and the launch ends
+// on the short ones -- or, by_sequence, sequences by that number of their heaviest item, the items of one sequence
+// together, the longest first: the workgroups of an XCD then work on one sequence at a time, whose keys its L2 holds
+// (list_by_sequence() in kernel_choice.hpp).
 // Single workgroup of 1024 threads.  counters: [0] number of items, [1] slots handed out, [2] number of split sequences,
 // [8 .. 15] the attention kernel's draw counters, one per XCD.  bucket is int32[n_buckets], n_buckets larger than the
 // number of such blocks in all keys.  Sequence bounds are clamped into [0, total], so no index leaves the arrays whatever
@@ -321,11 +324,11 @@ constexpr int kListSeqs = 1024, kListBuckets = 2048;
 __global__ __launch_bounds__(1024) void build_worklist_kernel(const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k,
                                                               int batch, int total_q, int total_k, int bm, int block_keys,
                                                               int range_len, int group, int capacity, int slot_capacity,
-                                                              int n_buckets, WorkItem* __restrict__ work,
+                                                              int n_buckets, int by_sequence, WorkItem* __restrict__ work,
                                                               int32_t* __restrict__ counters, int32_t* __restrict__ bucket,
                                                               SplitSeq* __restrict__ split_seqs) {
     struct Seq {
-        int q0, len_q, k0, len_k, slot0, n_items;   // slot0 -1: not split
+        int q0, len_q, k0, len_k, slot0, n_items, pos0;   // slot0 -1: not split; pos0: list position of its first item
     };
     __shared__ Seq seqs[kListSeqs];
     __shared__ int32_t lds_bucket[kListBuckets];
@@ -350,50 +353,47 @@ __global__ __launch_bounds__(1024) void build_worklist_kernel(const int32_t* __r
                                      : min(s.len_k, max(0, s.len_k - s.len_q + min(s.len_q, bm * (i + 1))));
         return min(n_buckets - 1, (keys + block_keys - 1) / block_keys);
     };
-    // Sequences c0 ... into LDS; the first time round, slots for the key ranges of split ones.  (A sequence that finds no
+    auto heaviest_of = [&](const Seq& s) { return weight_of(s, is_split(s) ? 0 : max(0, s.n_items - 1)); };
+    // Sequence c0 + tid into LDS; the first time round, slots for the key ranges of split ones.  (A sequence that finds no
     // room -- only possible with offsets that are not monotone, whose clamped lengths can add up to more than total_k -- is
     // left out altogether.)  Slots are handed out once per sequence: with more than kListSeqs sequences they are kept in
     // split_seqs and looked up there.
-    auto load_seqs = [&](int c0, bool first) {
+    auto load_seq = [&](int c0, bool first) {
         const int b = c0 + tid;
-        if (b < batch) {
-            Seq s = bounds_of(b);
-            if (is_split(s)) {
-                const int n_ranges = (s.len_k + range_len - 1) / range_len;
-                s.n_items = (n_ranges + group - 1) / group;
-                if (first) {
-                    s.slot0 = atomicAdd(&n_slots, n_ranges);
-                    if (s.slot0 + n_ranges <= slot_capacity) {
-                        split_seqs[atomicAdd(&n_split, 1)] = SplitSeq{b, s.slot0, n_ranges, 0};
-                    } else {
-                        s.n_items = 0;
-                    }
+        if (b >= batch) return;
+        Seq s = bounds_of(b);
+        if (is_split(s)) {
+            const int n_ranges = (s.len_k + range_len - 1) / range_len;
+            s.n_items = (n_ranges + group - 1) / group;
+            if (first) {
+                s.slot0 = atomicAdd(&n_slots, n_ranges);
+                if (s.slot0 + n_ranges <= slot_capacity) {
+                    split_seqs[atomicAdd(&n_split, 1)] = SplitSeq{b, s.slot0, n_ranges, 0};
                 } else {
                     s.n_items = 0;
-                    for (int i = 0; i < n_split; ++i) {
-                        const SplitSeq ss = split_seqs[i];
-                        if (ss.seq != b) continue;
-                        s.slot0 = ss.slot0;
-                        s.n_items = (n_ranges + group - 1) / group;
-                    }
+                }
+            } else {
+                s.n_items = 0;
+                for (int i = 0; i < n_split; ++i) {
+                    const SplitSeq ss = split_seqs[i];
+                    if (ss.seq != b) continue;
+                    s.slot0 = ss.slot0;
+                    s.n_items = (n_ranges + group - 1) / group;
                 }
             }
-            seqs[tid] = s;
         }
-        __syncthreads();
+        seqs[tid] = s;
     };
     auto for_items = [&](int c0, auto&& f) {      // one wavefront per sequence, one lane per item
+        __syncthreads();
         const int n = min(batch - c0, kListSeqs);
         for (int b = wave; b < n; b += 16) {
             const Seq s = seqs[b];
             for (int i = lane; i < s.n_items; i += 64) f(s, i);
         }
     };
-    int mx = 0;   // heaviest item: the last one of a sequence of query tiles, the first one of a split sequence
-    for (int b = tid; b < batch; b += 1024) {
-        const Seq s = bounds_of(b);
-        mx = max(mx, weight_of(s, is_split(s) ? 0 : max(0, s.n_items - 1)));
-    }
+    int mx = 0;   // heaviest item
+    for (int b = tid; b < batch; b += 1024) mx = max(mx, heaviest_of(bounds_of(b)));
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) mx = max(mx, __shfl_xor(mx, off));
     if (lane == 0) red[wave] = mx;
@@ -401,13 +401,14 @@ __global__ __launch_bounds__(1024) void build_worklist_kernel(const int32_t* __r
 #pragma unroll
     for (int w = 0; w < 16; ++w) mx = max(mx, red[w]);
     const int n_w = mx + 1;
-    auto build = [&](auto* slots) {   // slots[w]: items of weight w, then the list position of the next one
+    auto build = [&](auto* slots) {   // slots[w]: items of weight w (of sequences whose heaviest has it), then the next one's place
         for (int t = tid; t < n_w; t += 1024) slots[t] = 0;
         __syncthreads();
         for (int c0 = 0; c0 < batch; c0 += kListSeqs) {
             if (c0 > 0) __syncthreads();
-            load_seqs(c0, true);
-            for_items(c0, [&](const Seq& s, int i) { atomicAdd(&slots[weight_of(s, i)], 1); });
+            load_seq(c0, true);
+            if (!by_sequence) for_items(c0, [&](const Seq& s, int i) { atomicAdd(&slots[weight_of(s, i)], 1); });
+            else if (c0 + tid < batch) atomicAdd(&slots[heaviest_of(seqs[tid])], seqs[tid].n_items);
         }
         __syncthreads();
         const int total = block_suffix_sum_1024(slots, n_w, red);
@@ -419,11 +420,12 @@ __global__ __launch_bounds__(1024) void build_worklist_kernel(const int32_t* __r
         for (int c0 = 0; c0 < batch; c0 += kListSeqs) {
             if (batch > kListSeqs) {
                 __syncthreads();
-                load_seqs(c0, false);
+                load_seq(c0, false);
             }
+            if (by_sequence && c0 + tid < batch) seqs[tid].pos0 = atomicAdd(&slots[heaviest_of(seqs[tid])], seqs[tid].n_items);
             for_items(c0, [&](const Seq& s, int i) {
-                const int pos = atomicAdd(&slots[weight_of(s, i)], 1);
-                if (pos >= capacity) return;
+                const int pos = !by_sequence ? atomicAdd(&slots[weight_of(s, i)], 1) : s.pos0 + (s.slot0 >= 0 ? i : s.n_items - 1 - i);
+                if ((uint32_t)pos >= (uint32_t)capacity) return;
                 const int r0 = i * group;   // first key range of a split sequence's item
                 work[pos] = s.slot0 >= 0 ? WorkItem{s.q0, 1, s.k0 + r0 * range_len, s.len_k - r0 * range_len, -1, s.slot0 + r0, {0, 0}}
                                          : WorkItem{s.q0, s.len_q, s.k0, s.len_k, i, 0, {0, 0}};

@@ -133,6 +133,17 @@ inline int rows_of_list_call(int cu, int n_q_heads, int n_kv_heads, int64_t batc
     return best;
 }
 
+// Whether a work list keeps the items of a sequence together (true) or orders all items by their own keys (false).  Together,
+// the 32 workgroups of an XCD walk the keys of one sequence at a time and find them in its L2; apart, neighbours belong to as
+// many sequences as there are of about that length, and with 256 prompts of up to 8,192 tokens a tile step took 1.85
+// instead of 1.6 us.  But only items in their own order let the launch end evenly, which counts with few of them per
+// compute unit.  Over 70 random batches, time by items / time by sequence, by items of 256 rows per compute unit: up to 2.5
+// 0.85 ... 1.03, 5 to 8 0.89 ... 1.01, 8 to 14 0.98 ... 1.03, from 15 on never below 1: 1.00 ... 1.08, on average 1.02.
+// 256 prompts with a decode step (181 items per compute unit) 11.11 -> 10.50 ms, with a 65,536-token prompt 37.3 -> 36.8 ms.
+inline bool list_by_sequence(int cu, int n_q_heads, int rows, int64_t batch, int64_t total_q) {
+    return rows == kBM && ((double)total_q / kBM + 0.5 * batch) * n_q_heads >= 16.0 * cu;
+}
+
 // Keys per range when sk keys are cut into n_splits ranges of whole tiles.
 inline int64_t range_keys(int64_t sk, int64_t n_splits, int tile) {
     return std::max<int64_t>(((sk + n_splits - 1) / n_splits + tile - 1) / tile * tile, tile);

@@ -621,8 +621,9 @@ int pec_attn_varlen(const pec_shape_t* shape, const void* q, const void* k, cons
     int32_t* n_work = reinterpret_cast<int32_t*>(ws + cap * sizeof(WorkItem));
     int32_t* bucket = reinterpret_cast<int32_t*>(ws + cap * sizeof(WorkItem) + 256);
     hipStream_t st = static_cast<hipStream_t>(stream);
+    const int by_sequence = list_by_sequence(compute_units(), shape->n_q_heads, rows, batch, total_tokens);
     hipLaunchKernelGGL(build_worklist_kernel, dim3(1), dim3(1024), 0, st, cu_seqlens, cu_seqlens, (int)batch,
-                       (int)total_tokens, (int)total_tokens, rows, rows, 0, 1, capacity, 0, capacity + 1, work, n_work, bucket,
+                       (int)total_tokens, (int)total_tokens, rows, rows, 0, 1, capacity, 0, capacity + 1, by_sequence, work, n_work, bucket,
                        static_cast<SplitSeq*>(nullptr));
     if (hipGetLastError() != hipSuccess) return PEC_ERR_HIP;
 
@@ -702,9 +703,10 @@ int pec_attn_colocated(const pec_shape_t* shape, const void* q, const void* k, c
     float* part_lse = reinterpret_cast<float*>(ws + L.off_part_lse);
     float* part_out = reinterpret_cast<float*>(ws + L.off_part_out);
     hipStream_t st = static_cast<hipStream_t>(stream);
+    const int by_sequence = list_by_sequence(compute_units(), shape->n_q_heads, rows, batch, total_q);
     hipLaunchKernelGGL(build_worklist_kernel, dim3(1), dim3(1024), 0, st, cu_seqlens_q, cu_seqlens_k, (int)batch,
                        (int)total_q, (int)total_k, rows, 256, kColocRange, (int)(shape->n_q_heads / shape->n_kv_heads),
-                       (int)L.cap_items, (int)L.slot_cap, (int)L.n_buckets, work, counters,
+                       (int)L.cap_items, (int)L.slot_cap, (int)L.n_buckets, by_sequence, work, counters,
                        reinterpret_cast<int32_t*>(ws + L.off_bucket), split_seqs);
     if (hipGetLastError() != hipSuccess) return PEC_ERR_HIP;
 

@@ -23,6 +23,9 @@ extern "C" int dense_heads(int cu, int hq, int hkv, int64_t sq, int64_t sk, int6
 extern "C" int list_heads(int cu, int hq, int hkv, int64_t batch, int64_t tq) {
     return 1 << pec::log_heads_of_list_call(cu, hq, hkv, batch, tq);
 }
+extern "C" int by_sequence(int cu, int hq, int rows, int64_t batch, int64_t tq) {
+    return pec::list_by_sequence(cu, hq, rows, batch, tq);
+}
 extern "C" int64_t ranges(int cu, int hq, int hkv, int64_t sk) { return pec::decode_default_ranges(cu, hq, hkv, sk); }
 extern "C" int split(int cu, int hq, int hkv, int64_t sk, int64_t n) { return pec::decode_on_split_kernel(cu, hq, hkv, sk, n); }
 """
@@ -41,6 +44,7 @@ def _lib():
     L.dense_heads.argtypes = L.dense.argtypes
     L.list_heads.argtypes = [ctypes.c_int] * 3 + [i64] * 2
     L.list.argtypes = [ctypes.c_int] * 3 + [i64] * 4 + [ctypes.c_int] * 2
+    L.by_sequence.argtypes = [ctypes.c_int] * 3 + [i64] * 2
     L.ranges.argtypes, L.ranges.restype = [ctypes.c_int] * 3 + [i64], i64
     L.split.argtypes = [ctypes.c_int] * 3 + [i64] * 2
     return L
@@ -60,6 +64,11 @@ def dense_heads(hq, hkv, sq, sk, q_off=0, kv_off=0, causal=True):
 def batch_heads(hq, hkv, len_q):
     """The same for a packed or mixed batch."""
     return _lib().list_heads(COMPUTE_UNITS, hq, hkv, len(len_q), int(sum(len_q)))
+
+
+def by_sequence(hq, rows, len_q):
+    """Whether the work list of a batch keeps the items of a sequence together."""
+    return bool(_lib().by_sequence(COMPUTE_UNITS, hq, rows, len(len_q), int(sum(len_q))))
 
 
 def packed_rows(hq, hkv, lengths, hint=None, causal=True):

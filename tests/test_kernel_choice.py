@@ -6,6 +6,7 @@ import test_gpu_decode_ranges as decode
 import test_gpu_head_tiles as head_tiles
 import test_gpu_pipelined_kernel as pipelined
 import test_gpu_underfilled as underfilled
+import test_gpu_work_list as work_list
 
 
 def cases(test):
@@ -78,3 +79,11 @@ def test_decode_cases_run_on_all_kernels():
 def test_a_dominating_prompt_counts_by_its_own_length():
     lengths = [9622] + [6] * 10 + [3]      # 32-row workgroups took 243 us, these take 197
     assert choice.packed_rows(5, 5, lengths) == 64
+
+
+def test_lists_by_sequence_cases():
+    for hq, hkv, n in cases(work_list.test_lists_by_sequence):
+        len_q = [1] * n + work_list.SEQ_Q       # at least as few queries as the test has
+        assert choice.mixed_rows(hq, hkv, len_q, len_q) == choice.packed_rows(hq, hkv, len_q) == 256
+        assert choice.by_sequence(hq, 256, [1] * n) and not choice.by_sequence(hq, 64, [1] * n)
+    assert not choice.by_sequence(32, 256, [1000] * 29) and choice.by_sequence(32, 256, [1000] * 30)
