@@ -242,7 +242,9 @@ size_t pec_colocated_workspace_bytes(const pec_shape_t* shape, int32_t batch, in
  * by log-sum-exp.  out [1, Hq, 128] in shape->out_dtype and
  * lse [Hq] form a partial pair over this shard: results of several shards / GPUs (the paper's
  * example merges the outputs of two GPUs) combine with pec_attn_merge (use out_dtype PEC_F32).
- * sk == 0 gives out = 0, lse = -inf.  workspace: pec_decode_workspace_bytes() bytes.
+ * sk == 0 gives out = 0, lse = -inf.  workspace: pec_decode_workspace_bytes() bytes, whatever they hold; few ranges are
+ * merged by the launch that makes them, which keeps some words behind the partial results for it (a workspace of
+ * n_splits * n_q_heads * 129 * 4 bytes, without room for them, is taken too and costs a second launch).
  * HBM-bound: K and V are read once, 2 * sk * Hkv * 128 * 2 bytes.
  */
 int pec_decode_splitkv(const pec_shape_t* shape, const void* q, const void* k, const void* v, int64_t sk,
@@ -258,7 +260,7 @@ size_t pec_decode_workspace_bytes(const pec_shape_t* shape, int32_t n_splits);
  * key ranges live in a buffer of PEC_DECODE_STATIC_SCRATCH_BYTES that is part of the library's
  * device image (one copy per GPU, held until the process ends).  The call allocates and frees
  * nothing, on the device or through any library.
- *   Limit: pec_decode_workspace_bytes(shape, n_splits) = n_splits * n_q_heads * 129 * 4 bytes must
+ *   Limit: the partial results, n_splits * n_q_heads * 129 * 4 bytes, must
  *   not exceed PEC_DECODE_STATIC_SCRATCH_BYTES (e.g. 128 key ranges x 64 query heads = 4.2 MB);
  *   beyond it the call returns PEC_ERR_SCRATCH_LIMIT and launches nothing.
  *   The first call on a device looks up the buffer's device address (hipGetSymbolAddress); make that
@@ -266,7 +268,7 @@ size_t pec_decode_workspace_bytes(const pec_shape_t* shape, int32_t n_splits);
  *   Every call on a GPU uses that GPU's one buffer: two calls that overlap in time on the same GPU
  *   (different streams, different threads) race on it and give undefined results.  Calls on one
  *   stream, or otherwise ordered, are safe; nothing in the buffer needs clearing between calls
- *   (every partial a call reads it has written itself).
+ *   (every partial a call reads it has written itself, and the words that say so are new for every call).
  */
 #define PEC_DECODE_STATIC_SCRATCH_BYTES ((size_t)8 << 20)
 int pec_decode_splitkv_static(const pec_shape_t* shape, const void* q, const void* k, const void* v, int64_t sk,

@@ -162,23 +162,27 @@ __global__ __launch_bounds__(kCombineThreads) void combine_splits_kernel(const f
     combine_one_head<OUT_F32>(o_part, lse_part, n_splits, n_heads, h, out_row, lse + h);
 }
 
-// The same for up to kCombineFew ranges by one wavefront per head, without LDS or barriers: lane i holds the weight of range
-// i, each half of the wavefront sums every second range, all loads in flight at once.  With so few ranges the kernel above
-// is made of the trips between its sixteen wavefronts.  GPU time of a decode step of 32 heads with ranges of 32 keys, that /
-// this: 1 range 8.0 / 7.0 us, 8 ranges 8.1 / 7.6, 16 ranges 8.6 / 8.3, 24 ranges 8.65 / 8.61, 32 ranges 8.84 / 8.92.
-constexpr int kCombineFew = 24;
-template <bool OUT_F32>
-__global__ __launch_bounds__(64) void combine_few_kernel(const float* __restrict__ o_part, const float* __restrict__ lse_part,
-                                                         int n_splits, int n_heads, void* __restrict__ out,
-                                                         float* __restrict__ lse) {
-    const int h = blockIdx.x, lane = threadIdx.x, half = lane >> 5, c = lane & 31;
-    const float l = lane < n_splits ? lse_part[(int64_t)lane * n_heads + h] : -INFINITY;
-    f32x4 x[kCombineFew / 2];
+// The same for up to N ranges by one wavefront, without LDS or barriers: lane i holds the weight of range i, each half of the
+// wavefront sums every second range, all loads in flight at once.  SHARED: the ranges come from this launch (load_shared()).
+template <int N, bool SHARED>
+__device__ __forceinline__ void combine_few(const float* o_part, const float* lse_part, int n_splits, int n_heads, int h,
+                                            void* out, bool out_f32, float* lse) {
+    static_assert(N <= 32, "the ranges' weights sit in the lower half of the wavefront");
+    const int lane = threadIdx.x & 63, half = lane >> 5, c = lane & 31;
+    float l = -INFINITY;
+    if (lane < n_splits) {
+        const float* const src = lse_part + (int64_t)lane * n_heads + h;
+        l = SHARED ? __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *src;
+    }
+    f32x4 x[N / 2];
 #pragma unroll
-    for (int i = 0; i < kCombineFew / 2; ++i) {
+    for (int i = 0; i < N / 2; ++i) {
         x[i] = f32x4{0.f, 0.f, 0.f, 0.f};
         const int s = 2 * i + half;
-        if (s < n_splits) x[i] = *reinterpret_cast<const f32x4*>(o_part + ((int64_t)s * n_heads + h) * kHeadDim + 4 * c);
+        if (s < n_splits) {
+            const float* const src = o_part + ((int64_t)s * n_heads + h) * kHeadDim + 4 * c;
+            x[i] = SHARED ? load_shared(src) : *reinterpret_cast<const f32x4*>(src);
+        }
     }
     float mx = l;
 #pragma unroll
@@ -191,7 +195,7 @@ __global__ __launch_bounds__(64) void combine_few_kernel(const float* __restrict
     den = __shfl(den, 0);
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < kCombineFew / 2; ++i) {
+    for (int i = 0; i < N / 2; ++i) {
         if (2 * i >= n_splits) break;
         const float ws = __shfl(w, 2 * i + half);
 #pragma unroll
@@ -203,12 +207,22 @@ __global__ __launch_bounds__(64) void combine_few_kernel(const float* __restrict
         if (mx != -INFINITY) acc[e] /= den;
     }
     if (half == 0) {
-        if constexpr (OUT_F32)
+        if (out_f32)
             *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(out) + (int64_t)h * kHeadDim + 4 * c) = acc;
         else
             *reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(out) + (int64_t)h * kHeadDim + 4 * c) = __builtin_convertvector(acc, bf16x4);
         if (c == 0) lse[h] = mx != -INFINITY ? mx + logf(den) : -INFINITY;
     }
+}
+
+// As a kernel, one wavefront per head: with few ranges combine_splits_kernel is made of the trips between its sixteen
+// wavefronts.  GPU time of a decode step of 32 heads with ranges of 32 keys, that / this: 1 range 8.0 / 7.0 us, 8 ranges
+// 8.1 / 7.6, 16 ranges 8.6 / 8.3, 24 ranges 8.65 / 8.61, 32 ranges 8.84 / 8.92.
+constexpr int kCombineFew = 24;
+template <bool OUT_F32>
+__global__ __launch_bounds__(64) void combine_few_kernel(const float* o_part, const float* lse_part, int n_splits, int n_heads,
+                                                         void* out, float* lse) {
+    combine_few<kCombineFew, false>(o_part, lse_part, n_splits, n_heads, blockIdx.x, out, OUT_F32, lse);
 }
 
 // The same combination for the one-token sequences of a colocated batch: split_seqs lists

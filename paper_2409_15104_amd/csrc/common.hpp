@@ -78,8 +78,14 @@ struct FwdParams {
     // [item * kv_split_len, ...), partial results go to out / lse + item * split_*_stride
     int32_t kv_split_len;
     int64_t split_out_stride, split_lse_stride;   // elements
+    // key ranges of a decode step whose last workgroup per KV head merges them (fwd_split_kernel; null: a kernel of its own
+    // does): per KV head an epoch and one word per range (last_workgroup()), and where the results go
+    uint64_t* arrived;
+    void* merged_out;
+    float* merged_lse;
+    int32_t merged_f32;
     // element strides of q / out / acc between rows and between heads (0 = the packed
-    // [tokens, n_q_heads, 128] layout; not in fwd_simple_kernel, and fwd_split_kernel reads them in split-KV mode only)
+    // [tokens, n_q_heads, 128] layout; not in fwd_simple_kernel, and fwd_split_kernel reads them for decode steps only)
     int64_t q_row_stride, q_head_stride;
     // colocated batch: partial results of the key ranges that one-token sequences with long caches are cut into
     float* part_out;            // [slots][n_q_heads][128] fp32
@@ -149,6 +155,27 @@ __device__ __forceinline__ void dma16(const unsigned char* sbase, uint32_t voff,
                      : "+s"(sbase)
                      : "v"(voff), "s"(lds_addr)
                      : "memory", "m0");
+}
+
+// Results that one workgroup writes and another one of the same launch reads, maybe on another XCD: accesses at device scope
+// go past the L2 that would keep them, so that no cache needs to be written back or invalidated (a __threadfence on
+// either side does that to the whole L2: a decode step of 4,096 keys took 28 instead of 10 us with them).  Stores are in
+// place when the wavefront's vmcnt is zero.
+__device__ __forceinline__ void store_shared(float* p, f32x4 x) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        __hip_atomic_store(reinterpret_cast<uint64_t*>(p) + i, __builtin_bit_cast(uint64_t, f32x2{x[2 * i], x[2 * i + 1]}),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ f32x4 load_shared(const float* p) {
+    f32x4 x;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const f32x2 y = __builtin_bit_cast(f32x2, __hip_atomic_load(reinterpret_cast<const uint64_t*>(p) + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        x[2 * i] = y[0];
+        x[2 * i + 1] = y[1];
+    }
+    return x;
 }
 
 __device__ __forceinline__ uint32_t k_lds_off(int key, int chunk16) {

@@ -29,6 +29,7 @@
 
 #include <type_traits>
 
+#include "aux_kernels.hpp"
 #include "common.hpp"
 
 namespace pec {
@@ -37,10 +38,49 @@ constexpr int kSplitWaves = 8;                              // key streams
 constexpr int kSplitTile = 32;                              // keys per tile
 constexpr int kSplitTileBytes = kSplitTile * kRowBytes;     // 8 KiB for K, 8 KiB for V
 
-// LIST: work items of a packed or colocated batch (device-built list of bm = 32 * NT rows per item) instead of the
-// query tiles of one call.
-template <int NT, bool LIST>
+// Merge of a decode step's key ranges in the launch that makes them, by whichever workgroup of a KV head finds that all of
+// its ranges are there: every workgroup writes its partial results, then its word, then reads the words of all ranges; of
+// the workgroups that do so last, at least one sees them all (several may: they write the same results).  A word says
+// "there" by holding arrived_mark() of the epoch, which every workgroup read when it started and which one that saw them
+// all raises by one: nothing needs clearing before or after a call, whatever the memory held (64 mixed bits, different for
+// every epoch, KV head and number of ranges, so that neither other data nor an earlier call's words pass for the mark).
+constexpr int kMergeRanges = 32;       // most ranges that one wavefront merges
+__device__ __forceinline__ uint64_t arrived_mark(uint64_t epoch, int kvh, int n_ranges) {
+    uint64_t x = epoch + 0x9e3779b97f4a7c15ull * (uint64_t)(kvh * (kMergeRanges + 1) + n_ranges);   // the splitmix64 mixer
+    x = (x ^ (x >> 30)) * 0xbf58476d1ce4e5b9ull;
+    x = (x ^ (x >> 27)) * 0x94d049bb133111ebull;
+    return x ^ (x >> 31);
+}
+
+// Called by all wavefronts of a workgroup behind its stores; `range`: its key range, `words`: epoch and words of its KV head.
+__device__ __forceinline__ bool last_workgroup(uint64_t* words, uint64_t epoch, uint64_t mark, int range, int n_ranges, int wave) {
+    __shared__ int all_there;
+    __builtin_amdgcn_s_waitcnt(0x0F70);    // vmcnt 0: this wavefront's results (store_shared()) are in place
+    asm volatile("" ::: "memory");
+    __syncthreads();
+    if (wave == 0) {
+        const int lane = threadIdx.x & 63;
+        if (lane == 0) __hip_atomic_store(words + 1 + range, mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_s_waitcnt(0x0F70);    // the word is in place before the others are read
+        asm volatile("" ::: "memory");
+        const bool there = lane >= n_ranges || __hip_atomic_load(words + 1 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == mark;
+        const bool all = __all(there);
+        if (lane == 0) {
+            all_there = all;
+            if (all) __hip_atomic_store(words, epoch + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    __syncthreads();
+    return all_there;
+}
+
+// What a launch works on: the query tiles of one call, the items of a packed or colocated batch (a device-built list of
+// bm = 32 * NT rows per item), or the key ranges of a decode step.
+enum { kSplitDense = 0, kSplitList = 1, kSplitDecode = 2 };
+template <int NT, int MODE>
 __global__ __launch_bounds__(kSplitWaves * 64, 2) void fwd_split_kernel(const FwdParams p) {
+    constexpr bool LIST = MODE == kSplitList;
+    constexpr bool DECODE = MODE == kSplitDecode;
     constexpr int KS = kSplitWaves;
     constexpr int BM = 32 * NT;
     constexpr int LOADS = 8;                 // load instructions (1 KiB each) per matrix and tile
@@ -72,7 +112,19 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void fwd_split_kernel(const Fw
     void* out_ptr = p.out;
     float* lse_ptr = p.lse;
     int out_f32 = p.out_f32;
-    if constexpr (LIST) {
+    uint64_t epoch = 0;
+    if constexpr (DECODE) {   // the item is a key range, all of it visible; the heads of a KV group are the rows
+        if (p.arrived && wave == 0) epoch = __hip_atomic_load(p.arrived + (int64_t)kvh * (n_items + 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        qt = 0;
+        sq = p.sq;
+        q_stride = p.q_row_stride;
+        q_off0 = o_off0 = (int64_t)head * p.q_head_stride;
+        lse_off0 = (int64_t)head * p.lse_stride;
+        kv_tok0 = (int64_t)item * p.kv_split_len;
+        sk = delta = (int)max((int64_t)0, min((int64_t)p.kv_split_len, (int64_t)p.sk - kv_tok0));
+        o_off0 += item * p.split_out_stride;
+        lse_off0 += item * p.split_lse_stride;
+    } else if constexpr (LIST) {
         const WorkItem w = p.work[item];
         sk = w.len_k;
         kv_tok0 = w.k0;
@@ -107,17 +159,8 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void fwd_split_kernel(const Fw
         qt = p.causal ? (n_items - 1 - item) : item;
         q_off0 = o_off0 = (int64_t)head * kHeadDim;
         lse_off0 = (int64_t)head * p.lse_stride;
-        if (p.kv_split_len > 0) {   // decode: the item is a key range, all of it visible; the heads of a KV group are the rows
-            qt = 0;
-            q_stride = p.q_row_stride;
-            q_off0 = o_off0 = (int64_t)head * p.q_head_stride;
-            kv_tok0 = (int64_t)item * p.kv_split_len;
-            sk = (int)max((int64_t)0, min((int64_t)p.kv_split_len, (int64_t)p.sk - kv_tok0));
-            o_off0 += item * p.split_out_stride;
-            lse_off0 += item * p.split_lse_stride;
-        }
     }
-    const int causal = p.causal;
+    const int causal = DECODE ? 0 : p.causal;
     const int row0 = qt * BM;
     int kv_end = sk;
     if (causal) kv_end = max(0, min(sk, min(sq, row0 + BM) + delta));
@@ -156,7 +199,7 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void fwd_split_kernel(const Fw
 #pragma unroll
             for (int r = 0; r < 16; ++r) o[nt][dt][r] = 0.f;
         const int row = row0 + nt * 32 + l32;
-        if (!LIST && p.acc_in && wave == 0 && row < sq) {
+        if (MODE == kSplitDense && p.acc_in && wave == 0 && row < sq) {
             const float lin = p.lse_in[lse_off0 + row];
             if (lin != -INFINITY) {
                 m_run[nt] = lin * kLog2e;
@@ -362,8 +405,11 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void fwd_split_kernel(const Fw
             const float inv = den > 0.f ? 1.f / den : 0.f;
             lds_w[k * 32 + r] = __builtin_amdgcn_exp2f(lds_m[k * 32 + r] - m_use) * inv;
             const int row = row0 + nt * 32 + r;
-            if (k == 0 && row < sq)
-                lse_ptr[lse_off0 + row] = den > 0.f ? (mx + __builtin_amdgcn_logf(den)) * kLn2 : -INFINITY;
+            if (k == 0 && row < sq) {
+                const float lse = den > 0.f ? (mx + __builtin_amdgcn_logf(den)) * kLn2 : -INFINITY;
+                if (DECODE) __hip_atomic_store(lse_ptr + lse_off0 + row, lse, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                else lse_ptr[lse_off0 + row] = lse;
+            }
         }
         __syncthreads();
         const int c = threadIdx.x & 31;
@@ -381,15 +427,25 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void fwd_split_kernel(const Fw
             }
             if (row < sq) {
                 const int64_t idx = o_off0 + row * q_stride + 4 * c;
-                if (!LIST && p.acc_out) *reinterpret_cast<f32x4*>(p.acc_out + idx) = a;
+                if (MODE == kSplitDense && p.acc_out) *reinterpret_cast<f32x4*>(p.acc_out + idx) = a;
                 if (out_ptr) {
-                    if (out_f32)
+                    if (DECODE && p.arrived)
+                        store_shared(reinterpret_cast<float*>(out_ptr) + idx, a);
+                    else if (out_f32)
                         *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(out_ptr) + idx) = a;
                     else
                         *reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(out_ptr) + idx) = __builtin_convertvector(a, bf16x4);
                 }
             }
         }
+    }
+    if constexpr (DECODE) {
+        if (!p.arrived || !last_workgroup(p.arrived + (int64_t)kvh * (n_items + 1), epoch, arrived_mark(epoch, kvh, n_items), item, n_items, wave))
+            return;
+        const int n_heads = p.n_kv_heads * sq;
+        for (int h = wave; h < sq; h += KS)
+            combine_few<kMergeRanges, true>(static_cast<const float*>(p.out), p.lse, n_items, n_heads, kvh * sq + h, p.merged_out,
+                                      p.merged_f32, p.merged_lse);
     }
 }
 

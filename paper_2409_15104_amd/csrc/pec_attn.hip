@@ -82,13 +82,13 @@ int launch_fwd(const FwdParams& p, bool simple, int rows, hipStream_t stream) {
     else if (rows == kBM)
         launch_il(p, (unsigned)grid, stream);
     else if (rows == 64 && p.work)
-        hipLaunchKernelGGL((fwd_split_kernel<2, true>), blocks, threads, 0, stream, p);
+        hipLaunchKernelGGL((fwd_split_kernel<2, kSplitList>), blocks, threads, 0, stream, p);
     else if (rows == 64)
-        hipLaunchKernelGGL((fwd_split_kernel<2, false>), blocks, threads, 0, stream, p);
+        hipLaunchKernelGGL((fwd_split_kernel<2, kSplitDense>), blocks, threads, 0, stream, p);
     else if (p.work)
-        hipLaunchKernelGGL((fwd_split_kernel<1, true>), blocks, threads, 0, stream, p);
+        hipLaunchKernelGGL((fwd_split_kernel<1, kSplitList>), blocks, threads, 0, stream, p);
     else
-        hipLaunchKernelGGL((fwd_split_kernel<1, false>), blocks, threads, 0, stream, p);
+        hipLaunchKernelGGL((fwd_split_kernel<1, kSplitDense>), blocks, threads, 0, stream, p);
     return hipGetLastError() == hipSuccess ? PEC_OK : PEC_ERR_HIP;
 }
 
@@ -397,6 +397,24 @@ int pec_sp_prefill_step(const pec_shape_t* shape, const void* q, const void* k, 
                       s_q, stream);
 }
 
+}  // extern "C"
+
+namespace {
+
+// A decode step's workspace: the fp32 partial O and LSE of every (range, query head), then, for the merge by the last
+// workgroup of each KV head, an epoch and a word per range.  Workspaces without these words do too: two launches then.
+size_t decode_partial_bytes(const pec_shape_t* shape, int32_t n_splits) {
+    return (size_t)n_splits * shape->n_q_heads * (kHeadDim + 1) * sizeof(float);
+}
+size_t decode_words_offset(const pec_shape_t* shape, int32_t n_splits) { return (decode_partial_bytes(shape, n_splits) + 7) & ~(size_t)7; }
+size_t decode_words_bytes(const pec_shape_t* shape, int32_t n_splits) {
+    return n_splits > kMergeRanges ? 0 : (size_t)std::max(0, shape->n_kv_heads) * (n_splits + 1) * sizeof(uint64_t);
+}
+
+}  // namespace
+
+extern "C" {
+
 int32_t pec_decode_default_splits(const pec_shape_t* shape, int64_t sk) {
     if (!shape || shape->n_kv_heads <= 0 || sk <= 0) return 1;
     return (int32_t)decode_default_ranges(compute_units(), shape->n_q_heads, shape->n_kv_heads, sk);
@@ -404,7 +422,7 @@ int32_t pec_decode_default_splits(const pec_shape_t* shape, int64_t sk) {
 
 size_t pec_decode_workspace_bytes(const pec_shape_t* shape, int32_t n_splits) {
     if (!shape || shape->n_q_heads <= 0 || n_splits <= 0) return 0;
-    return (size_t)n_splits * shape->n_q_heads * (kHeadDim + 1) * sizeof(float);
+    return decode_words_offset(shape, n_splits) + decode_words_bytes(shape, n_splits);
 }
 
 }  // extern "C"
@@ -414,7 +432,9 @@ namespace {
 // Scratch of pec_decode_splitkv_static: the fp32 partial (O, LSE) of every (key range, query head).
 // One copy per GPU, held until the process ends; its device address is looked up once per device.
 static_assert(PEC_DECODE_STATIC_SCRATCH_BYTES == (size_t)kStaticScratchBytes, "the default range count reckons with it");
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+// Behind the partials the words of the merge, for as many ranges and KV heads as fwd_split_kernel takes on any device.
+constexpr size_t kStaticWords = 1024;
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + 2 * kStaticWords * sizeof(uint64_t)];
 
 int static_scratch(void** out) {
     static void* ptr[64] = {nullptr};
@@ -431,15 +451,17 @@ int static_scratch(void** out) {
     return PEC_OK;
 }
 
-// Common body of the two decode entry points; `workspace` holds pec_decode_workspace_bytes(shape, n_splits) bytes.
+// Common body of the two decode entry points; `workspace` holds the partial results, `words`, if any, the words of the merge.
 int decode_impl(const pec_shape_t* shape, float scale, const void* q, const void* k, const void* v, int64_t sk,
-                int32_t n_splits, void* out, float* lse, void* workspace, void* stream) {
+                int32_t n_splits, void* out, float* lse, void* workspace, void* words, void* stream) {
     const int g = shape->n_q_heads / shape->n_kv_heads;
     float* o_part = static_cast<float*>(workspace);
     float* lse_part = o_part + (size_t)n_splits * shape->n_q_heads * kHeadDim;
     hipStream_t st = static_cast<hipStream_t>(stream);
 
     const bool split = decode_on_split_kernel(compute_units(), shape->n_q_heads, shape->n_kv_heads, sk, n_splits);
+    const bool f32 = shape->out_dtype == PEC_F32;
+    bool merged = false;
     if (g <= 32 && !split) {   // one key range per wavefront (decode_kernel.hpp)
         DecodeParams d{};
         d.q = static_cast<const __bf16*>(q);
@@ -485,13 +507,26 @@ int decode_impl(const pec_shape_t* shape, float scale, const void* q, const void
     p.q_row_stride = kHeadDim;
     p.q_head_stride = (int64_t)g * kHeadDim;
     const int64_t total = (int64_t)n_splits * shape->n_kv_heads;
+    if (split && n_splits == 1) {      // nothing to merge
+        p.out = out;
+        p.lse = lse;
+        p.out_f32 = f32;
+        merged = true;
+    } else if (split && words && n_splits <= kMergeRanges && merge_in_launch(g, n_splits)) {
+        p.arrived = static_cast<uint64_t*>(words);
+        p.merged_out = out;
+        p.merged_lse = lse;
+        p.merged_f32 = f32;
+        merged = true;
+    }
     if (split)
-        hipLaunchKernelGGL((fwd_split_kernel<1, false>), dim3((unsigned)(((total + 7) / 8) * 8)), dim3(kSplitWaves * 64), 0, st, p);
+        hipLaunchKernelGGL((fwd_split_kernel<1, kSplitDecode>), dim3((unsigned)(((total + 7) / 8) * 8)), dim3(kSplitWaves * 64), 0, st, p);
     else
         launch_il(p, (unsigned)(((total + 7) / 8) * 8), st);
     if (hipGetLastError() != hipSuccess) return PEC_ERR_HIP;
     }
-    const bool few = n_splits <= kCombineFew, f32 = shape->out_dtype == PEC_F32;
+    if (merged) return PEC_OK;
+    const bool few = n_splits <= kCombineFew;
     auto* const merge = few ? (f32 ? combine_few_kernel<true> : combine_few_kernel<false>)
                             : (f32 ? combine_splits_kernel<true> : combine_splits_kernel<false>);
     hipLaunchKernelGGL(merge, dim3(shape->n_q_heads), dim3(few ? 64 : kCombineThreads), 0, st, o_part, lse_part, (int)n_splits,
@@ -514,8 +549,10 @@ int pec_decode_splitkv(const pec_shape_t* shape, const void* q, const void* k, c
         return PEC_ERR_MISALIGNED;
     if (n_splits == 0) n_splits = pec_decode_default_splits(shape, sk);
     if (shape->n_q_heads / shape->n_kv_heads > 256) return PEC_ERR_UNSUPPORTED;
-    if (!workspace || workspace_bytes < pec_decode_workspace_bytes(shape, n_splits)) return PEC_ERR_WORKSPACE;
-    return decode_impl(shape, scale, q, k, v, sk, n_splits, out, lse, workspace, stream);
+    if (!workspace || workspace_bytes < decode_partial_bytes(shape, n_splits)) return PEC_ERR_WORKSPACE;
+    char* const words = static_cast<char*>(workspace) + decode_words_offset(shape, n_splits);
+    const bool room = workspace_bytes >= pec_decode_workspace_bytes(shape, n_splits);
+    return decode_impl(shape, scale, q, k, v, sk, n_splits, out, lse, workspace, room ? words : nullptr, stream);
 }
 
 int pec_decode_splitkv_static(const pec_shape_t* shape, const void* q, const void* k, const void* v, int64_t sk,
@@ -528,10 +565,12 @@ int pec_decode_splitkv_static(const pec_shape_t* shape, const void* q, const voi
     if (misaligned(q) || misaligned(k) || misaligned(v) || misaligned(out)) return PEC_ERR_MISALIGNED;
     if (n_splits == 0) n_splits = pec_decode_default_splits(shape, sk);
     if (shape->n_q_heads / shape->n_kv_heads > 256) return PEC_ERR_UNSUPPORTED;
-    if (pec_decode_workspace_bytes(shape, n_splits) > kStaticScratchBytes) return PEC_ERR_SCRATCH_LIMIT;
+    if (decode_partial_bytes(shape, n_splits) > (size_t)kStaticScratchBytes) return PEC_ERR_SCRATCH_LIMIT;
     void* ws = nullptr;
     if (int rc = static_scratch(&ws)) return rc;
-    return decode_impl(shape, scale, q, k, v, sk, n_splits, out, lse, ws, stream);
+    char* const words = static_cast<char*>(ws) + kStaticScratchBytes;
+    const bool room = decode_words_bytes(shape, n_splits) <= 2 * kStaticWords * sizeof(uint64_t);
+    return decode_impl(shape, scale, q, k, v, sk, n_splits, out, lse, ws, room ? words : nullptr, stream);
 }
 
 int pec_ulysses_layout(const void* src, void* dst, int64_t s, int32_t n_heads, int32_t head_dim, int32_t n_gpus,

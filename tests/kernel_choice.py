@@ -26,6 +26,7 @@ extern "C" int list_heads(int cu, int hq, int hkv, int64_t batch, int64_t tq) {
 extern "C" int by_sequence(int cu, int hq, int rows, int64_t batch, int64_t tq) {
     return pec::list_by_sequence(cu, hq, rows, batch, tq);
 }
+extern "C" int merged(int g, int64_t n) { return pec::merge_in_launch(g, n); }
 extern "C" int64_t ranges(int cu, int hq, int hkv, int64_t sk) { return pec::decode_default_ranges(cu, hq, hkv, sk); }
 extern "C" int split(int cu, int hq, int hkv, int64_t sk, int64_t n) { return pec::decode_on_split_kernel(cu, hq, hkv, sk, n); }
 """
@@ -45,6 +46,7 @@ def _lib():
     L.list_heads.argtypes = [ctypes.c_int] * 3 + [i64] * 2
     L.list.argtypes = [ctypes.c_int] * 3 + [i64] * 4 + [ctypes.c_int] * 2
     L.by_sequence.argtypes = [ctypes.c_int] * 3 + [i64] * 2
+    L.merged.argtypes = [ctypes.c_int, i64]
     L.ranges.argtypes, L.ranges.restype = [ctypes.c_int] * 3 + [i64], i64
     L.split.argtypes = [ctypes.c_int] * 3 + [i64] * 2
     return L
@@ -78,6 +80,11 @@ def packed_rows(hq, hkv, lengths, hint=None, causal=True):
 
 def mixed_rows(hq, hkv, len_q, len_k, causal=True):
     return _lib().list(COMPUTE_UNITS, hq, hkv, len(len_q), int(sum(len_q)), int(sum(len_k)), 0, int(causal), COLOC_RANGE)
+
+
+def merged_in_launch(hq, hkv, sk, n_splits):
+    """Whether a decode step of so many ranges is one launch."""
+    return bool(decode_kernel_of(hq, hkv, sk, n_splits)[1] == "fwd_split_kernel" and n_splits <= 32 and _lib().merged(hq // hkv, n_splits))
 
 
 def decode_kernel_of(hq, hkv, sk, n_splits):

@@ -37,3 +37,39 @@ def test_decode_ranges_match_oracle(sk, hq, hkv, n_splits):
         lse = torch.full((hq,), float("nan"), dtype=torch.float32, device=DEV)
         pec.pec_decode_splitkv(q.to(DEV), k.to(DEV), v.to(DEV), n_splits=n_splits, out_dtype=dt, out=out, lse=lse)
         assert_close(out, lse.reshape(hq, 1), o_ref, l_ref, "%s" % dt)
+
+
+@pytest.mark.parametrize("hq,hkv,n", [(8, 8, 2), (8, 8, 32), (8, 8, 33), (64, 32, 8), (64, 2, 2), (66, 2, 2), (6, 2, 21), (6, 2, 22), (33, 33, 7)])
+def test_merge_in_the_launch(hq, hkv, n):
+    """Ranges merged by the workgroup that is there last, on either side of its limits, against the merge by a second launch
+    (a workspace without room for its words): the same bits for up to 24 ranges, which that one sums in the same order.  One
+    workspace, filled with different bytes and used by steps of other shapes in between, and a graph replayed over it."""
+    sk = n * 96 - 37
+    q, k, v = [t.to(DEV) for t in synth.qkv(8500 + hq + n, 1, sk, hq, hkv)]
+    o_ref, l_ref = oracle.attention(q.cpu(), k.cpu(), v.cpu(), causal=False)
+    q2, k2, v2 = [t.to(DEV) for t in synth.qkv(8600, 1, 700, 8, 4)]
+    ws = torch.empty(1 << 20, dtype=torch.uint8, device=DEV)
+    partials = n * hq * 129 * 4
+    two = pec.pec_decode_splitkv(q, k, v, n_splits=n, workspace=ws[:partials])
+    out, lse = torch.empty_like(two[0]), torch.empty_like(two[1])
+
+    def check(what):
+        torch.cuda.synchronize()
+        assert_close(out, lse.reshape(hq, 1), o_ref, l_ref, what)
+        assert n > 24 or (torch.equal(out, two[0]) and torch.equal(lse, two[1])), what
+        out.fill_(float("nan"))
+        lse.fill_(float("nan"))
+
+    for fill in (0, 255, 90):
+        ws.fill_(fill)
+        for again in range(3):
+            pec.pec_decode_splitkv(q, k, v, n_splits=n, out=out, lse=lse, workspace=ws)
+            check((fill, again))
+            pec.pec_decode_splitkv(q2, k2, v2, n_splits=2 + again, workspace=ws)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        pec.pec_decode_splitkv(q, k, v, n_splits=n, out=out, lse=lse, workspace=ws)
+    for again in range(3):
+        graph.replay()
+        check(again)
+        pec.pec_decode_splitkv(q2, k2, v2, n_splits=3, workspace=ws)

@@ -87,3 +87,8 @@ def test_lists_by_sequence_cases():
         assert choice.mixed_rows(hq, hkv, len_q, len_q) == choice.packed_rows(hq, hkv, len_q) == 256
         assert choice.by_sequence(hq, 256, [1] * n) and not choice.by_sequence(hq, 64, [1] * n)
     assert not choice.by_sequence(32, 256, [1000] * 29) and choice.by_sequence(32, 256, [1000] * 30)
+
+
+def test_merge_in_the_launch_cases():
+    got = [choice.merged_in_launch(hq, hkv, n * 96 - 37, n) for hq, hkv, n in cases(decode.test_merge_in_the_launch)]
+    assert got == [True, True, False, True, True, False, True, False, True]
