@@ -284,9 +284,10 @@ def main():
 
 def attention_kernel(torch, pec, args, dev, n_q_heads, rows):
     """Kernel of one ring member's launches.  Of the workloads here only the 512-row members have fewer than 256 rows per
-    compute unit; as calls that cannot be stopped they run on the kernel that shares the keys out among wavefronts."""
+    compute unit; they run on the kernel that shares the keys out among wavefronts (as stoppable sweeps too: segments of
+    under 1024 keys leave nothing to stop at)."""
     underfilled = rows * n_q_heads < 256 * torch.cuda.get_device_properties(dev).multi_processor_count
-    return "pec::fwd_split_kernel" if underfilled and args.kernel_flag == 0 and args.sp_mode != "resumable" else \
+    return "pec::fwd_split_kernel" if underfilled and args.kernel_flag == 0 else \
         pec.KERNEL_NAMES[args.kernel_flag]
 
 

@@ -144,6 +144,28 @@ inline bool list_by_sequence(int cu, int n_q_heads, int rows, int64_t batch, int
     return rows == kBM && ((double)total_q / kBM + 0.5 * batch) * n_q_heads >= 16.0 * cu;
 }
 
+// Whether a stop word can change what a launch of the resumable sweep does.  fwd_il_kernel leaves an item ahead of a segment
+// boundary inside the keys that none of the item's 256 rows has masked (segments of 16 tiles and more; the last whole query
+// tile sees most), and a workgroup leaves out every item but its first.  Where neither can happen the sweep is a plain call
+// and runs on whatever kernel that takes.  Microseconds per call, sweep kernel / plain, 8 query heads: 704 rows x 1408 keys
+// 35.8 / 13.7, 448 x 448 18.8 / 9.9, 3328 x 3328 (segments of 3328) 71.7 / 37.2; 256 x 512 of 4 heads 21.3 / 10.2, 256 x 1024 of
+// 64 heads 30.9 / 17.6.
+inline bool sweep_can_stop(int cu, int n_q_heads, int64_t sq, int64_t sk, int64_t delta, bool causal, int64_t seg_tiles) {
+    const int64_t items = (sq + kBM - 1) / kBM * n_q_heads;
+    if ((items + 7) / 8 > std::max(1, cu / 8)) return true;      // a workgroup has more than one item
+    if (seg_tiles < 16 || sq < kBM) return false;
+    const int64_t row0 = sq / kBM * kBM - kBM, tile = 64;
+    int64_t whole = sk / tile, tiles = (sk + tile - 1) / tile, seen = tiles;   // tiles that all rows / any row / the first 32 see
+    if (causal) {
+        const int64_t keys = std::max<int64_t>(0, std::min(sk, row0 + kBM + delta));
+        tiles = (keys + tile - 1) / tile;
+        whole = std::min(whole, std::max<int64_t>(0, row0 + delta + 1) / tile);
+        seen = std::min(tiles, std::max<int64_t>(0, row0 + 31 + delta + tile) / tile);
+    }
+    const int64_t last = std::min(std::max<int64_t>(0, std::min(whole, seen) - 1) & ~(int64_t)1, tiles - 1);
+    return seg_tiles <= last;
+}
+
 // Keys per range when sk keys are cut into n_splits ranges of whole tiles.
 inline int64_t range_keys(int64_t sk, int64_t n_splits, int tile) {
     return std::max<int64_t>(((sk + n_splits - 1) / n_splits + tile - 1) / tile * tile, tile);

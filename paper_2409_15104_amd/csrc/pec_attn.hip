@@ -332,11 +332,20 @@ int pec_sp_prefill_resumable(const pec_shape_t* shape, const void* q, const void
     const size_t l_bytes = (((size_t)s_q * shape->n_q_heads * 2 * sizeof(float)) + 255) & ~(size_t)255;
     float* l_part = s_q > 0 ? reinterpret_cast<float*>(static_cast<char*>(workspace) + o_bytes) : nullptr;
     int32_t* progress = s_q > 0 ? reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + o_bytes + l_bytes) : nullptr;
-    if (!resume || s_q == 0) {
-        hipLaunchKernelGGL(sweep_init_kernel, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>((items + 255) / 256, 1024))),
-                           dim3(256), 0, st, progress, items, pending);
-        if (hipGetLastError() != hipSuccess) return PEC_ERR_HIP;
+    auto set_table = [&](int32_t done) {
+        hipLaunchKernelGGL(sweep_table_kernel, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>((items + 255) / 256, 1024))),
+                           dim3(256), 0, st, progress, items, pending, done);
+        return hipGetLastError() == hipSuccess ? PEC_OK : PEC_ERR_HIP;
+    };
+    const int64_t delta = std::max<int64_t>(-s_q - 1, std::min<int64_t>(q_off, s_kv));      // as in chunk_impl
+    if (s_q > 0 && !resume && !sweep_can_stop(compute_units(), shape->n_q_heads, s_q, s_kv, delta, causal != 0, chunk / kBN)) {
+        if (int rc = chunk_impl(shape, q, k, v, s_q, s_kv, q_off, 0, causal, out, shape->out_dtype == PEC_F32, lse, nullptr, nullptr,
+                                nullptr, s_q, stream))
+            return rc;
+        return set_table(1);      // (a call that resumes such a sweep finds everything done)
     }
+    if (!resume || s_q == 0)
+        if (int rc = set_table(0)) return rc;
     if (s_q == 0) return PEC_OK;
     const Sweep sweep{l_part, progress, pending, stop, (int32_t)(chunk / kBN)};
     return chunk_impl(shape, q, k, v, s_q, s_kv, q_off, 0, causal, out, shape->out_dtype == PEC_F32, lse, o_acc, lse, o_acc,

@@ -1,10 +1,13 @@
 """The GPU tests that are about one kernel run on it: the library's own choice, asked for the sizes that they use."""
+import random
+
 import pytest
 
 import kernel_choice as choice
 import test_gpu_decode_ranges as decode
 import test_gpu_head_tiles as head_tiles
 import test_gpu_pipelined_kernel as pipelined
+import test_gpu_small_sweeps as small_sweeps
 import test_gpu_underfilled as underfilled
 import test_gpu_work_list as work_list
 
@@ -92,3 +95,28 @@ def test_lists_by_sequence_cases():
 def test_merge_in_the_launch_cases():
     got = [choice.merged_in_launch(hq, hkv, n * 96 - 37, n) for hq, hkv, n in cases(decode.test_merge_in_the_launch)]
     assert got == [True, True, False, True, True, False, True, False, True]
+
+
+def test_sweeps_that_cannot_stop_are_those_whose_tiles_have_no_boundary_to_stop_at():
+    """Against the limits of fwd_il_kernel itself, tile by tile."""
+    rng, left = random.Random(17), 0
+    for _ in range(20000):
+        hq, sq, sk = rng.choice((1, 4, 8, 64)), rng.randint(1, 1500), rng.randint(0, 4000)
+        q_off, causal = rng.randint(0, 4000), rng.random() < 0.8
+        chunk = 64 * rng.choice((4, 15, 16, 17, 20, rng.randint(1, 40)))
+        delta, seg = max(-sq - 1, min(q_off, sk)), chunk // 64
+        stops = (-(-sq // 256) * hq + 7) // 8 > 32
+        for row0 in range(0, sq - 255, 256):
+            n_tiles = -(-(max(0, min(sk, row0 + 255 + delta + 1)) if causal else sk) // 64)
+            whole = min(sk // 64, max(0, row0 + delta + 1) // 64) if causal else sk // 64
+            seen = min(n_tiles, max(0, row0 + 31 + delta + 64) // 64) if causal else n_tiles
+            stops |= seg >= 16 and seg <= min(max(0, min(whole - 1, seen - 1)) & ~1, n_tiles - 1)
+        assert choice.sweep_can_stop(hq, sq, sk, q_off, chunk, causal) == stops
+        left += not stops
+    assert 2000 < left < 18000
+
+
+def test_small_sweep_cases():
+    got = [choice.sweep_can_stop(hq, sq, sk, q_off, chunk, causal) for sq, sk, hq, hkv, q_off, chunk, causal, _ in
+           cases(small_sweeps.test_sweeps_around_the_line_of_those_that_can_stop)]
+    assert got == [False, True, False, True, False, False, False, False, True]
