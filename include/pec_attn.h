@@ -140,7 +140,8 @@ size_t pec_sp_workspace_bytes(const pec_shape_t* shape, int64_t s_q);
  * A later call with resume = 1 and the same arguments and workspace continues every
  * tile from where it stopped; *pending is then the number of query tiles x heads
  * that have not yet seen their last key (0: out and lse are complete).  A launch
- * always takes each workgroup's first unfinished tile through at least one more
+ * always takes each workgroup's first unfinished tile (or piece of one: few tiles with
+ * many keys are shared out among more workgroups than tiles) through at least one more
  * segment, so repeated calls end even if *stop stays set.  A stopped tile's state
  * is stored as the kernel held it (un-normalised O, softmax reference, partial
  * denominators), so a stop adds no rounding step: the result equals the
@@ -151,7 +152,8 @@ size_t pec_sp_workspace_bytes(const pec_shape_t* shape, int64_t s_q);
  *             host, or device memory written by a copy or a kernel on another stream (it is
  *             read past the caches); NULL = never stop.  Segments
  *             shorter than 1024 keys, and query tiles with fewer than 256 rows, are
- *             only left between tiles, not between segments.
+ *             only left between tiles (pieces), not between segments; a sweep that this
+ *             leaves nothing to stop at runs as a plain call.
  *   pending : DEVICE int32, written by the call (resume = 0 sets it to the tile count).
  *   resume  : 0 starts from the first segment and ignores the workspace contents.
  *   chunk   : a multiple of 64 (PEC_ERR_UNSUPPORTED otherwise).

@@ -450,12 +450,74 @@ __global__ __launch_bounds__(1024) void build_worklist_kernel(const int32_t* __r
     else build(bucket);
 }
 
-// Start of a resumable sweep: no item has a segment behind it, all of them are pending.  Or its end, where a plain call did
-// the work: every item is through, none is pending.
-__global__ void sweep_table_kernel(int32_t* progress, int64_t n_items, int32_t* pending, int32_t done) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_items; i += (int64_t)gridDim.x * blockDim.x)
+// Merge of the pieces of every item that fwd_il_kernel<kFwdSpan> has cut, 32 rows of it per workgroup: grid (spans - 1, 8).
+// Workgroup x does the item that span x + 1 starts inside, if no earlier span does.  Its pieces are the last one of span x
+// and the first ones of the spans that start inside it.  Memory-bound: 132 KB per piece are read once, the item is written.
+// With a progress table an item is merged by the first launch that finds all its pieces done.
+__global__ __launch_bounds__(256) void span_merge_kernel(const FwdParams p) {
+    const int w0 = blockIdx.x + 1, strip = blockIdx.y;
+    const int pos = span_start(p, w0), n_spans = gridDim.x + 1;
+    const SpanPos at = span_locate(p, pos);
+    const int unit_start = pos - at.tile;
+    if (at.tile == 0 || unit_start < span_start(p, w0 - 1)) return;
+    const int units = p.group >> p.log_heads;
+    const int item = at.unit / units % p.n_items;
+    const int unit_end = unit_start + span_steps_of(p, item);
+    int w_last = w0;
+    while (w_last + 1 < n_spans && span_start(p, w_last + 1) < unit_end) ++w_last;
+    if (p.progress) {
+        int32_t* const merged = p.progress + n_spans + 8 * w0 + strip;
+        bool there = *merged == 0;
+        for (int w = w0 - 1; w <= w_last; ++w)
+            there = there && p.progress[w] >= min(unit_end, span_start(p, w + 1)) - span_start(p, w);
+        if (!there) return;
+        __syncthreads();      // everyone has read the word
+        if (threadIdx.x == 0) {
+            *merged = 1;
+            if (strip == 0) atomicSub(p.pending, 1);
+        }
+    }
+    const int bm = 256 >> p.log_heads;
+    const int head = at.unit / units / p.n_items * p.group + (at.unit % units << p.log_heads) + (strip >> (3 - p.log_heads));
+    const int row0 = (p.causal ? p.n_items - 1 - item : item) * bm + ((strip << 5) & (bm - 1));
+    const int n_pieces = w_last - w0 + 2, c = threadIdx.x & 31;
+    auto slot_row = [&](int i, int r) { return (int64_t)(2 * (w0 - 1 + i) + (i == 0 ? 1 : 0)) * 256 + strip * 32 + r; };
+    for (int r = threadIdx.x >> 5; r < 32; r += 8) {
+        const int row = row0 + r;
+        if (row >= p.sq) return;
+        float mx = -INFINITY, den = 0.f;
+        for (int i = 0; i < n_pieces; ++i) mx = fmaxf(mx, p.slot_lse[slot_row(i, r)]);
+        f32x4 a = {0.f, 0.f, 0.f, 0.f};
+        if (mx != -INFINITY) {
+#pragma unroll 4
+            for (int i = 0; i < n_pieces; ++i) {
+                const int64_t s = slot_row(i, r);
+                const float wgt = __builtin_amdgcn_exp2f((p.slot_lse[s] - mx) * kLog2e);
+                const f32x4 x = *reinterpret_cast<const f32x4*>(p.slot_out + s * kHeadDim + 4 * c);
+                den += wgt;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) a[e] += wgt * x[e];
+            }
+            const float inv = 1.f / den;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a[e] *= inv;
+        }
+        const int64_t idx = ((int64_t)row * p.n_q_heads + head) * kHeadDim + 4 * c;
+        if (p.acc_out) *reinterpret_cast<f32x4*>(p.acc_out + idx) = a;
+        if (p.out) {
+            if (p.out_f32) *reinterpret_cast<f32x4*>(static_cast<float*>(p.out) + idx) = a;
+            else *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(p.out) + idx) = __builtin_convertvector(a, bf16x4);
+        }
+        if (c == 0) p.lse[(int64_t)head * p.lse_stride + row] = mx == -INFINITY ? mx : mx + logf(den);
+    }
+}
+
+// Start of a resumable sweep: nothing of it is done, all of its items are pending.  Or its end, where a plain call did the
+// work: every item is through, none is pending.
+__global__ void sweep_table_kernel(int32_t* progress, int64_t n_words, int32_t n_items, int32_t* pending, int32_t done) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_words; i += (int64_t)gridDim.x * blockDim.x)
         progress[i] = done ? kSweepDone : 0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *pending = done ? 0 : (int32_t)n_items;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *pending = done ? 0 : n_items;
 }
 
 }  // namespace pec

@@ -51,17 +51,22 @@ __device__ __forceinline__ void scale_acc_in_place(f32x16 (&o)[4], float a) {
         for (int r = 0; r < 16; ++r) asm volatile("v_mul_f32 %0, %0, %1" : "+v"(o[dt][r]) : "v"(a));
 }
 
-// Three instances, so that each carries only its own bookkeeping through the (register-starved) work-item code:
+// Four instances, so that each carries only its own bookkeeping through the (register-starved) work-item code:
 // kFwdDense -- one call = one problem, work items dealt in fixed rounds (ring step, fused merge, key splits, the
 // plain sweep); kFwdSweep -- the resumable sweep (progress table, stop word, state of stopped items);
-// kFwdList -- device-built work lists (packed and colocated batch), work items drawn at run time.
-enum { kFwdDense = 0, kFwdSweep = 1, kFwdList = 2 };
+// kFwdList -- device-built work lists (packed and colocated batch), work items drawn at run time;
+// kFwdSpan -- one problem per call, stoppable or not, as one span of tile steps per workgroup: the items, one after the other,
+// are cut wherever a workgroup's equal share ends, and span_merge_kernel merges the pieces of an item.
+enum { kFwdDense = 0, kFwdSweep = 1, kFwdList = 2, kFwdSpan = 3 };
+constexpr int kSlotFloats = 256 * kHeadDim;     // of one piece's result
 
 template <int MODE>
 __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
     constexpr bool kSweep = MODE == kFwdSweep;
     constexpr bool kList = MODE == kFwdList;
-    constexpr bool kAhead = !kSweep;   // the next item's first loads go out before this item's results
+    constexpr bool kSpan = MODE == kFwdSpan;
+    constexpr bool kStops = kSweep || kSpan;
+    constexpr bool kAhead = !kStops;   // the next item's first loads go out before this item's results
     constexpr int NWAVES = 8;
     constexpr int BM = NWAVES * 32;
 
@@ -277,7 +282,21 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
         if (unit < 0) return;
         next = dense_geometry(unit);
     }
-    for (int64_t round0 = 0; kAhead || round0 < per_xcd; round0 += n_slots) {
+    // spans: workgroup w's, the steps of it that are done, and where it goes on; `kept`: inside a piece whose state is in a slot
+    const int span = (int)(blockIdx.x & 7) * n_slots + slot;
+    int span_done = 0, span_all = 0, unit_now = 0, tile_now = 0;
+    bool kept = false;
+    if constexpr (kSpan) {
+        const int start = span_start(p, span);
+        span_all = span_start(p, span + 1) - start;
+        if (p.progress) span_done = max(0, p.progress[span]);     // (a table that was never initialised leads nowhere else)
+        if (span_done >= span_all) return;
+        const SpanPos at = span_locate(p, start + span_done);
+        unit_now = at.unit;
+        tile_now = at.tile;
+        kept = span_done > 0 && tile_now > 0;
+    }
+    for (int64_t round0 = 0; kAhead || (kSpan ? span_done < span_all : round0 < per_xcd); round0 += n_slots) {
     // Lane-derived values are recomputed for every work item (the empty asm hides that they are
     // loop invariant): hoisted out of this loop they would stay live through the tile loop, which
     // has no register to spare -- a spill reload there waits on the tile loads just issued.
@@ -291,7 +310,20 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
     const float* acc_in = p.acc_in;
     float* acc_out = p.acc_out;
     int seg_done = 0;          // resumable sweep: key segments this item has behind it
-    if constexpr (kAhead) {
+    int tile_end = 0, piece_slot = 0;      // spans: the piece in hand ends here; its slot; whether it is a whole item
+    bool whole = false;
+    if constexpr (kSpan) {
+        g = dense_geometry(unit_now);
+        const int n = max(1, tiles_of(g));
+        tile_end = min(n, tile_now + span_all - span_done);
+        const bool from_start = tile_now <= span_done;      // the item begins inside this span
+        whole = from_start && tile_end == n;
+        piece_slot = 2 * span + (from_start ? 1 : 0);
+        g.kv_tok0 = (int64_t)tile_now * kBN;
+        g.sk = (int)(min((int64_t)g.sk, (int64_t)tile_end * kBN) - g.kv_tok0);
+        g.delta -= (int)g.kv_tok0;
+        acc_in = kept ? p.slot_out : tile_now == 0 ? p.acc_in : nullptr;
+    } else if constexpr (kAhead) {
         g = next;
         if (kList && g.part) {
             out_ptr = p.part_out;
@@ -314,7 +346,7 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
         g.delta -= (int)g.kv_tok0;
     }
     const int sq = g.sq, sk = g.sk, delta = g.delta, row0 = g.row0, rw0 = g.rw0;
-    const int64_t q_stride = g.q_stride, o_off0 = g.o_off0, lse_off0 = g.lse_off0;
+    int64_t q_stride = g.q_stride, o_off0 = g.o_off0, lse_off0 = g.lse_off0;
     const int causal = p.causal;
     const int wave_last = rw0 + 31;
     int n_tiles = tiles_of(g);
@@ -361,12 +393,19 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
     if (acc_in) {
         const int row = rw0 + l32;
         if (row < sq) {
-            const float lin = p.lse_in[lse_off0 + row];
-            constexpr bool raw = kSweep;   // state of a stopped sweep item, stored as the registers held it
+            int64_t lse_at = lse_off0 + row, acc_at = o_off0 + row * q_stride;
+            if constexpr (kSpan) {
+                if (kept) {
+                    lse_at = piece_slot * BM + wave * 32 + l32;
+                    acc_at = lse_at * kHeadDim;
+                }
+            }
+            const float lin = (kSpan && kept ? p.slot_lse : p.lse_in)[lse_at];
+            const bool raw = kSpan ? kept : kSweep;   // state of a stopped item, stored as the registers held it
             if (raw || lin != -INFINITY) {
                 m_run = raw ? lin : lin * kLog2e;
-                l_run = raw ? p.l_part[(lse_off0 + row) * 2 + hl] : (hl == 0 ? 1.f : 0.f);
-                const float* arow = acc_in + o_off0 + row * q_stride + 4 * hl;
+                l_run = raw ? p.l_part[lse_at * 2 + hl] : (hl == 0 ? 1.f : 0.f);
+                const float* arow = acc_in + acc_at + 4 * hl;
 #pragma unroll
                 for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
@@ -723,7 +762,7 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
     using P1 = std::integral_constant<int, 1>;
 
     // ---- prologue: K(0), K(1), and finite data in the V stage that iteration 0 reads with P = 0
-    const bool may_stop = kSweep && p.stop != nullptr;
+    const bool may_stop = kStops && p.stop != nullptr;
     if constexpr (kAhead) {
         if (!requested) {
             issue_q(g);
@@ -789,6 +828,10 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
         }
         stop_limit = min(max(0, min(nf0 - 1, na0 - 1)) & ~1, n_tiles - 1);
         stop_b = p.seg_tiles;
+        if constexpr (kSpan) {   // a piece may start inside a segment; a boundary right behind its start is left out
+            stop_b -= tile_now % p.seg_tiles;
+            if (stop_b < 16) stop_b += p.seg_tiles;
+        }
         if (stop_b <= stop_limit) stop_evt = (stop_b & ~1) - 8;
     }
     for (;;) {
@@ -849,11 +892,19 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
     if constexpr (kSweep) {   // an item stopped short keeps its fp32 state; one that is through writes the result
         if (stopped) out_ptr = nullptr; else acc_out = nullptr;
     }
+    if (kSpan && (stopped || !whole)) {   // to the piece's slot, whose first row is this workgroup's
+        out_ptr = nullptr;
+        acc_out = p.slot_out;
+        lse_ptr = p.slot_lse;
+        lse_off0 = piece_slot * BM + wave * 32 - rw0;
+        q_stride = kHeadDim;
+        o_off0 = lse_off0 * kHeadDim;
+    }
     {
         const int row = rw0 + l32;
         const float l_tot = l_run + __shfl_xor(l_run, 32);
         if (row < sq) {
-            const bool raw = kSweep && stopped;   // a stopped sweep item keeps its state as it stands
+            const bool raw = kStops && stopped;   // a stopped item keeps its state as it stands
             const float inv = raw ? 1.f : (l_tot > 0.f ? 1.f / l_tot : 0.f);
             const float lse = raw ? m_run : (l_tot > 0.f ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY);
             if (raw) p.l_part[(lse_off0 + row) * 2 + hl] = l_run;
@@ -900,7 +951,17 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
         p.progress[g.logical] = stopped ? seg_done + stop_b / p.seg_tiles : kSweepDone;
         if (!stopped) atomicSub(p.pending, 1);
     }
-    if (kSweep && stopped) return;  // a stop request: this workgroup takes no further item
+    if constexpr (kSpan) {
+        span_done += stopped ? stop_b : tile_end - tile_now;
+        if (p.progress && threadIdx.x == 0) {
+            p.progress[span] = span_done;
+            if (whole && !stopped) atomicSub(p.pending, 1);
+        }
+        ++unit_now;
+        tile_now = 0;
+        kept = false;
+    }
+    if (kStops && stopped) return;  // a stop request: this workgroup takes no further item
     if constexpr (kAhead) {
         if (!more) return;
         requested = true;

@@ -35,6 +35,11 @@ int compute_units() {
     }
     return cached[dev];
 }
+// Scratch of a call cut into spans: two slots per workgroup (fp32 O, softmax reference or LSE, two partial denominators per row
+// of a stopped piece), then the progress table (a word per span, eight per span for the merge).
+size_t span_slots_bytes(int groups) { return (size_t)2 * groups * kBM * (kHeadDim + 3) * sizeof(float); }
+size_t span_table_words(int groups) { return (size_t)9 * groups; }
+
 // The pipelined kernel is persistent: one workgroup per compute unit (its registers allow no
 // second one), each walking its share of the `grid` logical work items.
 void launch_il(const FwdParams& p, unsigned grid, hipStream_t st) {
@@ -99,6 +104,8 @@ struct Sweep {   // resumable sweep: per-item progress table, count of unfinishe
     int32_t* pending;
     const int32_t* stop;
     int32_t seg_tiles;
+    SpanPlan spans;      // groups != 0: cut into spans, their slots behind o_acc and l_part
+    float* slots;
 };
 
 int chunk_impl(const pec_shape_t* shape, const void* q, const void* k, const void* v, int64_t sq, int64_t sk,
@@ -141,6 +148,21 @@ int chunk_impl(const pec_shape_t* shape, const void* q, const void* k, const voi
         p.pending = sweep->pending;
         p.stop = sweep->stop;
         p.seg_tiles = sweep->seg_tiles;
+        if (const int groups = sweep->spans.groups) {
+            const int64_t steps = sweep->spans.steps_per_kvh * p.n_kv_heads;
+            p.slot_out = sweep->slots;
+            p.slot_lse = p.slot_out + (size_t)2 * groups * kBM * kHeadDim;
+            p.l_part = p.slot_lse + (size_t)2 * groups * kBM;
+            p.span_kvh = (int32_t)sweep->spans.steps_per_kvh;
+            p.span_len = (int32_t)(steps / groups);
+            p.span_extra = (int32_t)(steps % groups);
+            p.n_items = (int32_t)((sq + kBM - 1) / kBM);
+            hipStream_t st = static_cast<hipStream_t>(stream);
+            hipLaunchKernelGGL(fwd_il_kernel<kFwdSpan>, dim3(groups), dim3(512), 0, st, p);
+            if (hipGetLastError() != hipSuccess) return PEC_ERR_HIP;
+            hipLaunchKernelGGL(span_merge_kernel, dim3(groups - 1, 8), dim3(256), 0, st, p);
+            return hipGetLastError() == hipSuccess ? PEC_OK : PEC_ERR_HIP;
+        }
     }
     const bool simple = (shape->flags & PEC_FLAG_SIMPLE_KERNEL) != 0;
     // (the progress table of the resumable sweep counts tiles of 256 rows of one head)
@@ -308,7 +330,9 @@ size_t pec_sp_resumable_workspace_bytes(const pec_shape_t* shape, int64_t s_q) {
     const size_t o = (size_t)s_q * shape->n_q_heads * kHeadDim * sizeof(float);
     const size_t l = (((size_t)s_q * shape->n_q_heads * 2 * sizeof(float)) + 255) & ~(size_t)255;
     const size_t items = (size_t)((s_q + kBM - 1) / kBM) * shape->n_q_heads;
-    return o + l + ((items * sizeof(int32_t) + 255) & ~(size_t)255);
+    const size_t plain = o + l + ((items * sizeof(int32_t) + 255) & ~(size_t)255);
+    const int groups = most_span_groups(compute_units(), shape->n_q_heads, s_q);
+    return std::max(plain, span_slots_bytes(groups) + span_table_words(groups) * sizeof(int32_t));
 }
 
 int pec_sp_prefill_resumable(const pec_shape_t* shape, const void* q, const void* k, const void* v, int64_t s_q,
@@ -332,9 +356,10 @@ int pec_sp_prefill_resumable(const pec_shape_t* shape, const void* q, const void
     const size_t l_bytes = (((size_t)s_q * shape->n_q_heads * 2 * sizeof(float)) + 255) & ~(size_t)255;
     float* l_part = s_q > 0 ? reinterpret_cast<float*>(static_cast<char*>(workspace) + o_bytes) : nullptr;
     int32_t* progress = s_q > 0 ? reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + o_bytes + l_bytes) : nullptr;
+    int64_t words = items;
     auto set_table = [&](int32_t done) {
-        hipLaunchKernelGGL(sweep_table_kernel, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>((items + 255) / 256, 1024))),
-                           dim3(256), 0, st, progress, items, pending, done);
+        hipLaunchKernelGGL(sweep_table_kernel, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>((words + 255) / 256, 1024))),
+                           dim3(256), 0, st, progress, words, (int32_t)items, pending, done);
         return hipGetLastError() == hipSuccess ? PEC_OK : PEC_ERR_HIP;
     };
     const int64_t delta = std::max<int64_t>(-s_q - 1, std::min<int64_t>(q_off, s_kv));      // as in chunk_impl
@@ -344,12 +369,19 @@ int pec_sp_prefill_resumable(const pec_shape_t* shape, const void* q, const void
             return rc;
         return set_table(1);      // (a call that resumes such a sweep finds everything done)
     }
+    SpanPlan spans{0, 0};
+    if (s_q > 0) spans = spans_of_sweep(compute_units(), shape->n_q_heads, shape->n_kv_heads, s_q, s_kv, delta, causal != 0);
+    if (spans.groups) {
+        progress = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + span_slots_bytes(spans.groups));
+        words = (int64_t)span_table_words(spans.groups);
+    }
     if (!resume || s_q == 0)
         if (int rc = set_table(0)) return rc;
     if (s_q == 0) return PEC_OK;
-    const Sweep sweep{l_part, progress, pending, stop, (int32_t)(chunk / kBN)};
-    return chunk_impl(shape, q, k, v, s_q, s_kv, q_off, 0, causal, out, shape->out_dtype == PEC_F32, lse, o_acc, lse, o_acc,
-                      s_q, stream, &sweep);
+    const Sweep sweep{l_part, progress, pending, stop, (int32_t)(chunk / kBN), spans, o_acc};
+    float* const acc = spans.groups ? nullptr : o_acc;
+    return chunk_impl(shape, q, k, v, s_q, s_kv, q_off, 0, causal, out, shape->out_dtype == PEC_F32, lse, acc, lse, acc, s_q,
+                      stream, &sweep);
 }
 
 int64_t pec_sp_prefill_num_steps(const pec_shape_t* shape, int64_t s_q, int64_t q_off, int64_t s_kv, int64_t chunk,

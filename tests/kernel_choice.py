@@ -29,6 +29,9 @@ extern "C" int by_sequence(int cu, int hq, int rows, int64_t batch, int64_t tq) 
 extern "C" int can_stop(int cu, int hq, int64_t sq, int64_t sk, int64_t delta, int causal, int64_t seg_tiles) {
     return pec::sweep_can_stop(cu, hq, sq, sk, delta, causal, seg_tiles);
 }
+extern "C" int spans(int cu, int hq, int hkv, int64_t sq, int64_t sk, int64_t delta, int causal) {
+    return pec::spans_of_sweep(cu, hq, hkv, sq, sk, delta, causal).groups;
+}
 extern "C" int merged(int g, int64_t n) { return pec::merge_in_launch(g, n); }
 extern "C" int64_t ranges(int cu, int hq, int hkv, int64_t sk) { return pec::decode_default_ranges(cu, hq, hkv, sk); }
 extern "C" int split(int cu, int hq, int hkv, int64_t sk, int64_t n) { return pec::decode_on_split_kernel(cu, hq, hkv, sk, n); }
@@ -50,6 +53,7 @@ def _lib():
     L.list.argtypes = [ctypes.c_int] * 3 + [i64] * 4 + [ctypes.c_int] * 2
     L.by_sequence.argtypes = [ctypes.c_int] * 3 + [i64] * 2
     L.can_stop.argtypes = [ctypes.c_int] * 2 + [i64] * 3 + [ctypes.c_int, i64]
+    L.spans.argtypes = L.dense.argtypes
     L.merged.argtypes = [ctypes.c_int, i64]
     L.ranges.argtypes, L.ranges.restype = [ctypes.c_int] * 3 + [i64], i64
     L.split.argtypes = [ctypes.c_int] * 3 + [i64] * 2
@@ -70,6 +74,11 @@ def dense_heads(hq, hkv, sq, sk, q_off=0, kv_off=0, causal=True):
 def sweep_can_stop(hq, sq, sk, q_off, chunk, causal=True):
     """Whether a stop word can change what the resumable sweep does; if not it runs as a plain call."""
     return bool(_lib().can_stop(COMPUTE_UNITS, hq, sq, sk, max(-sq - 1, min(q_off, sk)), int(causal), chunk // 64))
+
+
+def sweep_spans(hq, hkv, sq, sk, q_off, causal=True):
+    """Workgroups of a resumable sweep that is cut into spans, 0 if it is not."""
+    return _lib().spans(COMPUTE_UNITS, hq, hkv, sq, sk, max(-sq - 1, min(q_off, sk)), int(causal))
 
 
 def batch_heads(hq, hkv, len_q):

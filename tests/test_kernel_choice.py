@@ -8,6 +8,7 @@ import test_gpu_decode_ranges as decode
 import test_gpu_head_tiles as head_tiles
 import test_gpu_pipelined_kernel as pipelined
 import test_gpu_small_sweeps as small_sweeps
+import test_gpu_spans as spans
 import test_gpu_underfilled as underfilled
 import test_gpu_work_list as work_list
 
@@ -120,3 +121,9 @@ def test_small_sweep_cases():
     got = [choice.sweep_can_stop(hq, sq, sk, q_off, chunk, causal) for sq, sk, hq, hkv, q_off, chunk, causal, _ in
            cases(small_sweeps.test_sweeps_around_the_line_of_those_that_can_stop)]
     assert got == [False, True, False, True, False, False, False, False, True]
+
+
+def test_span_cases():
+    got = [(choice.sweep_spans(hq, hkv, sq, sk, q_off, causal), choice.sweep_can_stop(hq, sq, sk, q_off, chunk, causal))
+           for sq, sk, hq, hkv, q_off, chunk, causal in spans.CASES]
+    assert all(groups >= 16 and can_stop for groups, can_stop in got)
