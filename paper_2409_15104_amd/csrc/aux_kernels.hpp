@@ -228,9 +228,6 @@ __global__ __launch_bounds__(64) void combine_few_kernel(const float* o_part, co
 // The same combination for the one-token sequences of a colocated batch: split_seqs lists
 // (sequence, first slot, number of key ranges); the result goes to the sequence's row of the packed
 // out [total_q, n_heads, 128] / lse [n_heads, total_q].  grid = (n_heads, up to batch).
-struct SplitSeq {
-    int32_t seq, slot0, n_ranges, pad;
-};
 template <bool OUT_F32>
 __global__ __launch_bounds__(kCombineThreads) void combine_colocated_kernel(
     const float* __restrict__ o_part, const float* __restrict__ lse_part, const SplitSeq* __restrict__ split_seqs,

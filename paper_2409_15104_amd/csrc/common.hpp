@@ -110,6 +110,16 @@ struct FwdParams {
     float* slot_out;
     float* slot_lse;
     int32_t span_len, span_extra, span_kvh;
+    // a batch of up to 64 sequences without a work list (fwd_split_kernel<kSplitBatch>): its offsets, and, for the merge of split
+    // sequences' key ranges, how many slots there are and where block 0 lists those sequences
+    const int32_t* cu_q;
+    const int32_t* cu_k;
+    int32_t batch, total_q, total_k, slot_capacity;
+    struct SplitSeq* split_seqs;
+    int32_t* n_split;
+};
+struct SplitSeq {        // a one-token sequence whose keys are cut into ranges
+    int32_t seq, slot0, n_ranges, pad;
 };
 
 // Tile steps of a query tile (in work order, number `item`) of a dense call cut into spans, at least one.

@@ -75,11 +75,69 @@ __device__ __forceinline__ bool last_workgroup(uint64_t* words, uint64_t epoch, 
 }
 
 // What a launch works on: the query tiles of one call, the items of a packed or colocated batch (a device-built list of
-// bm = 32 * NT rows per item), or the key ranges of a decode step.
-enum { kSplitDense = 0, kSplitList = 1, kSplitDecode = 2 };
+// bm = 32 * NT rows per item), or the key ranges of a decode step; kSplitBatch: the items of a batch of up to 64 sequences,
+// which every wavefront finds in the offsets by itself.
+enum { kSplitDense = 0, kSplitList = 1, kSplitDecode = 2, kSplitBatch = 3 };
+
+// Items of a batch of up to 64 sequences in the order of a work list (build_worklist_kernel) that keeps the items of a
+// sequence together: a lane per sequence, sequences by the keys of their heaviest item, a sequence's longest item first.
+// Building the list would be a launch of its own, 3 us of the host's time and 6 of the GPU's; here it is one trip to memory
+// and a few instructions per sequence at the start of every workgroup.
+struct BatchItems {
+    int q0, len_q, k0, len_k, first, count, slot0;     // of this lane's sequence; slot0 -1: not split
+    int total;                                         // items of the batch
+    __device__ __forceinline__ BatchItems(const FwdParams& p, int bm) {
+        const int b = threadIdx.x & 63;
+        q0 = len_q = k0 = len_k = first = count = 0;
+        slot0 = -1;
+        if (b < p.batch) {      // bounds clamped as in build_worklist_kernel
+            q0 = min(max(p.cu_q[b], 0), p.total_q);
+            len_q = min(max(p.cu_q[b + 1], q0), p.total_q) - q0;
+            k0 = min(max(p.cu_k[b], 0), p.total_k);
+            len_k = min(max(p.cu_k[b + 1], k0), p.total_k) - k0;
+        }
+        const bool split = p.range_len > 0 && len_q == 1 && len_k > p.range_len;
+        const int ranges = split ? (len_k + p.range_len - 1) / p.range_len : 0;
+        count = split ? (ranges + p.group - 1) / p.group : (len_q + bm - 1) / bm;
+        if (p.range_len > 0) {
+            int upto = ranges;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const int y = __shfl_up(upto, d);
+                if (b >= d) upto += y;
+            }
+            if (split) slot0 = upto - ranges;
+            if (split && upto > p.slot_capacity) {      // offsets that are not monotone: left out
+                count = 0;
+                slot0 = -1;
+            }
+            const uint64_t listed = __ballot(slot0 >= 0);
+            if (blockIdx.x == 0 && threadIdx.x < 64) {
+                if (slot0 >= 0) p.split_seqs[__popcll(listed & ((1ull << b) - 1))] = SplitSeq{b, slot0, ranges, 0};
+                if (b == 0) *p.n_split = __popcll(listed);
+            }
+        }
+        const int keys = split ? min(p.range_len, len_k) : len_k;
+        total = 0;
+        for (int i = 0; i < p.batch; ++i) {
+            const int n = __builtin_amdgcn_readlane(count, i), other = __builtin_amdgcn_readlane(keys, i);
+            total += n;
+            if (other > keys || (other == keys && i < b)) first += n;
+        }
+    }
+    __device__ __forceinline__ WorkItem item(const FwdParams& p, int n) const {     // n < total, uniform
+        const int b = __builtin_ctzll(__ballot((uint32_t)(n - first) < (uint32_t)count));
+        const int i = n - __builtin_amdgcn_readlane(first, b), s = __builtin_amdgcn_readlane(slot0, b);
+        const int sq0 = __builtin_amdgcn_readlane(q0, b), sk0 = __builtin_amdgcn_readlane(k0, b), lk = __builtin_amdgcn_readlane(len_k, b);
+        const int r0 = i * p.group;      // first key range of a split sequence's item
+        if (s >= 0) return WorkItem{sq0, 1, sk0 + r0 * p.range_len, lk - r0 * p.range_len, -1, s + r0, {0, 0}};
+        return WorkItem{sq0, __builtin_amdgcn_readlane(len_q, b), sk0, lk, __builtin_amdgcn_readlane(count, b) - 1 - i, 0, {0, 0}};
+    }
+};
 template <int NT, int MODE>
 __global__ __launch_bounds__(kSplitWaves * 64, 2) void fwd_split_kernel(const FwdParams p) {
-    constexpr bool LIST = MODE == kSplitList;
+    constexpr bool BATCH = MODE == kSplitBatch;
+    constexpr bool LIST = MODE == kSplitList || BATCH;
     constexpr bool DECODE = MODE == kSplitDecode;
     constexpr int KS = kSplitWaves;
     constexpr int BM = 32 * NT;
@@ -95,7 +153,14 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void fwd_split_kernel(const Fw
     const int lane = threadIdx.x & 63;
     const int l32 = lane & 31, hl = lane >> 5;
 
-    const int n_items = LIST ? min(*p.n_work, p.n_items) : p.n_items;
+    using Items = std::conditional_t<BATCH, BatchItems, int>;
+    const Items items = [&]() -> Items {
+        if constexpr (BATCH) return BatchItems(p, BM);
+        else return 0;
+    }();
+    int n_items = p.n_items;
+    if constexpr (BATCH) n_items = min(items.total, n_items);
+    else if constexpr (LIST) n_items = min(*p.n_work, n_items);
     const WorkOrder order(n_items, p.group, p.n_kv_heads);
     if ((blockIdx.x >> 3) >= order.count) return;
     const int64_t logical = order.unit(blockIdx.x & 7, blockIdx.x >> 3);
@@ -125,7 +190,9 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void fwd_split_kernel(const Fw
         o_off0 += item * p.split_out_stride;
         lse_off0 += item * p.split_lse_stride;
     } else if constexpr (LIST) {
-        const WorkItem w = p.work[item];
+        WorkItem w;
+        if constexpr (BATCH) w = items.item(p, item);
+        else w = p.work[item];
         sk = w.len_k;
         kv_tok0 = w.k0;
         if (w.qtile >= 0) {

@@ -210,6 +210,16 @@ inline bool sweep_can_stop(int cu, int n_q_heads, int64_t sq, int64_t sk, int64_
     return seg_tiles <= last;
 }
 
+// Whether a batch does without a work list: the workgroups of fwd_split_kernel find their items in the offsets, a lane per
+// sequence.  That saves a launch, 3 ... 4 us, and costs every workgroup a loop over the sequences, one workgroup at a time on a
+// compute unit.  Over 36 random batches of 4 to 64 sequences, microseconds won, by workgroups (bound) and sequences: 70 x 5
+// 4.3 (11.5 -> 7.2), 302 x 14 3.3, 345 x 42 2.9, 535 x 13 3.9, 695 x 16 3.5; 731 x 14 -0.5, 433 x 45 0.1, 640 x 29 -0.1, 515 x 54 -3.4,
+// 1190 x 29 -7.8, 1990 x 55 -45.
+inline bool batch_without_list(int cu, int rows, int n_q_heads, int64_t batch, int64_t total_q) {
+    const int64_t groups = (total_q / rows + batch) * n_q_heads;
+    return rows < kBM && batch <= 64 && 4 * groups <= 11 * cu && groups * batch <= 64 * cu;
+}
+
 // Keys per range when sk keys are cut into n_splits ranges of whole tiles.
 inline int64_t range_keys(int64_t sk, int64_t n_splits, int tile) {
     return std::max<int64_t>(((sk + n_splits - 1) / n_splits + tile - 1) / tile * tile, tile);

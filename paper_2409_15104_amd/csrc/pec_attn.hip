@@ -76,7 +76,7 @@ int check_shape(const pec_shape_t* s, float* scale_out) {
 
 // `rows`: query rows per workgroup; p.n_items counts tiles of `rows` positions (lists) or rows >> log_heads (dense).
 int launch_fwd(const FwdParams& p, bool simple, int rows, hipStream_t stream) {
-    const int64_t total = (int64_t)p.n_items * (p.work ? p.n_q_heads : p.n_q_heads >> p.log_heads);
+    const int64_t total = (int64_t)p.n_items * (p.work || p.cu_q ? p.n_q_heads : p.n_q_heads >> p.log_heads);
     if (total <= 0) return PEC_OK;
     const int64_t per_xcd = (total + 7) / 8;
     const int64_t grid = per_xcd * 8;
@@ -86,6 +86,10 @@ int launch_fwd(const FwdParams& p, bool simple, int rows, hipStream_t stream) {
         hipLaunchKernelGGL(fwd_simple_kernel, blocks, dim3(kSimpleWaves * 64), 0, stream, p);
     else if (rows == kBM)
         launch_il(p, (unsigned)grid, stream);
+    else if (rows == 64 && p.cu_q)
+        hipLaunchKernelGGL((fwd_split_kernel<2, kSplitBatch>), blocks, threads, 0, stream, p);
+    else if (p.cu_q)
+        hipLaunchKernelGGL((fwd_split_kernel<1, kSplitBatch>), blocks, threads, 0, stream, p);
     else if (rows == 64 && p.work)
         hipLaunchKernelGGL((fwd_split_kernel<2, kSplitList>), blocks, threads, 0, stream, p);
     else if (rows == 64)
@@ -701,13 +705,21 @@ int pec_attn_varlen(const pec_shape_t* shape, const void* q, const void* k, cons
     int32_t* n_work = reinterpret_cast<int32_t*>(ws + cap * sizeof(WorkItem));
     int32_t* bucket = reinterpret_cast<int32_t*>(ws + cap * sizeof(WorkItem) + 256);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const int by_sequence = list_by_sequence(compute_units(), shape->n_q_heads, rows, batch, total_tokens);
-    hipLaunchKernelGGL(build_worklist_kernel, dim3(1), dim3(1024), 0, st, cu_seqlens, cu_seqlens, (int)batch,
-                       (int)total_tokens, (int)total_tokens, rows, rows, 0, 1, capacity, 0, capacity + 1, by_sequence, work, n_work, bucket,
-                       static_cast<SplitSeq*>(nullptr));
-    if (hipGetLastError() != hipSuccess) return PEC_ERR_HIP;
-
     FwdParams p{};
+    if (batch_without_list(compute_units(), rows, shape->n_q_heads, batch, total_tokens)) {
+        p.cu_q = p.cu_k = cu_seqlens;
+        p.batch = batch;
+        p.total_q = p.total_k = (int32_t)total_tokens;
+    } else {
+        const int by_sequence = list_by_sequence(compute_units(), shape->n_q_heads, rows, batch, total_tokens);
+        hipLaunchKernelGGL(build_worklist_kernel, dim3(1), dim3(1024), 0, st, cu_seqlens, cu_seqlens, (int)batch,
+                           (int)total_tokens, (int)total_tokens, rows, rows, 0, 1, capacity, 0, capacity + 1, by_sequence, work, n_work,
+                           bucket, static_cast<SplitSeq*>(nullptr));
+        if (hipGetLastError() != hipSuccess) return PEC_ERR_HIP;
+        p.work = work;
+        p.n_work = n_work;
+        p.sched = n_work + 8;   // same 256-byte block, zeroed by the builder
+    }
     p.q = static_cast<const __bf16*>(q);
     p.k = static_cast<const __bf16*>(k);
     p.v = static_cast<const __bf16*>(v);
@@ -722,9 +734,6 @@ int pec_attn_varlen(const pec_shape_t* shape, const void* q, const void* k, cons
     p.n_items = capacity;
     p.out_f32 = shape->out_dtype == PEC_F32;
     p.scale_log2 = scale * kLog2e;
-    p.work = work;
-    p.n_work = n_work;
-    p.sched = n_work + 8;   // same 256-byte block, zeroed by the builder
     return launch_fwd(p, simple, rows, st);
 }
 
@@ -783,14 +792,30 @@ int pec_attn_colocated(const pec_shape_t* shape, const void* q, const void* k, c
     float* part_lse = reinterpret_cast<float*>(ws + L.off_part_lse);
     float* part_out = reinterpret_cast<float*>(ws + L.off_part_out);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const int by_sequence = list_by_sequence(compute_units(), shape->n_q_heads, rows, batch, total_q);
-    hipLaunchKernelGGL(build_worklist_kernel, dim3(1), dim3(1024), 0, st, cu_seqlens_q, cu_seqlens_k, (int)batch,
-                       (int)total_q, (int)total_k, rows, 256, kColocRange, (int)(shape->n_q_heads / shape->n_kv_heads),
-                       (int)L.cap_items, (int)L.slot_cap, (int)L.n_buckets, by_sequence, work, counters,
-                       reinterpret_cast<int32_t*>(ws + L.off_bucket), split_seqs);
-    if (hipGetLastError() != hipSuccess) return PEC_ERR_HIP;
-
     FwdParams p{};
+    // items of proper offsets (workgroups beyond what there is cost fwd_split_kernel a look at it each)
+    const int64_t range_item = (int64_t)kColocRange * (shape->n_q_heads / shape->n_kv_heads);   // keys of an item of ranges
+    p.n_items = (int32_t)std::min<int64_t>(L.cap_items, total_q / rows + batch + total_k / range_item);
+    if (batch_without_list(compute_units(), rows, shape->n_q_heads, batch, total_q)) {
+        p.cu_q = cu_seqlens_q;
+        p.cu_k = cu_seqlens_k;
+        p.batch = batch;
+        p.total_q = (int32_t)total_q;
+        p.total_k = (int32_t)total_k;
+        p.slot_capacity = (int32_t)L.slot_cap;
+        p.split_seqs = split_seqs;
+        p.n_split = counters + 2;
+    } else {
+        const int by_sequence = list_by_sequence(compute_units(), shape->n_q_heads, rows, batch, total_q);
+        hipLaunchKernelGGL(build_worklist_kernel, dim3(1), dim3(1024), 0, st, cu_seqlens_q, cu_seqlens_k, (int)batch,
+                           (int)total_q, (int)total_k, rows, 256, kColocRange, (int)(shape->n_q_heads / shape->n_kv_heads),
+                           (int)L.cap_items, (int)L.slot_cap, (int)L.n_buckets, by_sequence, work, counters,
+                           reinterpret_cast<int32_t*>(ws + L.off_bucket), split_seqs);
+        if (hipGetLastError() != hipSuccess) return PEC_ERR_HIP;
+        p.work = work;
+        p.n_work = counters;
+        p.sched = counters + 8;   // same 256-byte block, zeroed by the builder
+    }
     p.q = static_cast<const __bf16*>(q);
     p.k = static_cast<const __bf16*>(k);
     p.v = static_cast<const __bf16*>(v);
@@ -802,12 +827,8 @@ int pec_attn_colocated(const pec_shape_t* shape, const void* q, const void* k, c
     p.n_kv_heads = shape->n_kv_heads;
     p.group = shape->n_q_heads / shape->n_kv_heads;
     if (rows == kBM) p.log_heads = log_heads_of_list_call(compute_units(), p.n_q_heads, p.n_kv_heads, batch, total_q);
-    p.n_items = (int32_t)L.cap_items;
     p.out_f32 = shape->out_dtype == PEC_F32;
     p.scale_log2 = scale * kLog2e;
-    p.work = work;
-    p.n_work = counters;
-    p.sched = counters + 8;   // same 256-byte block, zeroed by the builder
     p.part_out = part_out;
     p.part_lse = part_lse;
     p.range_len = kColocRange;

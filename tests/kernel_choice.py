@@ -32,6 +32,7 @@ extern "C" int can_stop(int cu, int hq, int64_t sq, int64_t sk, int64_t delta, i
 extern "C" int spans(int cu, int hq, int hkv, int64_t sq, int64_t sk, int64_t delta, int causal) {
     return pec::spans_of_sweep(cu, hq, hkv, sq, sk, delta, causal).groups;
 }
+extern "C" int without_list(int cu, int rows, int hq, int64_t batch, int64_t tq) { return pec::batch_without_list(cu, rows, hq, batch, tq); }
 extern "C" int merged(int g, int64_t n) { return pec::merge_in_launch(g, n); }
 extern "C" int64_t ranges(int cu, int hq, int hkv, int64_t sk) { return pec::decode_default_ranges(cu, hq, hkv, sk); }
 extern "C" int split(int cu, int hq, int hkv, int64_t sk, int64_t n) { return pec::decode_on_split_kernel(cu, hq, hkv, sk, n); }
@@ -54,6 +55,7 @@ def _lib():
     L.by_sequence.argtypes = [ctypes.c_int] * 3 + [i64] * 2
     L.can_stop.argtypes = [ctypes.c_int] * 2 + [i64] * 3 + [ctypes.c_int, i64]
     L.spans.argtypes = L.dense.argtypes
+    L.without_list.argtypes = [ctypes.c_int] * 3 + [i64] * 2
     L.merged.argtypes = [ctypes.c_int, i64]
     L.ranges.argtypes, L.ranges.restype = [ctypes.c_int] * 3 + [i64], i64
     L.split.argtypes = [ctypes.c_int] * 3 + [i64] * 2
@@ -89,6 +91,11 @@ def batch_heads(hq, hkv, len_q):
 def by_sequence(hq, rows, len_q):
     """Whether the work list of a batch keeps the items of a sequence together."""
     return bool(_lib().by_sequence(COMPUTE_UNITS, hq, rows, len(len_q), int(sum(len_q))))
+
+
+def without_list(rows, hq, len_q):
+    """Whether the workgroups of a batch find their items in the offsets."""
+    return bool(_lib().without_list(COMPUTE_UNITS, rows, hq, len(len_q), int(sum(len_q))))
 
 
 def packed_rows(hq, hkv, lengths, hint=None, causal=True):

@@ -7,6 +7,7 @@ import kernel_choice as choice
 import test_gpu_decode_ranges as decode
 import test_gpu_head_tiles as head_tiles
 import test_gpu_pipelined_kernel as pipelined
+import test_gpu_small_batches as small_batches
 import test_gpu_small_sweeps as small_sweeps
 import test_gpu_spans as spans
 import test_gpu_underfilled as underfilled
@@ -127,3 +128,14 @@ def test_span_cases():
     got = [(choice.sweep_spans(hq, hkv, sq, sk, q_off, causal), choice.sweep_can_stop(hq, sq, sk, q_off, chunk, causal))
            for sq, sk, hq, hkv, q_off, chunk, causal in spans.CASES]
     assert all(groups >= 16 and can_stop for groups, can_stop in got)
+
+
+def test_small_batch_cases_run_with_and_without_a_list():
+    got = []
+    for n, hq, hkv, first in cases(small_batches.test_small_batches_match_oracle):
+        len_q, len_k = small_batches.lengths(n, first)
+        rows = choice.packed_rows(hq, hkv, len_q), choice.mixed_rows(hq, hkv, len_q, len_k)
+        got.append((rows, *[choice.without_list(r, hq, len_q) for r in rows]))
+    assert [g[1:] for g in got] == [(True, True)] * 7 + [(False, False)] * 4
+    assert {r for g in got[:7] for r in g[0]} == {32, 64}
+    assert not choice.without_list(256, 1, [8] * 8)
