@@ -221,8 +221,8 @@ size_t pec_varlen_workspace_bytes(int32_t batch, int64_t total_tokens);
  *   q, out [total_q, Hq, 128]; k, v [total_k, Hkv, 128]; lse [Hq, total_q].
  *   cu_seqlens_q, cu_seqlens_k: DEVICE int32 [batch + 1], non-decreasing from 0 (values are clamped on
  *   the device; malformed ones can misplace or drop results but never index out of bounds).
- * One-token sequences with more than 4096 keys are cut into key ranges of 4096 keys that run as work
- * items of the same launch (the query heads of a KV group share one pass over the keys); a second,
+ * One-token sequences with long caches are cut into key ranges (of 512 to 4096 keys, the shorter the less
+ * else there is to do) that run as work items of the same launch (the query heads of a KV group share one pass over the keys); a second,
  * small launch merges their partial (O, LSE) pairs by log-sum-exp.  Rows without a visible key get
  * out = 0, lse = -inf.  workspace: pec_colocated_workspace_bytes() bytes.
  * PEC_FLAG_SIMPLE_KERNEL is not supported here (PEC_ERR_UNSUPPORTED).

@@ -210,6 +210,33 @@ inline bool sweep_can_stop(int cu, int n_q_heads, int64_t sq, int64_t sk, int64_
     return seg_tiles <= last;
 }
 
+// Keys per range of the decode steps in a mixed batch.  A range is one workgroup's walk: fwd_il_kernel, whose launches fill the
+// chip, takes the longest; on fwd_split_kernel 4,096 keys are 25 us, often all of the call, and 512 keys 8 us, of which 6 do
+// not depend on the keys.  Estimated: the longer of a range's walk and the work shared out over the compute units, 12 us per
+// workgroup of the other sequences, a quarter of the shorter, 0.04 us for a range's part in the merge and 2.5 us for a merge
+// that might not be needed; shorter ranges where that gives 12 %.  Over 130 random batches 0.81 of the time with 4,096 keys
+// throughout (0.79 without that line, but then 13 of them are up to 9 % slower), over 90 others 0.89, three of them 1 ... 6 %
+// slower; microseconds with 512 / 1,024 / 2,048 / 4,096 keys: 4 heads, 17 sequences and 13,057 keys 13.6 / 15.7 / 19.5 /
+// 26.4; 24 and 122,882 29.3 / 21.1 / 23.5 / 32.7; 8 heads, 39 and 299,920 85 / 75 / 77 / 72; 26 and 6,458 44.1 / 43.9 / 43.9 / 41.9.
+constexpr int kMinRange = 512, kMaxRange = 4096;
+inline int range_of_mixed_call(int cu, int rows, int n_q_heads, int n_kv_heads, int64_t batch, int64_t total_q, int64_t total_k) {
+    int best = kMaxRange;
+    if (rows == kBM) return best;
+    const double others = ((double)total_q / rows + 0.3 * batch) * n_q_heads;
+    const double cached = (double)std::max<int64_t>(0, total_k - total_q);
+    double best_t = 0;
+    for (int keys = kMaxRange; keys >= kMinRange; keys /= 2) {
+        const double walk = 6 + 1.2 * std::min<double>(keys, cached) / 256;
+        const double share = (others * 12 + cached * n_kv_heads / keys * walk) / cu;
+        const double t = std::max(walk, share) + 0.25 * std::min(walk, share) + 0.04 * cached / keys + (cached > keys ? 2.5 : 0.0);
+        if (keys == kMaxRange || t < best_t) {
+            best = keys;
+            best_t = keys == kMaxRange ? 0.88 * t : t;
+        }
+    }
+    return best;
+}
+
 // Whether a batch does without a work list: the workgroups of fwd_split_kernel find their items in the offsets, a lane per
 // sequence.  That saves a launch, 3 ... 4 us, and costs every workgroup a loop over the sequences, one workgroup at a time on a
 // compute unit.  Over 36 random batches of 4 to 64 sequences, microseconds won, by workgroups (bound) and sequences: 70 x 5

@@ -738,15 +738,19 @@ int pec_attn_varlen(const pec_shape_t* shape, const void* q, const void* k, cons
 }
 
 namespace {
-constexpr int kColocRange = 4096;   // keys per range of a split one-token sequence (64 tiles)
+// keys per range of a split one-token sequence
+int coloc_range(const pec_shape_t* shape, int32_t batch, int64_t total_q, int64_t total_k, int rows) {
+    return range_of_mixed_call(compute_units(), rows, shape->n_q_heads, shape->n_kv_heads, batch, total_q, total_k);
+}
 struct ColocLayout {
     size_t cap_items, n_buckets, slot_cap;
     size_t off_counters, off_bucket, off_split, off_part_lse, off_part_out, bytes;
 };
-ColocLayout coloc_layout(int n_q_heads, int32_t batch, int64_t total_q, int64_t total_k, int rows) {
+ColocLayout coloc_layout(const pec_shape_t* shape, int32_t batch, int64_t total_q, int64_t total_k, int rows) {
+    const int n_q_heads = shape->n_q_heads;
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
     ColocLayout L;
-    L.slot_cap = (size_t)(total_k / kColocRange) + (size_t)batch;
+    L.slot_cap = (size_t)(total_k / coloc_range(shape, batch, total_q, total_k, rows)) + (size_t)batch;
     L.cap_items = (size_t)(total_q / rows) + (size_t)batch + L.slot_cap + 1;
     L.n_buckets = (size_t)(total_k / 256) + 2;
     size_t o = up(L.cap_items * sizeof(WorkItem));
@@ -761,8 +765,10 @@ ColocLayout coloc_layout(int n_q_heads, int32_t batch, int64_t total_q, int64_t 
 }  // namespace
 
 size_t pec_colocated_workspace_bytes(const pec_shape_t* shape, int32_t batch, int64_t total_q, int64_t total_k) {
-    if (!shape || shape->n_q_heads <= 0 || batch < 0 || total_q < 0 || total_k < 0) return 0;
-    return coloc_layout(shape->n_q_heads, batch, total_q, total_k, 32).bytes;   // the most any choice of rows needs
+    if (!shape || shape->n_q_heads <= 0 || shape->n_kv_heads <= 0 || batch < 0 || total_q < 0 || total_k < 0) return 0;
+    size_t most = 0;
+    for (const RowChoice& c : kRowChoices) most = std::max(most, coloc_layout(shape, batch, total_q, total_k, c.rows).bytes);
+    return most;
 }
 
 int pec_attn_colocated(const pec_shape_t* shape, const void* q, const void* k, const void* v,
@@ -780,8 +786,9 @@ int pec_attn_colocated(const pec_shape_t* shape, const void* q, const void* k, c
     if (misaligned(q) || misaligned(k) || misaligned(v) || misaligned(out) || misaligned(workspace) ||
         (reinterpret_cast<uintptr_t>(cu_seqlens_q) & 3u) || (reinterpret_cast<uintptr_t>(cu_seqlens_k) & 3u))
         return PEC_ERR_MISALIGNED;
-    const int rows = rows_of_list_call(compute_units(), shape->n_q_heads, shape->n_kv_heads, batch, total_q, total_k, 0, causal, kColocRange);
-    const ColocLayout L = coloc_layout(shape->n_q_heads, batch, total_q, total_k, rows);
+    const int rows = rows_of_list_call(compute_units(), shape->n_q_heads, shape->n_kv_heads, batch, total_q, total_k, 0, causal, kMaxRange);
+    const int range_len = coloc_range(shape, batch, total_q, total_k, rows);
+    const ColocLayout L = coloc_layout(shape, batch, total_q, total_k, rows);
     if (!workspace || workspace_bytes < pec_colocated_workspace_bytes(shape, batch, total_q, total_k)) return PEC_ERR_WORKSPACE;
     if (L.cap_items > 0x7fffffff || L.n_buckets > 0x7fffffff) return PEC_ERR_UNSUPPORTED;
 
@@ -794,7 +801,7 @@ int pec_attn_colocated(const pec_shape_t* shape, const void* q, const void* k, c
     hipStream_t st = static_cast<hipStream_t>(stream);
     FwdParams p{};
     // items of proper offsets (workgroups beyond what there is cost fwd_split_kernel a look at it each)
-    const int64_t range_item = (int64_t)kColocRange * (shape->n_q_heads / shape->n_kv_heads);   // keys of an item of ranges
+    const int64_t range_item = (int64_t)range_len * (shape->n_q_heads / shape->n_kv_heads);   // keys of an item of ranges
     p.n_items = (int32_t)std::min<int64_t>(L.cap_items, total_q / rows + batch + total_k / range_item);
     if (batch_without_list(compute_units(), rows, shape->n_q_heads, batch, total_q)) {
         p.cu_q = cu_seqlens_q;
@@ -808,7 +815,7 @@ int pec_attn_colocated(const pec_shape_t* shape, const void* q, const void* k, c
     } else {
         const int by_sequence = list_by_sequence(compute_units(), shape->n_q_heads, rows, batch, total_q);
         hipLaunchKernelGGL(build_worklist_kernel, dim3(1), dim3(1024), 0, st, cu_seqlens_q, cu_seqlens_k, (int)batch,
-                           (int)total_q, (int)total_k, rows, 256, kColocRange, (int)(shape->n_q_heads / shape->n_kv_heads),
+                           (int)total_q, (int)total_k, rows, 256, range_len, (int)(shape->n_q_heads / shape->n_kv_heads),
                            (int)L.cap_items, (int)L.slot_cap, (int)L.n_buckets, by_sequence, work, counters,
                            reinterpret_cast<int32_t*>(ws + L.off_bucket), split_seqs);
         if (hipGetLastError() != hipSuccess) return PEC_ERR_HIP;
@@ -831,7 +838,7 @@ int pec_attn_colocated(const pec_shape_t* shape, const void* q, const void* k, c
     p.scale_log2 = scale * kLog2e;
     p.part_out = part_out;
     p.part_lse = part_lse;
-    p.range_len = kColocRange;
+    p.range_len = range_len;
     if (int rc = launch_fwd(p, false, rows, st)) return rc;
 
     const dim3 grid((unsigned)shape->n_q_heads, (unsigned)std::min<int32_t>(batch, 1024));

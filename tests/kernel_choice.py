@@ -33,6 +33,9 @@ extern "C" int spans(int cu, int hq, int hkv, int64_t sq, int64_t sk, int64_t de
     return pec::spans_of_sweep(cu, hq, hkv, sq, sk, delta, causal).groups;
 }
 extern "C" int without_list(int cu, int rows, int hq, int64_t batch, int64_t tq) { return pec::batch_without_list(cu, rows, hq, batch, tq); }
+extern "C" int range_keys_of(int cu, int rows, int hq, int hkv, int64_t batch, int64_t tq, int64_t tk) {
+    return pec::range_of_mixed_call(cu, rows, hq, hkv, batch, tq, tk);
+}
 extern "C" int merged(int g, int64_t n) { return pec::merge_in_launch(g, n); }
 extern "C" int64_t ranges(int cu, int hq, int hkv, int64_t sk) { return pec::decode_default_ranges(cu, hq, hkv, sk); }
 extern "C" int split(int cu, int hq, int hkv, int64_t sk, int64_t n) { return pec::decode_on_split_kernel(cu, hq, hkv, sk, n); }
@@ -56,6 +59,7 @@ def _lib():
     L.can_stop.argtypes = [ctypes.c_int] * 2 + [i64] * 3 + [ctypes.c_int, i64]
     L.spans.argtypes = L.dense.argtypes
     L.without_list.argtypes = [ctypes.c_int] * 3 + [i64] * 2
+    L.range_keys_of.argtypes = [ctypes.c_int] * 4 + [i64] * 3
     L.merged.argtypes = [ctypes.c_int, i64]
     L.ranges.argtypes, L.ranges.restype = [ctypes.c_int] * 3 + [i64], i64
     L.split.argtypes = [ctypes.c_int] * 3 + [i64] * 2
@@ -91,6 +95,11 @@ def batch_heads(hq, hkv, len_q):
 def by_sequence(hq, rows, len_q):
     """Whether the work list of a batch keeps the items of a sequence together."""
     return bool(_lib().by_sequence(COMPUTE_UNITS, hq, rows, len(len_q), int(sum(len_q))))
+
+
+def mixed_range(hq, hkv, len_q, len_k, causal=True):
+    """Keys per range of the one-token sequences of a mixed batch."""
+    return _lib().range_keys_of(COMPUTE_UNITS, mixed_rows(hq, hkv, len_q, len_k, causal), hq, hkv, len(len_q), int(sum(len_q)), int(sum(len_k)))
 
 
 def without_list(rows, hq, len_q):

@@ -44,6 +44,27 @@ def test_small_batches_match_oracle(n, hq, hkv, first):
         assert_close(out, lse, o_ref, l_ref, "packed batch of %d sequences" % n)
 
 
+# one range more or less than a whole number, none, and ranges of all four lengths (the last argument)
+RANGES = [
+    (8, 2, [5, 1, 1, 1, 1, 1], [5, 511, 512, 513, 1, 4097], 512), (4, 1, [1, 32], [20481, 32], 512),
+    (4, 1, [1, 1, 40], [61441, 1024, 40], 1024), (8, 2, [1, 200, 1, 1], [150016, 200, 2047, 2049], 2048),
+    (4, 1, [1, 1], [900001, 4096], 4096), (8, 8, [1, 1], [8193, 1023], 512), (16, 1, [1] * 70, [600 + 13 * i for i in range(70)], 2048)]
+
+
+@pytest.mark.parametrize("hq,hkv,len_q,len_k,keys", RANGES)
+def test_key_ranges_of_every_length(hq, hkv, len_q, len_k, keys):
+    cq, ck = synth.cu_seqlens_of(len_q), synth.cu_seqlens_of(len_k)
+    q, _, _ = synth.qkv(9960, int(cq[-1]), 1, hq, hkv)
+    _, k, v = synth.qkv(9961, 1, int(ck[-1]), hq, hkv)
+    o_ref, l_ref = oracle.colocated(q, k, v, cq, ck, causal=True)
+    for dt in (torch.float32, torch.bfloat16):
+        out = torch.full(o_ref.shape, float("nan"), dtype=dt, device=DEV)
+        lse = torch.full(l_ref.shape, float("nan"), dtype=torch.float32, device=DEV)
+        pec.pec_attn_colocated(q.to(DEV), k.to(DEV), v.to(DEV), torch.from_numpy(cq).to(DEV), torch.from_numpy(ck).to(DEV), True,
+                               out_dtype=dt, out=out, lse=lse)
+        assert_close(out, lse, o_ref, l_ref, "ranges of %d keys" % keys)
+
+
 def test_list_with_an_item_heavier_than_its_buckets():
     len_q, len_k = [3] + [1] * 65 + [70], [2048 * 256 + 1] + [1] * 65 + [70]
     cq, ck = synth.cu_seqlens_of(len_q), synth.cu_seqlens_of(len_k)

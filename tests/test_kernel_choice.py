@@ -1,9 +1,11 @@
 """The GPU tests that are about one kernel run on it: the library's own choice, asked for the sizes that they use."""
+import ctypes
 import random
 
 import pytest
 
 import kernel_choice as choice
+from paper_2409_15104_amd import binding
 import test_gpu_decode_ranges as decode
 import test_gpu_head_tiles as head_tiles
 import test_gpu_pipelined_kernel as pipelined
@@ -12,6 +14,11 @@ import test_gpu_small_sweeps as small_sweeps
 import test_gpu_spans as spans
 import test_gpu_underfilled as underfilled
 import test_gpu_work_list as work_list
+
+
+@pytest.fixture(scope="module")
+def lib():
+    return binding.lib()
 
 
 def cases(test):
@@ -139,3 +146,17 @@ def test_small_batch_cases_run_with_and_without_a_list():
     assert [g[1:] for g in got] == [(True, True)] * 7 + [(False, False)] * 4
     assert {r for g in got[:7] for r in g[0]} == {32, 64}
     assert not choice.without_list(256, 1, [8] * 8)
+
+
+def test_key_range_cases_have_ranges_of_every_length():
+    assert [choice.mixed_range(*c[:4]) for c in small_batches.RANGES] == [c[4] for c in small_batches.RANGES]
+    assert choice.mixed_range(32, 8, [1000] * 100 + [1], [1000] * 100 + [50000]) == 4096      # on fwd_il_kernel
+
+
+@pytest.mark.parametrize("hq,hkv,batch,tq,tk", [(8, 2, 6, 10, 5635), (64, 8, 3, 80, 400000), (8, 1, 40, 3000, 90000), (32, 8, 300, 200000, 900000)])
+def test_workspace_of_a_mixed_batch_holds_the_slots_of_every_choice(lib, hq, hkv, batch, tq, tk):
+    need = lib.pec_colocated_workspace_bytes(ctypes.byref(binding.PecShape(hq, hkv, 128, binding.PEC_F32, 0.0, 0)), batch, tq, tk)
+    for rows in (32, 64, 256):
+        keys = choice._lib().range_keys_of(choice.COMPUTE_UNITS, rows, hq, hkv, batch, tq, tk)
+        slots = tk // keys + batch
+        assert need >= slots * hq * 129 * 4 + (tq // rows + batch + slots + 1) * 32
