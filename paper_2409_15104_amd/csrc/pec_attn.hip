@@ -367,14 +367,15 @@ int pec_sp_prefill_resumable(const pec_shape_t* shape, const void* q, const void
         return hipGetLastError() == hipSuccess ? PEC_OK : PEC_ERR_HIP;
     };
     const int64_t delta = std::max<int64_t>(-s_q - 1, std::min<int64_t>(q_off, s_kv));      // as in chunk_impl
-    if (s_q > 0 && !resume && !sweep_can_stop(compute_units(), shape->n_q_heads, s_q, s_kv, delta, causal != 0, chunk / kBN)) {
+    const bool can_stop = s_q > 0 && sweep_can_stop(compute_units(), shape->n_q_heads, s_q, s_kv, delta, causal != 0, chunk / kBN);
+    if (s_q > 0 && !resume && !can_stop) {
         if (int rc = chunk_impl(shape, q, k, v, s_q, s_kv, q_off, 0, causal, out, shape->out_dtype == PEC_F32, lse, nullptr, nullptr,
                                 nullptr, s_q, stream))
             return rc;
         return set_table(1);      // (a call that resumes such a sweep finds everything done)
     }
     SpanPlan spans{0, 0};
-    if (s_q > 0) spans = spans_of_sweep(compute_units(), shape->n_q_heads, shape->n_kv_heads, s_q, s_kv, delta, causal != 0);
+    if (can_stop) spans = spans_of_sweep(compute_units(), shape->n_q_heads, shape->n_kv_heads, s_q, s_kv, delta, causal != 0);
     if (spans.groups) {
         progress = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + span_slots_bytes(spans.groups));
         words = (int64_t)span_table_words(spans.groups);

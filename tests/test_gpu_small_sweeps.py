@@ -19,6 +19,7 @@ DEV = "cuda:0"
     (700, 2900, 4, 1, 2200, 960, True, 1),     # segments of 15 tiles
     (448, 448, 8, 1, 0, 448, True, 1),
     (1, 100, 3, 3, 99, 64, True, 1),
+    (256, 16384, 8, 1, 16128, 512, True, 1),   # would be cut into spans if there were something to stop at
     (513, 900, 64, 8, 0, 1024, False, 1),      # more rows and heads, one segment
     (2048, 1000, 40, 8, 0, 128, True, 2),      # more items than compute units: the second of a workgroup is left out
 ])

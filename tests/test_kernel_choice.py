@@ -128,7 +128,8 @@ def test_sweeps_that_cannot_stop_are_those_whose_tiles_have_no_boundary_to_stop_
 def test_small_sweep_cases():
     got = [choice.sweep_can_stop(hq, sq, sk, q_off, chunk, causal) for sq, sk, hq, hkv, q_off, chunk, causal, _ in
            cases(small_sweeps.test_sweeps_around_the_line_of_those_that_can_stop)]
-    assert got == [False, True, False, True, False, False, False, False, True]
+    assert got == [False, True, False, True, False, False, False, False, False, True]
+    assert choice.sweep_spans(8, 1, 256, 16384, 16128) > 0
 
 
 def test_span_cases():
