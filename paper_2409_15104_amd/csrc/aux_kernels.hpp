@@ -450,33 +450,29 @@ __global__ __launch_bounds__(1024) void build_worklist_kernel(const int32_t* __r
 // Merge of the pieces of every item that fwd_il_kernel<kFwdSpan> has cut, 32 rows of it per workgroup: grid (spans - 1, 8).
 // Workgroup x does the item that span x + 1 starts inside, if no earlier span does.  Its pieces are the last one of span x
 // and the first ones of the spans that start inside it.  Memory-bound: 132 KB per piece are read once, the item is written.
-// With a progress table an item is merged by the first launch that finds all its pieces done.
+// An item is merged by the first launch that finds all its pieces done.
 __global__ __launch_bounds__(256) void span_merge_kernel(const FwdParams p) {
     const int w0 = blockIdx.x + 1, strip = blockIdx.y;
     const int pos = span_start(p, w0), n_spans = gridDim.x + 1;
     const SpanPos at = span_locate(p, pos);
     const int unit_start = pos - at.tile;
     if (at.tile == 0 || unit_start < span_start(p, w0 - 1)) return;
-    const int units = p.group >> p.log_heads;
-    const int item = at.unit / units % p.n_items;
+    const int item = at.unit / p.group % p.n_items;
     const int unit_end = unit_start + span_steps_of(p, item);
     int w_last = w0;
     while (w_last + 1 < n_spans && span_start(p, w_last + 1) < unit_end) ++w_last;
-    if (p.progress) {
-        int32_t* const merged = p.progress + n_spans + 8 * w0 + strip;
-        bool there = *merged == 0;
-        for (int w = w0 - 1; w <= w_last; ++w)
-            there = there && p.progress[w] >= min(unit_end, span_start(p, w + 1)) - span_start(p, w);
-        if (!there) return;
-        __syncthreads();      // everyone has read the word
-        if (threadIdx.x == 0) {
-            *merged = 1;
-            if (strip == 0) atomicSub(p.pending, 1);
-        }
+    int32_t* const merged = p.progress + n_spans + 8 * w0 + strip;
+    bool there = *merged == 0;
+    for (int w = w0 - 1; w <= w_last; ++w)
+        there = there && p.progress[w] >= min(unit_end, span_start(p, w + 1)) - span_start(p, w);
+    if (!there) return;
+    __syncthreads();      // everyone has read the word
+    if (threadIdx.x == 0) {
+        *merged = 1;
+        if (strip == 0) atomicSub(p.pending, 1);
     }
-    const int bm = 256 >> p.log_heads;
-    const int head = at.unit / units / p.n_items * p.group + (at.unit % units << p.log_heads) + (strip >> (3 - p.log_heads));
-    const int row0 = (p.causal ? p.n_items - 1 - item : item) * bm + ((strip << 5) & (bm - 1));
+    const int head = at.unit / p.group / p.n_items * p.group + at.unit % p.group;
+    const int row0 = (p.causal ? p.n_items - 1 - item : item) * 256 + strip * 32;
     const int n_pieces = w_last - w0 + 2, c = threadIdx.x & 31;
     auto slot_row = [&](int i, int r) { return (int64_t)(2 * (w0 - 1 + i) + (i == 0 ? 1 : 0)) * 256 + strip * 32 + r; };
     for (int r = threadIdx.x >> 5; r < 32; r += 8) {
@@ -500,11 +496,8 @@ __global__ __launch_bounds__(256) void span_merge_kernel(const FwdParams p) {
             for (int e = 0; e < 4; ++e) a[e] *= inv;
         }
         const int64_t idx = ((int64_t)row * p.n_q_heads + head) * kHeadDim + 4 * c;
-        if (p.acc_out) *reinterpret_cast<f32x4*>(p.acc_out + idx) = a;
-        if (p.out) {
-            if (p.out_f32) *reinterpret_cast<f32x4*>(static_cast<float*>(p.out) + idx) = a;
-            else *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(p.out) + idx) = __builtin_convertvector(a, bf16x4);
-        }
+        if (p.out_f32) *reinterpret_cast<f32x4*>(static_cast<float*>(p.out) + idx) = a;
+        else *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(p.out) + idx) = __builtin_convertvector(a, bf16x4);
         if (c == 0) p.lse[(int64_t)head * p.lse_stride + row] = mx == -INFINITY ? mx : mx + logf(den);
     }
 }

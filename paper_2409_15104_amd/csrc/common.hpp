@@ -103,10 +103,10 @@ struct FwdParams {
     int32_t* pending;
     const int32_t* stop;
     int32_t seg_tiles;
-    // dense calls cut into one span of tile steps per workgroup (fwd_il_kernel<kFwdSpan>): the first span_extra workgroups
-    // take span_len + 1 steps, the others span_len; span_kvh steps per KV head.  A piece of an item leaves its fp32 result in
-    // one of its workgroup's two slots, slot_out [2 x workgroups][256][128] and slot_lse [2 x workgroups][256].  With a
-    // progress table: progress[w] steps of span w are done; words behind it say which items span_merge_kernel has merged.
+    // resumable sweep cut into one span of tile steps per workgroup (fwd_il_kernel<kFwdSpan>): the first span_extra workgroups
+    // take span_len + 1 steps, the others span_len; span_kvh steps per KV head.  A piece of an item leaves its fp32 result, or
+    // its state, in one of its workgroup's two slots, slot_out [2 x workgroups][256][128] and slot_lse [2 x workgroups][256].
+    // progress[w] steps of span w are done; words behind them say which items span_merge_kernel has merged.
     float* slot_out;
     float* slot_lse;
     int32_t span_len, span_extra, span_kvh;
@@ -122,10 +122,10 @@ struct SplitSeq {        // a one-token sequence whose keys are cut into ranges
     int32_t seq, slot0, n_ranges, pad;
 };
 
-// Tile steps of a query tile (in work order, number `item`) of a dense call cut into spans, at least one.
+// Tile steps of a query tile (in work order, number `item`) of a sweep cut into spans, at least one.
 __device__ __forceinline__ int span_steps_of(const FwdParams& p, int item) {
-    const int bm = 256 >> p.log_heads, qt = p.causal ? p.n_items - 1 - item : item;
-    const int keys = p.causal ? max(0, min(p.sk, min(p.sq, (qt + 1) * bm) + p.delta)) : p.sk;
+    const int qt = p.causal ? p.n_items - 1 - item : item;
+    const int keys = p.causal ? max(0, min(p.sk, min(p.sq, (qt + 1) * 256) + p.delta)) : p.sk;
     return max(1, (keys + kBN - 1) / kBN);
 }
 __device__ __forceinline__ int span_start(const FwdParams& p, int w) { return w * p.span_len + min(w, p.span_extra); }
@@ -136,11 +136,11 @@ struct SpanPos {
     int unit, tile;
 };
 __device__ __forceinline__ SpanPos span_locate(const FwdParams& p, int pos) {
-    const int units = p.group >> p.log_heads, lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63;
     const int kvh = pos / p.span_kvh;
     int left = pos - kvh * p.span_kvh;
     for (int item0 = 0;; item0 += 64) {
-        const int own = item0 + lane < p.n_items ? span_steps_of(p, item0 + lane) * units : 0;
+        const int own = item0 + lane < p.n_items ? span_steps_of(p, item0 + lane) * p.group : 0;
         int upto = own;                       // steps of the query tiles up to this lane's
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
@@ -150,9 +150,9 @@ __device__ __forceinline__ SpanPos span_locate(const FwdParams& p, int pos) {
         const uint64_t behind = __ballot(upto > left);
         if (behind != 0 || item0 + 64 >= p.n_items) {
             const int l = behind != 0 ? __builtin_ctzll(behind) : 63;
-            const int in_tile = left - (__shfl(upto, l) - __shfl(own, l)), steps = __shfl(own, l) / units;
+            const int in_tile = left - (__shfl(upto, l) - __shfl(own, l)), steps = __shfl(own, l) / p.group;
             const int head = in_tile / max(1, steps);
-            return SpanPos{__builtin_amdgcn_readfirstlane((kvh * p.n_items + item0 + l) * units + head),
+            return SpanPos{__builtin_amdgcn_readfirstlane((kvh * p.n_items + item0 + l) * p.group + head),
                            __builtin_amdgcn_readfirstlane(in_tile - head * steps)};
         }
         left -= __shfl(upto, 63);

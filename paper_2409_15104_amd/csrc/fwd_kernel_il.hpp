@@ -55,10 +55,9 @@ __device__ __forceinline__ void scale_acc_in_place(f32x16 (&o)[4], float a) {
 // kFwdDense -- one call = one problem, work items dealt in fixed rounds (ring step, fused merge, key splits, the
 // plain sweep); kFwdSweep -- the resumable sweep (progress table, stop word, state of stopped items);
 // kFwdList -- device-built work lists (packed and colocated batch), work items drawn at run time;
-// kFwdSpan -- one problem per call, stoppable or not, as one span of tile steps per workgroup: the items, one after the other,
-// are cut wherever a workgroup's equal share ends, and span_merge_kernel merges the pieces of an item.
+// kFwdSpan -- the resumable sweep as one span of tile steps per workgroup: the items, one after the other, are cut wherever a
+// workgroup's equal share ends, and span_merge_kernel merges the pieces of an item.
 enum { kFwdDense = 0, kFwdSweep = 1, kFwdList = 2, kFwdSpan = 3 };
-constexpr int kSlotFloats = 256 * kHeadDim;     // of one piece's result
 
 template <int MODE>
 __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
@@ -88,7 +87,7 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
     // every workgroup draws its next item from its XCD's counter, and from the next XCD's once that share is
     // used up; the heaviest items come first in the list, so the launch ends on the lightest ones.
     const int n_items_eff = kList ? min(*p.n_work, p.n_items) : p.n_items;
-    const int log_heads = kSweep ? 0 : p.log_heads;
+    const int log_heads = kStops ? 0 : p.log_heads;
     // work units per item and KV head: lists hold tiles of 256 positions, cut further inside this kernel
     const int units = kList ? p.group : p.group >> log_heads;
     const WorkOrder order(n_items_eff, units, p.n_kv_heads);
@@ -243,7 +242,7 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
         g.o_off0 = g.q_off0;
         g.lse_off0 = (int64_t)head * p.lse_stride;
         g.part = false;
-        if (!kSweep && p.kv_split_len > 0) {   // the work item is a key range; all of it is visible (decode)
+        if (!kStops && p.kv_split_len > 0) {   // the work item is a key range; all of it is visible (decode)
             qt = 0;
             g.kv_tok0 = (int64_t)item * p.kv_split_len;
             g.sk = (int)max((int64_t)0, min((int64_t)p.kv_split_len, (int64_t)p.sk - g.kv_tok0));
@@ -289,7 +288,7 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
     if constexpr (kSpan) {
         const int start = span_start(p, span);
         span_all = span_start(p, span + 1) - start;
-        if (p.progress) span_done = max(0, p.progress[span]);     // (a table that was never initialised leads nowhere else)
+        span_done = max(0, p.progress[span]);     // (a table that was never initialised leads nowhere else)
         if (span_done >= span_all) return;
         const SpanPos at = span_locate(p, start + span_done);
         unit_now = at.unit;
@@ -322,7 +321,7 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
         g.kv_tok0 = (int64_t)tile_now * kBN;
         g.sk = (int)(min((int64_t)g.sk, (int64_t)tile_end * kBN) - g.kv_tok0);
         g.delta -= (int)g.kv_tok0;
-        acc_in = kept ? p.slot_out : tile_now == 0 ? p.acc_in : nullptr;
+        acc_in = kept ? p.slot_out : nullptr;
     } else if constexpr (kAhead) {
         g = next;
         if (kList && g.part) {
@@ -393,15 +392,10 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
     if (acc_in) {
         const int row = rw0 + l32;
         if (row < sq) {
-            int64_t lse_at = lse_off0 + row, acc_at = o_off0 + row * q_stride;
-            if constexpr (kSpan) {
-                if (kept) {
-                    lse_at = piece_slot * BM + wave * 32 + l32;
-                    acc_at = lse_at * kHeadDim;
-                }
-            }
-            const float lin = (kSpan && kept ? p.slot_lse : p.lse_in)[lse_at];
-            const bool raw = kSpan ? kept : kSweep;   // state of a stopped item, stored as the registers held it
+            const int64_t lse_at = kSpan ? piece_slot * BM + wave * 32 + l32 : lse_off0 + row;
+            const int64_t acc_at = kSpan ? lse_at * kHeadDim : o_off0 + row * q_stride;
+            const float lin = (kSpan ? p.slot_lse : p.lse_in)[lse_at];
+            constexpr bool raw = kStops;   // state of a stopped item, stored as the registers held it
             if (raw || lin != -INFINITY) {
                 m_run = raw ? lin : lin * kLog2e;
                 l_run = raw ? p.l_part[lse_at * 2 + hl] : (hl == 0 ? 1.f : 0.f);
@@ -953,7 +947,7 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
     }
     if constexpr (kSpan) {
         span_done += stopped ? stop_b : tile_end - tile_now;
-        if (p.progress && threadIdx.x == 0) {
+        if (threadIdx.x == 0) {
             p.progress[span] = span_done;
             if (whole && !stopped) atomicSub(p.pending, 1);
         }
