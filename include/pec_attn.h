@@ -5,9 +5,10 @@
  * C ABI: plain pointers and sizes only.  Unless said otherwise every pointer is a
  * DEVICE pointer owned by the caller, 16-byte aligned, and every call is
  * asynchronous on `stream` (a hipStream_t passed as void*; NULL = the default
- * stream).  The library keeps no state between calls (every option travels in
- * pec_shape_t.flags, so concurrent callers cannot disturb each other), allocates
- * no device memory, and never synchronises the device.
+ * stream).  The library keeps no state between calls but a count of them that no
+ * result depends on (every option travels in pec_shape_t.flags, so concurrent callers
+ * cannot disturb each other), allocates no device memory, and never synchronises the
+ * device.
  *
  * Layouts (row-major, contiguous, counts in elements):
  *   q, out  : [tokens, n_q_heads, 128]   bf16 (out: bf16 or fp32, see out_dtype)
@@ -245,8 +246,9 @@ size_t pec_colocated_workspace_bytes(const pec_shape_t* shape, int32_t batch, in
  * lse [Hq] form a partial pair over this shard: results of several shards / GPUs (the paper's
  * example merges the outputs of two GPUs) combine with pec_attn_merge (use out_dtype PEC_F32).
  * sk == 0 gives out = 0, lse = -inf.  workspace: pec_decode_workspace_bytes() bytes, whatever they hold; few ranges are
- * merged by the launch that makes them, which keeps some words behind the partial results for it (a workspace of
- * n_splits * n_q_heads * 129 * 4 bytes, without room for them, is taken too and costs a second launch).
+ * merged by the launch that makes them, which keeps some words behind the partial results for it.  A workspace of
+ * n_splits * n_q_heads * 129 * 4 bytes, without room for them, is taken too and costs a second launch, and so does a call on
+ * a stream that is being captured; the results have the same bits.
  * HBM-bound: K and V are read once, 2 * sk * Hkv * 128 * 2 bytes.
  */
 int pec_decode_splitkv(const pec_shape_t* shape, const void* q, const void* k, const void* v, int64_t sk,
@@ -270,7 +272,7 @@ size_t pec_decode_workspace_bytes(const pec_shape_t* shape, int32_t n_splits);
  *   Every call on a GPU uses that GPU's one buffer: two calls that overlap in time on the same GPU
  *   (different streams, different threads) race on it and give undefined results.  Calls on one
  *   stream, or otherwise ordered, are safe; nothing in the buffer needs clearing between calls
- *   (every partial a call reads it has written itself, and the words that say so are new for every call).
+ *   (every partial a call reads it has written itself, and the words that say so hold a number that is new for every call).
  */
 #define PEC_DECODE_STATIC_SCRATCH_BYTES ((size_t)8 << 20)
 int pec_decode_splitkv_static(const pec_shape_t* shape, const void* q, const void* k, const void* v, int64_t sk,

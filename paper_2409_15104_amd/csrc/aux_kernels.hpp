@@ -164,6 +164,7 @@ __global__ __launch_bounds__(kCombineThreads) void combine_splits_kernel(const f
 
 // The same for up to N ranges by one wavefront, without LDS or barriers: lane i holds the weight of range i, each half of the
 // wavefront sums every second range, all loads in flight at once.  SHARED: the ranges come from this launch (load_shared()).
+constexpr int kMergeRanges = 32;       // most ranges that one wavefront merges
 template <int N, bool SHARED>
 __device__ __forceinline__ void combine_few(const float* o_part, const float* lse_part, int n_splits, int n_heads, int h,
                                             void* out, bool out_f32, float* lse) {
@@ -218,11 +219,12 @@ __device__ __forceinline__ void combine_few(const float* o_part, const float* ls
 // As a kernel, one wavefront per head: with few ranges combine_splits_kernel is made of the trips between its sixteen
 // wavefronts.  GPU time of a decode step of 32 heads with ranges of 32 keys, that / this: 1 range 8.0 / 7.0 us, 8 ranges
 // 8.1 / 7.6, 16 ranges 8.6 / 8.3, 24 ranges 8.65 / 8.61, 32 ranges 8.84 / 8.92.
+// A step whose launch merges its own ranges, up to kMergeRanges, is merged here as well where that launch cannot: same bits.
 constexpr int kCombineFew = 24;
 template <bool OUT_F32>
 __global__ __launch_bounds__(64) void combine_few_kernel(const float* o_part, const float* lse_part, int n_splits, int n_heads,
                                                          void* out, float* lse) {
-    combine_few<kCombineFew, false>(o_part, lse_part, n_splits, n_heads, blockIdx.x, out, OUT_F32, lse);
+    combine_few<kMergeRanges, false>(o_part, lse_part, n_splits, n_heads, blockIdx.x, out, OUT_F32, lse);
 }
 
 // The same combination for the one-token sequences of a colocated batch: split_seqs lists

@@ -79,8 +79,9 @@ struct FwdParams {
     int32_t kv_split_len;
     int64_t split_out_stride, split_lse_stride;   // elements
     // key ranges of a decode step whose last workgroup per KV head merges them (fwd_split_kernel; null: a kernel of its own
-    // does): per KV head an epoch and one word per range (last_workgroup()), and where the results go
+    // does): one word per KV head and range, the mark that this call writes there (last_workgroup()), and where the results go
     uint64_t* arrived;
+    uint64_t mark;
     void* merged_out;
     float* merged_lse;
     int32_t merged_f32;

@@ -41,34 +41,24 @@ constexpr int kSplitTileBytes = kSplitTile * kRowBytes;     // 8 KiB for K, 8 Ki
 // Merge of a decode step's key ranges in the launch that makes them, by whichever workgroup of a KV head finds that all of
 // its ranges are there: every workgroup writes its partial results, then its word, then reads the words of all ranges; of
 // the workgroups that do so last, at least one sees them all (several may: they write the same results).  A word says
-// "there" by holding arrived_mark() of the epoch, which every workgroup read when it started and which one that saw them
-// all raises by one: nothing needs clearing before or after a call, whatever the memory held (64 mixed bits, different for
-// every epoch, KV head and number of ranges, so that neither other data nor an earlier call's words pass for the mark).
-constexpr int kMergeRanges = 32;       // most ranges that one wavefront merges
-__device__ __forceinline__ uint64_t arrived_mark(uint64_t epoch, int kvh, int n_ranges) {
-    uint64_t x = epoch + 0x9e3779b97f4a7c15ull * (uint64_t)(kvh * (kMergeRanges + 1) + n_ranges);   // the splitmix64 mixer
-    x = (x ^ (x >> 30)) * 0xbf58476d1ce4e5b9ull;
-    x = (x ^ (x >> 27)) * 0x94d049bb133111ebull;
-    return x ^ (x >> 31);
-}
+// "there" by holding the mark of this call, which the host makes anew for every launch (merge_mark(); a launch that a graph
+// replays would bring the same one again, so captured steps are merged by a launch of their own).  Words stay behind a call,
+// and any of them may be overwritten or put back between calls: no call has the mark of another.
 
-// Called by all wavefronts of a workgroup behind its stores; `range`: its key range, `words`: epoch and words of its KV head.
-__device__ __forceinline__ bool last_workgroup(uint64_t* words, uint64_t epoch, uint64_t mark, int range, int n_ranges, int wave) {
+// Called by all wavefronts of a workgroup behind its stores; `range`: its key range, `words`: the words of its KV head.
+__device__ __forceinline__ bool last_workgroup(uint64_t* words, uint64_t mark, int range, int n_ranges, int wave) {
     __shared__ int all_there;
     __builtin_amdgcn_s_waitcnt(0x0F70);    // vmcnt 0: this wavefront's results (store_shared()) are in place
     asm volatile("" ::: "memory");
     __syncthreads();
     if (wave == 0) {
         const int lane = threadIdx.x & 63;
-        if (lane == 0) __hip_atomic_store(words + 1 + range, mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (lane == 0) __hip_atomic_store(words + range, mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __builtin_amdgcn_s_waitcnt(0x0F70);    // the word is in place before the others are read
         asm volatile("" ::: "memory");
-        const bool there = lane >= n_ranges || __hip_atomic_load(words + 1 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == mark;
+        const bool there = lane >= n_ranges || __hip_atomic_load(words + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == mark;
         const bool all = __all(there);
-        if (lane == 0) {
-            all_there = all;
-            if (all) __hip_atomic_store(words, epoch + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        if (lane == 0) all_there = all;
     }
     __syncthreads();
     return all_there;
@@ -177,9 +167,7 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void fwd_split_kernel(const Fw
     void* out_ptr = p.out;
     float* lse_ptr = p.lse;
     int out_f32 = p.out_f32;
-    uint64_t epoch = 0;
     if constexpr (DECODE) {   // the item is a key range, all of it visible; the heads of a KV group are the rows
-        if (p.arrived && wave == 0) epoch = __hip_atomic_load(p.arrived + (int64_t)kvh * (n_items + 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         qt = 0;
         sq = p.sq;
         q_stride = p.q_row_stride;
@@ -507,7 +495,7 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void fwd_split_kernel(const Fw
         }
     }
     if constexpr (DECODE) {
-        if (!p.arrived || !last_workgroup(p.arrived + (int64_t)kvh * (n_items + 1), epoch, arrived_mark(epoch, kvh, n_items), item, n_items, wave))
+        if (!p.arrived || !last_workgroup(p.arrived + (int64_t)kvh * n_items, p.mark, item, n_items, wave))
             return;
         const int n_heads = p.n_kv_heads * sq;
         for (int h = wave; h < sq; h += KS)

@@ -274,6 +274,16 @@ inline bool decode_on_split_kernel(int cu, int n_q_heads, int n_kv_heads, int64_
 // over and over on one cache, where the host is the slower: 12.3 -> 10.2.
 inline bool merge_in_launch(int group, int64_t n_splits) { return group * n_splits <= 64; }
 
+// What the words of such a call hold once their ranges are there: call number n of a process, a mixer of 64 bits (splitmix64)
+// on a stepped seed of the process.  Both are one to one, so no two calls of a process have the same mark; that data of
+// another origin passes for it takes 64 equal bits.
+inline uint64_t merge_mark(uint64_t seed, uint64_t n) {
+    uint64_t x = seed + 0x9e3779b97f4a7c15ull * n;
+    x = (x ^ (x >> 30)) * 0xbf58476d1ce4e5b9ull;
+    x = (x ^ (x >> 27)) * 0x94d049bb133111ebull;
+    return x ^ (x >> 31);
+}
+
 // Key ranges of a decode step whose caller leaves the number to the library: as many as give every compute unit a workgroup
 // of fwd_split_kernel, of 256 keys at least (a tile of 32 for each of eight wavefronts) -- or, with more than 11 KV heads
 // and 768 keys per compute unit in all, of decode_kernel, whose workgroups read four neighbouring KV heads of a token.

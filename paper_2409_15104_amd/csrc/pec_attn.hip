@@ -4,7 +4,12 @@
 
 #include <hip/hip_runtime.h>
 
+#include <sys/random.h>
+#include <time.h>
+#include <unistd.h>
+
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdint>
 #include <cstdlib>
@@ -448,13 +453,36 @@ int pec_sp_prefill_step(const pec_shape_t* shape, const void* q, const void* k, 
 namespace {
 
 // A decode step's workspace: the fp32 partial O and LSE of every (range, query head), then, for the merge by the last
-// workgroup of each KV head, an epoch and a word per range.  Workspaces without these words do too: two launches then.
+// workgroup of each KV head, a word per range.  Workspaces without these words do too: two launches then.
 size_t decode_partial_bytes(const pec_shape_t* shape, int32_t n_splits) {
     return (size_t)n_splits * shape->n_q_heads * (kHeadDim + 1) * sizeof(float);
 }
 size_t decode_words_offset(const pec_shape_t* shape, int32_t n_splits) { return (decode_partial_bytes(shape, n_splits) + 7) & ~(size_t)7; }
 size_t decode_words_bytes(const pec_shape_t* shape, int32_t n_splits) {
-    return n_splits > kMergeRanges ? 0 : (size_t)std::max(0, shape->n_kv_heads) * (n_splits + 1) * sizeof(uint64_t);
+    return n_splits > kMergeRanges ? 0 : (size_t)std::max(0, shape->n_kv_heads) * n_splits * sizeof(uint64_t);
+}
+
+// The mark of the next call that merges its ranges in the launch (kernel_choice.hpp), from any thread.
+uint64_t next_merge_mark() {
+    static const uint64_t seed = [] {
+        uint64_t s = 0;
+        if (getentropy(&s, sizeof s) != 0) {
+            timespec t{};
+            clock_gettime(CLOCK_REALTIME, &t);
+            s = (uint64_t)t.tv_sec * 1000000000u + (uint64_t)t.tv_nsec + ((uint64_t)getpid() << 40);
+        }
+        return s;
+    }();
+    static std::atomic<uint64_t> calls{0};
+    return merge_mark(seed, calls.fetch_add(1, std::memory_order_relaxed));
+}
+
+// Whether what is launched on the stream is recorded, to run again with the same arguments.
+bool is_captured(hipStream_t st) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();      // the legacy stream during another one's capture
+    return true;
 }
 
 }  // namespace
@@ -480,7 +508,7 @@ namespace {
 static_assert(PEC_DECODE_STATIC_SCRATCH_BYTES == (size_t)kStaticScratchBytes, "the default range count reckons with it");
 // Behind the partials the words of the merge, for as many ranges and KV heads as fwd_split_kernel takes on any device.
 constexpr size_t kStaticWords = 1024;
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + 2 * kStaticWords * sizeof(uint64_t)];
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kStaticWords * sizeof(uint64_t)];
 
 int static_scratch(void** out) {
     static void* ptr[64] = {nullptr};
@@ -507,6 +535,7 @@ int decode_impl(const pec_shape_t* shape, float scale, const void* q, const void
 
     const bool split = decode_on_split_kernel(compute_units(), shape->n_q_heads, shape->n_kv_heads, sk, n_splits);
     const bool f32 = shape->out_dtype == PEC_F32;
+    const bool in_launch = split && n_splits <= kMergeRanges && merge_in_launch(g, n_splits);
     bool merged = false;
     if (g <= 32 && !split) {   // one key range per wavefront (decode_kernel.hpp)
         DecodeParams d{};
@@ -558,8 +587,9 @@ int decode_impl(const pec_shape_t* shape, float scale, const void* q, const void
         p.lse = lse;
         p.out_f32 = f32;
         merged = true;
-    } else if (split && words && n_splits <= kMergeRanges && merge_in_launch(g, n_splits)) {
+    } else if (in_launch && words && !is_captured(st)) {
         p.arrived = static_cast<uint64_t*>(words);
+        p.mark = next_merge_mark();
         p.merged_out = out;
         p.merged_lse = lse;
         p.merged_f32 = f32;
@@ -572,7 +602,7 @@ int decode_impl(const pec_shape_t* shape, float scale, const void* q, const void
     if (hipGetLastError() != hipSuccess) return PEC_ERR_HIP;
     }
     if (merged) return PEC_OK;
-    const bool few = n_splits <= kCombineFew;
+    const bool few = in_launch || n_splits <= kCombineFew;
     auto* const merge = few ? (f32 ? combine_few_kernel<true> : combine_few_kernel<false>)
                             : (f32 ? combine_splits_kernel<true> : combine_splits_kernel<false>);
     hipLaunchKernelGGL(merge, dim3(shape->n_q_heads), dim3(few ? 64 : kCombineThreads), 0, st, o_part, lse_part, (int)n_splits,
@@ -615,7 +645,7 @@ int pec_decode_splitkv_static(const pec_shape_t* shape, const void* q, const voi
     void* ws = nullptr;
     if (int rc = static_scratch(&ws)) return rc;
     char* const words = static_cast<char*>(ws) + kStaticScratchBytes;
-    const bool room = decode_words_bytes(shape, n_splits) <= 2 * kStaticWords * sizeof(uint64_t);
+    const bool room = decode_words_bytes(shape, n_splits) <= kStaticWords * sizeof(uint64_t);
     return decode_impl(shape, scale, q, k, v, sk, n_splits, out, lse, ws, room ? words : nullptr, stream);
 }
 

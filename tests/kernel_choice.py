@@ -37,6 +37,7 @@ extern "C" int range_keys_of(int cu, int rows, int hq, int hkv, int64_t batch, i
     return pec::range_of_mixed_call(cu, rows, hq, hkv, batch, tq, tk);
 }
 extern "C" int merged(int g, int64_t n) { return pec::merge_in_launch(g, n); }
+extern "C" uint64_t mark(uint64_t seed, uint64_t n) { return pec::merge_mark(seed, n); }
 extern "C" int64_t ranges(int cu, int hq, int hkv, int64_t sk) { return pec::decode_default_ranges(cu, hq, hkv, sk); }
 extern "C" int split(int cu, int hq, int hkv, int64_t sk, int64_t n) { return pec::decode_on_split_kernel(cu, hq, hkv, sk, n); }
 """
@@ -61,6 +62,7 @@ def _lib():
     L.without_list.argtypes = [ctypes.c_int] * 3 + [i64] * 2
     L.range_keys_of.argtypes = [ctypes.c_int] * 4 + [i64] * 3
     L.merged.argtypes = [ctypes.c_int, i64]
+    L.mark.argtypes, L.mark.restype = [ctypes.c_uint64] * 2, ctypes.c_uint64
     L.ranges.argtypes, L.ranges.restype = [ctypes.c_int] * 3 + [i64], i64
     L.split.argtypes = [ctypes.c_int] * 3 + [i64] * 2
     return L
@@ -119,6 +121,11 @@ def mixed_rows(hq, hkv, len_q, len_k, causal=True):
 def merged_in_launch(hq, hkv, sk, n_splits):
     """Whether a decode step of so many ranges is one launch."""
     return bool(decode_kernel_of(hq, hkv, sk, n_splits)[1] == "fwd_split_kernel" and n_splits <= 32 and _lib().merged(hq // hkv, n_splits))
+
+
+def merge_mark(seed, n):
+    """What the words of call number n of a process hold where the launch merges its own key ranges."""
+    return _lib().mark(seed, n)
 
 
 def decode_kernel_of(hq, hkv, sk, n_splits):
