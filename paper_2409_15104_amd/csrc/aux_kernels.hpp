@@ -481,26 +481,25 @@ __global__ __launch_bounds__(256) void span_merge_kernel(const FwdParams p) {
         const int row = row0 + r;
         if (row >= p.sq) return;
         float mx = -INFINITY, den = 0.f;
-        for (int i = 0; i < n_pieces; ++i) mx = fmaxf(mx, p.slot_lse[slot_row(i, r)]);
+        for (int i = 0; i < n_pieces; ++i) mx = fmaxf(mx, p.slot_lse[slot_row(i, r)]);      // (NaN: as if it were not there)
+        const float ref = mx == -INFINITY ? 0.f : mx;
         f32x4 a = {0.f, 0.f, 0.f, 0.f};
-        if (mx != -INFINITY) {
 #pragma unroll 4
-            for (int i = 0; i < n_pieces; ++i) {
-                const int64_t s = slot_row(i, r);
-                const float wgt = __builtin_amdgcn_exp2f((p.slot_lse[s] - mx) * kLog2e);
-                const f32x4 x = *reinterpret_cast<const f32x4*>(p.slot_out + s * kHeadDim + 4 * c);
-                den += wgt;
+        for (int i = 0; i < n_pieces; ++i) {     // a row without a key takes O = 0 from every piece, one with NaN weights NaN
+            const int64_t s = slot_row(i, r);
+            const float wgt = __builtin_amdgcn_exp2f((p.slot_lse[s] - ref) * kLog2e);
+            const f32x4 x = *reinterpret_cast<const f32x4*>(p.slot_out + s * kHeadDim + 4 * c);
+            den += wgt;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) a[e] += wgt * x[e];
-            }
-            const float inv = 1.f / den;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) a[e] *= inv;
+            for (int e = 0; e < 4; ++e) a[e] += wgt * x[e];
         }
+        const float inv = den > 0.f ? 1.f / den : 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a[e] *= inv;
         const int64_t idx = ((int64_t)row * p.n_q_heads + head) * kHeadDim + 4 * c;
         if (p.out_f32) *reinterpret_cast<f32x4*>(static_cast<float*>(p.out) + idx) = a;
         else *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(p.out) + idx) = __builtin_convertvector(a, bf16x4);
-        if (c == 0) p.lse[(int64_t)head * p.lse_stride + row] = mx == -INFINITY ? mx : mx + logf(den);
+        if (c == 0) p.lse[(int64_t)head * p.lse_stride + row] = den > 0.f ? ref + logf(den) : -INFINITY;
     }
 }
 

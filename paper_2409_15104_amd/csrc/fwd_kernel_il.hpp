@@ -900,7 +900,9 @@ __global__ __launch_bounds__(512) void fwd_il_kernel(const FwdParams p) {
         if (row < sq) {
             const bool raw = kStops && stopped;   // a stopped item keeps its state as it stands
             const float inv = raw ? 1.f : (l_tot > 0.f ? 1.f / l_tot : 0.f);
-            const float lse = raw ? m_run : (l_tot > 0.f ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY);
+            // (a piece whose weights are NaN says so in its LSE: span_merge_kernel tells it from one without a key)
+            const float none = kSpan && !whole && l_tot != l_tot ? l_tot : -INFINITY;
+            const float lse = raw ? m_run : (l_tot > 0.f ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : none);
             if (raw) p.l_part[(lse_off0 + row) * 2 + hl] = l_run;
             if (hl == 0) lse_ptr[lse_off0 + row] = lse;
             const int64_t obase = o_off0 + row * q_stride;
