@@ -99,32 +99,32 @@ __device__ __forceinline__ void combine_one_head(const float* __restrict__ o_par
     for (int w = 1; w < kWaves; ++w) mx = fmaxf(mx, red_mx[w]);
     float den = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    if (mx != -INFINITY) {
-        for (int s0 = 0; s0 < n_splits; s0 += kCombineThreads) {   // as many ranges as there are weights in LDS
-            const int n = min(n_splits - s0, kCombineThreads);
-            if (s0 > 0) {
-                l = tid < n ? lse_of(s0 + tid) : -INFINITY;
-                __syncthreads();     // the weights of the round before have been read
-            }
-            const float w = expf(l - mx);
-            den += w;
-            weight[tid] = w;
-            __syncthreads();
+    // (nothing is skipped where no range has a key: O is 0 then, or NaN from NaN weights, and stays that)
+    const float ref = mx == -INFINITY ? 0.f : mx;
+    for (int s0 = 0; s0 < n_splits; s0 += kCombineThreads) {   // as many ranges as there are weights in LDS
+        const int n = min(n_splits - s0, kCombineThreads);
+        if (s0 > 0) {
+            l = tid < n ? lse_of(s0 + tid) : -INFINITY;
+            __syncthreads();     // the weights of the round before have been read
+        }
+        const float w = expf(l - ref);
+        den += w;
+        weight[tid] = w;
+        __syncthreads();
 #pragma unroll
-            for (int i = 0; i < kCombineAhead; ++i) {
-                const int s = grp + i * kCombineGroups;
-                if (s < n) {
-                    const f32x4 x = s0 == 0 ? ahead[i] : o_of(s0 + s);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[e] += weight[s] * x[e];
-                }
-            }
-#pragma unroll 4
-            for (int s = grp + kCombineAhead * kCombineGroups; s < n; s += kCombineGroups) {
-                const f32x4 x = o_of(s0 + s);
+        for (int i = 0; i < kCombineAhead; ++i) {
+            const int s = grp + i * kCombineGroups;
+            if (s < n) {
+                const f32x4 x = s0 == 0 ? ahead[i] : o_of(s0 + s);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) acc[e] += weight[s] * x[e];
             }
+        }
+#pragma unroll 4
+        for (int s = grp + kCombineAhead * kCombineGroups; s < n; s += kCombineGroups) {
+            const f32x4 x = o_of(s0 + s);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] += weight[s] * x[e];
         }
     }
 #pragma unroll
@@ -141,12 +141,12 @@ __device__ __forceinline__ void combine_one_head(const float* __restrict__ o_par
             a += red[w][tid];
             dn += red_den[w];
         }
-        if (mx != -INFINITY) a /= dn;
+        if (dn > 0.f) a /= dn;
         if constexpr (OUT_F32)
             reinterpret_cast<float*>(out_row)[tid] = a;
         else
             reinterpret_cast<__bf16*>(out_row)[tid] = (__bf16)a;
-        if (tid == 0) *lse_dst = mx != -INFINITY ? mx + logf(dn) : -INFINITY;
+        if (tid == 0) *lse_dst = dn > 0.f ? ref + logf(dn) : -INFINITY;
     }
 }
 

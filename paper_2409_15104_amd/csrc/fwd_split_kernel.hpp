@@ -461,7 +461,9 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void fwd_split_kernel(const Fw
             lds_w[k * 32 + r] = __builtin_amdgcn_exp2f(lds_m[k * 32 + r] - m_use) * inv;
             const int row = row0 + nt * 32 + r;
             if (k == 0 && row < sq) {
-                const float lse = den > 0.f ? (mx + __builtin_amdgcn_logf(den)) * kLn2 : -INFINITY;
+                // (a key range of a batch whose weights are NaN says so in its LSE, which makes the merged row's what it is uncut)
+                const float none = LIST && out_ptr == p.part_out && den != den ? den : -INFINITY;
+                const float lse = den > 0.f ? (mx + __builtin_amdgcn_logf(den)) * kLn2 : none;
                 if (DECODE) __hip_atomic_store(lse_ptr + lse_off0 + row, lse, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 else lse_ptr[lse_off0 + row] = lse;
             }

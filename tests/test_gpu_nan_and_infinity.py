@@ -56,3 +56,27 @@ def test_sweeps_cut_and_uncut(s_q, s_kv, hq, hkv, q_off, chunk, what):
                 break
         same_kind(out, o_ref, "out, stop %d" % raised)
         same_kind(lse, l_ref, "lse, stop %d" % raised)
+
+
+# caches around the lengths at which they are cut into ranges, of 512, 1024, 2048 and 4096 keys (the last: more rows per workgroup)
+@pytest.mark.parametrize("what", PLANTS)
+@pytest.mark.parametrize("hq,hkv,len_q,len_k", [
+    (8, 2, [5, 1, 1], [5, 600, 4000]), (4, 1, [1, 1, 40], [61441, 1025, 40]), (8, 2, [1, 200, 1], [150016, 200, 2049]),
+    (32, 8, [1000] * 40 + [1, 1], [1000] * 40 + [50000, 4097])])
+def test_decode_steps_of_a_mixed_batch_cut_and_uncut(hq, hkv, len_q, len_k, what):
+    """Every one-token sequence, cut into ranges or not, against the same decode step in one range."""
+    cq, ck = synth.cu_seqlens_of(len_q), synth.cu_seqlens_of(len_k)
+    q, _, _ = [t.to(DEV) for t in synth.qkv(9970, int(cq[-1]), 1, hq, hkv)]
+    _, k, v = [t.to(DEV) for t in synth.qkv(9971, 1, int(ck[-1]), hq, hkv)]
+    steps = [i for i, n in enumerate(len_q) if n == 1]
+    for i in steps:
+        plant(what, q[int(cq[i]):int(cq[i + 1])], k[int(ck[i]):int(ck[i + 1])], v[int(ck[i]):int(ck[i + 1])], hq // hkv, len_k[i] // 3)
+    out, lse = pec.pec_attn_colocated(q, k, v, torch.from_numpy(cq).to(DEV), torch.from_numpy(ck).to(DEV), out_dtype=torch.float32)
+    for i in steps:
+        row = slice(int(cq[i]), int(cq[i + 1]))
+        keys = slice(int(ck[i]), int(ck[i + 1]))
+        o_ref, l_ref = pec.pec_decode_splitkv(q[row], k[keys], v[keys], n_splits=1)
+        assert o_ref.isnan().any()
+        same_kind(out[row], o_ref, (i, len_k[i]))
+        if len_k[i] <= 4096:
+            same_kind(lse[:, row].reshape(-1), l_ref, (i, len_k[i]))
