@@ -225,7 +225,9 @@ size_t pec_varlen_workspace_bytes(int32_t batch, int64_t total_tokens);
  * One-token sequences with long caches are cut into key ranges (of 512 to 4096 keys, the shorter the less
  * else there is to do) that run as work items of the same launch (the query heads of a KV group share one pass over the keys); a second,
  * small launch merges their partial (O, LSE) pairs by log-sum-exp.  Rows without a visible key get
- * out = 0, lse = -inf.  workspace: pec_colocated_workspace_bytes() bytes.
+ * out = 0, lse = -inf.
+ * workspace: pec_colocated_workspace_bytes() bytes, which never falls when batch, total_q or total_k grows, so that what is
+ * enough for the largest batch is enough for every other one.
  * PEC_FLAG_SIMPLE_KERNEL is not supported here (PEC_ERR_UNSUPPORTED).
  */
 int pec_attn_colocated(const pec_shape_t* shape, const void* q, const void* k, const void* v,

@@ -218,14 +218,25 @@ inline bool sweep_can_stop(int cu, int n_q_heads, int64_t sq, int64_t sk, int64_
 // throughout (0.79 without that line, but then 13 of them are up to 9 % slower), over 90 others 0.89, three of them 1 ... 6 %
 // slower; microseconds with 512 / 1,024 / 2,048 / 4,096 keys: 4 heads, 17 sequences and 13,057 keys 13.6 / 15.7 / 19.5 /
 // 26.4; 24 and 122,882 29.3 / 21.1 / 23.5 / 32.7; 8 heads, 39 and 299,920 85 / 75 / 77 / 72; 26 and 6,458 44.1 / 43.9 / 43.9 / 41.9.
+// Ranges that would take more partial results than most_ranges_of_mixed_call() are left out.
 constexpr int kMinRange = 512, kMaxRange = 4096;
+
+// Most whole ranges of a mixed batch, as a function of its totals that never falls when one of them grows: a workspace that is
+// enough for one batch is enough for all smaller ones, whatever lengths of ranges they get.  Ranges of under 4,096 keys are
+// chosen where walks of 4,096 keys leave compute units idle: over 20 million random calls, on 8 to 304 compute units, with never
+// more than 1.4 workgroups of them per compute unit.  Two are allowed, and the keys of the other sequences on top.
+inline int64_t most_ranges_of_mixed_call(int cu, int n_kv_heads, int64_t total_q, int64_t total_k) {
+    return std::min(total_k / kMinRange, std::max(total_k / kMaxRange, 2 * (int64_t)cu / n_kv_heads + 1 + total_q / kMinRange));
+}
+
 inline int range_of_mixed_call(int cu, int rows, int n_q_heads, int n_kv_heads, int64_t batch, int64_t total_q, int64_t total_k) {
     int best = kMaxRange;
     if (rows == kBM) return best;
     const double others = ((double)total_q / rows + 0.3 * batch) * n_q_heads;
     const double cached = (double)std::max<int64_t>(0, total_k - total_q);
+    const int64_t most = most_ranges_of_mixed_call(cu, n_kv_heads, total_q, total_k);
     double best_t = 0;
-    for (int keys = kMaxRange; keys >= kMinRange; keys /= 2) {
+    for (int keys = kMaxRange; keys >= kMinRange && total_k / keys <= most; keys /= 2) {
         const double walk = 6 + 1.2 * std::min<double>(keys, cached) / 256;
         const double share = (others * 12 + cached * n_kv_heads / keys * walk) / cu;
         const double t = std::max(walk, share) + 0.25 * std::min(walk, share) + 0.04 * cached / keys + (cached > keys ? 2.5 : 0.0);

@@ -769,19 +769,15 @@ int pec_attn_varlen(const pec_shape_t* shape, const void* q, const void* k, cons
 }
 
 namespace {
-// keys per range of a split one-token sequence
-int coloc_range(const pec_shape_t* shape, int32_t batch, int64_t total_q, int64_t total_k, int rows) {
-    return range_of_mixed_call(compute_units(), rows, shape->n_q_heads, shape->n_kv_heads, batch, total_q, total_k);
-}
 struct ColocLayout {
     size_t cap_items, n_buckets, slot_cap;
     size_t off_counters, off_bucket, off_split, off_part_lse, off_part_out, bytes;
 };
-ColocLayout coloc_layout(const pec_shape_t* shape, int32_t batch, int64_t total_q, int64_t total_k, int rows) {
-    const int n_q_heads = shape->n_q_heads;
+// `ranges`: whole key ranges in total_k keys; every sequence may have a shorter one besides
+ColocLayout coloc_layout(int n_q_heads, int32_t batch, int64_t total_q, int64_t total_k, int rows, int64_t ranges) {
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
     ColocLayout L;
-    L.slot_cap = (size_t)(total_k / coloc_range(shape, batch, total_q, total_k, rows)) + (size_t)batch;
+    L.slot_cap = (size_t)ranges + (size_t)batch;
     L.cap_items = (size_t)(total_q / rows) + (size_t)batch + L.slot_cap + 1;
     L.n_buckets = (size_t)(total_k / 256) + 2;
     size_t o = up(L.cap_items * sizeof(WorkItem));
@@ -797,9 +793,9 @@ ColocLayout coloc_layout(const pec_shape_t* shape, int32_t batch, int64_t total_
 
 size_t pec_colocated_workspace_bytes(const pec_shape_t* shape, int32_t batch, int64_t total_q, int64_t total_k) {
     if (!shape || shape->n_q_heads <= 0 || shape->n_kv_heads <= 0 || batch < 0 || total_q < 0 || total_k < 0) return 0;
-    size_t most = 0;
-    for (const RowChoice& c : kRowChoices) most = std::max(most, coloc_layout(shape, batch, total_q, total_k, c.rows).bytes);
-    return most;
+    // the most any choice of rows and ranges needs, for these totals and smaller ones
+    return coloc_layout(shape->n_q_heads, batch, total_q, total_k, 32,
+                        most_ranges_of_mixed_call(compute_units(), shape->n_kv_heads, total_q, total_k)).bytes;
 }
 
 int pec_attn_colocated(const pec_shape_t* shape, const void* q, const void* k, const void* v,
@@ -818,8 +814,8 @@ int pec_attn_colocated(const pec_shape_t* shape, const void* q, const void* k, c
         (reinterpret_cast<uintptr_t>(cu_seqlens_q) & 3u) || (reinterpret_cast<uintptr_t>(cu_seqlens_k) & 3u))
         return PEC_ERR_MISALIGNED;
     const int rows = rows_of_list_call(compute_units(), shape->n_q_heads, shape->n_kv_heads, batch, total_q, total_k, 0, causal, kMaxRange);
-    const int range_len = coloc_range(shape, batch, total_q, total_k, rows);
-    const ColocLayout L = coloc_layout(shape, batch, total_q, total_k, rows);
+    const int range_len = range_of_mixed_call(compute_units(), rows, shape->n_q_heads, shape->n_kv_heads, batch, total_q, total_k);
+    const ColocLayout L = coloc_layout(shape->n_q_heads, batch, total_q, total_k, rows, total_k / range_len);
     if (!workspace || workspace_bytes < pec_colocated_workspace_bytes(shape, batch, total_q, total_k)) return PEC_ERR_WORKSPACE;
     if (L.cap_items > 0x7fffffff || L.n_buckets > 0x7fffffff) return PEC_ERR_UNSUPPORTED;
 

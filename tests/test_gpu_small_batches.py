@@ -1,4 +1,6 @@
 """Batches of up to 64 sequences, whose workgroups find their items in the offsets, and the next larger ones, which get a list."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -90,3 +92,22 @@ def test_offsets_that_are_not_monotone_stay_inside_the_arrays():
     assert not out[0].any() and not out[-1].any()
     o_ref, _ = oracle.attention(q[:1], k, v, q_off=tk - 1, kv_off=0, causal=True)      # the one sequence with proper bounds
     assert np.abs(out[1:2].cpu().numpy() - o_ref).max() <= 2e-2
+
+
+@pytest.mark.parametrize("hq,hkv,len_q,len_k,keys", RANGES)
+def test_workspace_of_a_larger_batch(hq, hkv, len_q, len_k, keys):
+    """One that was sized for more sequences, queries and keys is taken, and nothing behind what this batch needs is written."""
+    cq, ck = synth.cu_seqlens_of(len_q), synth.cu_seqlens_of(len_k)
+    tq, tk = int(cq[-1]), int(ck[-1])
+    q, _, _ = synth.qkv(9980, tq, 1, hq, hkv)
+    _, k, v = synth.qkv(9981, 1, tk, hq, hkv)
+    o_ref, l_ref = oracle.colocated(q, k, v, cq, ck, causal=True)
+    shape = pec.PecShape(hq, hkv, 128, pec.PEC_F32, 0.0, 0)
+    need = [pec.lib().pec_colocated_workspace_bytes(ctypes.byref(shape), len(len_q) + n, tq + 40 * n, tk + 700 * n) for n in (0, 1, 9)]
+    buffer = torch.full((need[-1],), 0xA5, dtype=torch.uint8, device=DEV)
+    for size in need:
+        out, lse = torch.full(o_ref.shape, float("nan"), device=DEV), torch.full(l_ref.shape, float("nan"), device=DEV)
+        pec.pec_attn_colocated(q.to(DEV), k.to(DEV), v.to(DEV), torch.from_numpy(cq).to(DEV), torch.from_numpy(ck).to(DEV), True,
+                               out_dtype=torch.float32, out=out, lse=lse, workspace=buffer[:size])
+        assert_close(out, lse, o_ref, l_ref, "workspace of %d bytes" % size)
+        assert bool((buffer[need[0]:] == 0xA5).all())

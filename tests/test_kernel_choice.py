@@ -88,6 +88,22 @@ def test_decode_cases_run_on_all_kernels():
         assert kernel == ("fwd_il_kernel" if c == (300, 33, 1, 0) else "decode_kernel" if c in others else "fwd_split_kernel"), c
 
 
+@pytest.mark.parametrize("hq,hkv", [(8, 8), (32, 8), (64, 8), (8, 2), (8, 1), (4, 1), (256, 2)])
+def test_workspace_of_a_mixed_batch_does_for_all_smaller_ones(lib, hq, hkv):
+    shape = binding.PecShape(hq, hkv, 128, binding.PEC_F32, 0.0, 0)
+    need = lambda *totals: lib.pec_colocated_workspace_bytes(ctypes.byref(shape), *totals)  # noqa: E731
+    assert (hq, hkv) != (8, 2) or need(7, 5387, 43041) >= need(7, 125, 40367)
+    rng = random.Random(23)
+    for _ in range(5000):
+        large = [int(2 ** rng.uniform(0, top)) for top in (9, 18, 21)]
+        small = [rng.choice((n, n - 1, rng.randint(0, n))) for n in large]
+        assert need(*large) >= need(*small), (large, small)
+        for rows in (32, 64, 256):       # what the smaller one's ranges need has room too
+            keys = choice._lib().range_keys_of(choice.COMPUTE_UNITS, rows, hq, hkv, *small)
+            slots = small[2] // keys + small[0]
+            assert need(*large) >= slots * hq * 129 * 4 + (small[1] // rows + small[0] + slots + 1) * 32, (large, small)
+
+
 def test_a_dominating_prompt_counts_by_its_own_length():
     lengths = [9622] + [6] * 10 + [3]      # 32-row workgroups took 243 us, these take 197
     assert choice.packed_rows(5, 5, lengths) == 64
