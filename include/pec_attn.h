@@ -158,9 +158,17 @@ size_t pec_sp_workspace_bytes(const pec_shape_t* shape, int64_t s_q);
  *   pending : DEVICE int32, written by the call (resume = 0 sets it to the tile count).
  *   resume  : 0 starts from the first segment and ignores the workspace contents.
  *   chunk   : a multiple of 64 (PEC_ERR_UNSUPPORTED otherwise).
- *   workspace: pec_sp_resumable_workspace_bytes() bytes, 16-byte aligned; holds the
+ *   workspace: at least pec_sp_resumable_workspace_bytes() bytes, 16-byte aligned; holds the
  *             state between calls (the caller may copy it away and back, together
- *             with lse, which holds part of the state of unfinished tiles meanwhile).
+ *             with lse, which holds part of the state of unfinished tiles meanwhile;
+ *             nothing has to be kept once *pending is 0).  Sharing few tiles out among
+ *             many workgroups takes room for their pieces, two of 134,144 bytes per workgroup,
+ *             up to pec_sp_resumable_best_workspace_bytes() (16 times as much for the fewest
+ *             tiles, at most 70 MB; never less than the other).  In a workspace without that
+ *             room a tile stays with one workgroup, which is slower, up to 2.6 times, rounds
+ *             differently, and leaves only the smaller workspace's bytes to keep.  With that room
+ *             all of the workspace may hold state.  Every call of a sweep needs the same
+ *             workspace_bytes, which this depends on.
  * PEC_FLAG_SIMPLE_KERNEL is refused (PEC_ERR_UNSUPPORTED).  Two calls that use one
  * workspace at the same time race; one sweep needs one workspace.
  */
@@ -169,6 +177,7 @@ int pec_sp_prefill_resumable(const pec_shape_t* shape, const void* q, const void
                              void* out, float* lse, void* workspace, size_t workspace_bytes,
                              const int32_t* stop, int32_t* pending, int resume, void* stream);
 size_t pec_sp_resumable_workspace_bytes(const pec_shape_t* shape, int64_t s_q);
+size_t pec_sp_resumable_best_workspace_bytes(const pec_shape_t* shape, int64_t s_q);
 
 /*
  * The same prefill one ring step at a time, for a scheduler that pauses a long prefill between

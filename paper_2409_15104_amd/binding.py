@@ -23,7 +23,7 @@ KERNEL_NAMES = {0: "pec::fwd_il_kernel", PEC_FLAG_SIMPLE_KERNEL: "pec::fwd_simpl
 
 EXPORTS = (
     "pec_attn_chunk", "pec_attn_chunk_merge", "pec_attn_merge", "pec_finalize", "pec_sp_prefill",
-    "pec_sp_workspace_bytes", "pec_sp_prefill_resumable", "pec_sp_resumable_workspace_bytes", "pec_sp_prefill_num_steps", "pec_sp_prefill_step", "pec_decode_splitkv", "pec_ulysses_layout", "pec_sp_select_strategy", "pec_decode_default_splits",
+    "pec_sp_workspace_bytes", "pec_sp_prefill_resumable", "pec_sp_resumable_workspace_bytes", "pec_sp_resumable_best_workspace_bytes", "pec_sp_prefill_num_steps", "pec_sp_prefill_step", "pec_decode_splitkv", "pec_ulysses_layout", "pec_sp_select_strategy", "pec_decode_default_splits",
     "pec_decode_workspace_bytes", "pec_decode_splitkv_static", "pec_mfma_probe", "pec_hbm_read_probe", "pec_attn_colocated", "pec_colocated_workspace_bytes", "pec_attn_varlen", "pec_varlen_workspace_bytes", "pec_status_string",
 )
 
@@ -75,6 +75,8 @@ def lib() -> ctypes.CDLL:
         L.pec_sp_prefill_resumable.argtypes = [sp, vp, vp, vp, i64, i64, i64, i64, ci, vp, vp, vp, sz, vp, vp, ci, vp]
         L.pec_sp_resumable_workspace_bytes.argtypes = [sp, i64]
         L.pec_sp_resumable_workspace_bytes.restype = sz
+        L.pec_sp_resumable_best_workspace_bytes.argtypes = [sp, i64]
+        L.pec_sp_resumable_best_workspace_bytes.restype = sz
         L.pec_sp_prefill_num_steps.argtypes = [sp, i64, i64, i64, i64, ci]
         L.pec_sp_prefill_num_steps.restype = i64
         L.pec_sp_prefill_step.argtypes = [sp, vp, vp, vp, i64, i64, i64, i64, ci, i64, vp, vp, vp, vp]
@@ -244,9 +246,11 @@ def pec_sp_prefill(q, k, v, q_off: int, chunk: int, causal: bool = True, out_dty
     return out, lse
 
 
-def pec_sp_resumable_workspace_bytes(q, k) -> int:
+def pec_sp_resumable_workspace_bytes(q, k, least: bool = False) -> int:
+    """The size with which the sweep is fastest, or the least one that it takes (for a scheduler that copies it away and back)."""
     shp = _shape(q, k, torch.bfloat16, 0.0)
-    return int(lib().pec_sp_resumable_workspace_bytes(ctypes.byref(shp), q.shape[0]))
+    size = lib().pec_sp_resumable_workspace_bytes if least else lib().pec_sp_resumable_best_workspace_bytes
+    return int(size(ctypes.byref(shp), q.shape[0]))
 
 
 def pec_sp_prefill_resumable(q, k, v, q_off: int, chunk: int, out, lse, workspace, pending, stop=None, resume: bool = False,

@@ -44,6 +44,7 @@ int compute_units() {
 // of a stopped piece), then the progress table (a word per span, eight per span for the merge).
 size_t span_slots_bytes(int groups) { return (size_t)2 * groups * kBM * (kHeadDim + 3) * sizeof(float); }
 size_t span_table_words(int groups) { return (size_t)9 * groups; }
+size_t span_bytes(int groups) { return span_slots_bytes(groups) + span_table_words(groups) * sizeof(int32_t); }
 
 // The pipelined kernel is persistent: one workgroup per compute unit (its registers allow no
 // second one), each walking its share of the `grid` logical work items.
@@ -339,9 +340,12 @@ size_t pec_sp_resumable_workspace_bytes(const pec_shape_t* shape, int64_t s_q) {
     const size_t o = (size_t)s_q * shape->n_q_heads * kHeadDim * sizeof(float);
     const size_t l = (((size_t)s_q * shape->n_q_heads * 2 * sizeof(float)) + 255) & ~(size_t)255;
     const size_t items = (size_t)((s_q + kBM - 1) / kBM) * shape->n_q_heads;
-    const size_t plain = o + l + ((items * sizeof(int32_t) + 255) & ~(size_t)255);
-    const int groups = most_span_groups(compute_units(), shape->n_q_heads, s_q);
-    return std::max(plain, span_slots_bytes(groups) + span_table_words(groups) * sizeof(int32_t));
+    return o + l + ((items * sizeof(int32_t) + 255) & ~(size_t)255);
+}
+
+size_t pec_sp_resumable_best_workspace_bytes(const pec_shape_t* shape, int64_t s_q) {
+    const size_t need = pec_sp_resumable_workspace_bytes(shape, s_q);
+    return need == 0 ? 0 : std::max(need, span_bytes(most_span_groups(compute_units(), shape->n_q_heads, s_q)));
 }
 
 int pec_sp_prefill_resumable(const pec_shape_t* shape, const void* q, const void* k, const void* v, int64_t s_q,
@@ -381,6 +385,7 @@ int pec_sp_prefill_resumable(const pec_shape_t* shape, const void* q, const void
     }
     SpanPlan spans{0, 0};
     if (can_stop) spans = spans_of_sweep(compute_units(), shape->n_q_heads, shape->n_kv_heads, s_q, s_kv, delta, causal != 0);
+    if (spans.groups && workspace_bytes < span_bytes(spans.groups)) spans.groups = 0;
     if (spans.groups) {
         progress = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + span_slots_bytes(spans.groups));
         words = (int64_t)span_table_words(spans.groups);

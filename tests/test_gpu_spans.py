@@ -5,6 +5,7 @@ import pytest
 import torch
 
 import test_gpu_parity as parity
+from paper_2409_15104_amd import binding as pec
 from paper_2409_15104_amd import synth
 
 pytestmark = pytest.mark.gpu
@@ -59,3 +60,36 @@ def test_spans_keep_every_bit_when_stopped(case):
     got = [parity._resumable_run(qd, kd, vd, q_off, chunk, causal, torch.full((1,), raised, dtype=torch.int32, device=DEV),
                                  out_dtype=torch.float32, between=other_work) for raised in (0, 1)]
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_sweeps_without_room_for_spans(case):
+    """The least workspace inside a larger buffer: taken, whole and stopped, with the same bits; only its bytes are written, and
+    they and lse are all the state there is.  A byte less is refused."""
+    s_q, s_kv, hq, hkv, q_off, chunk, causal = case
+    q, k, v = synth.qkv(70 + s_q + s_kv, s_q, s_kv, hq, hkv)
+    qd, kd, vd = parity.gpu(q, k, v)
+    least, best = [pec.pec_sp_resumable_workspace_bytes(qd, kd, least) for least in (True, False)]
+    buffer = torch.full((best,), 0xA5, dtype=torch.uint8, device=DEV)
+    pending = torch.zeros(1, dtype=torch.int32, device=DEV)
+    got = []
+    for raised in (0, 1):
+        stop = torch.full((1,), raised, dtype=torch.int32, device=DEV)
+        out, lse = torch.full((s_q, hq, 128), float("nan"), device=DEV), torch.full((hq, s_q), float("nan"), device=DEV)
+        for call in range(400):
+            pec.pec_sp_prefill_resumable(qd, kd, vd, q_off, chunk, out, lse, buffer[:least], pending, stop=stop, resume=call > 0,
+                                         causal=causal)
+            assert bool((buffer[least:] == 0xA5).all())
+            if int(pending.item()) == 0:
+                break
+            saved = buffer[:least].clone(), lse.clone()
+            buffer[:least].fill_(0x5A), lse.fill_(7)
+            buffer[:least].copy_(saved[0]), lse.copy_(saved[1])
+        assert int(pending.item()) == 0
+        got.append((out, lse))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    rows = np.unique(np.clip([0, 31, 255, 256, s_q // 2, s_q - 1], 0, s_q - 1))
+    parity._sampled_check(qd, kd, vd, *got[0], q_off if causal else s_kv, rows, heads=hkv - 1, what=str(case))
+    with pytest.raises(pec.PecError) as refused:
+        pec.pec_sp_prefill_resumable(qd, kd, vd, q_off, chunk, out, lse, buffer[:least - 1], pending, causal=causal)
+    assert refused.value.status == -4

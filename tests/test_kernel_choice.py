@@ -154,6 +154,20 @@ def test_span_cases():
     assert all(groups >= 16 and can_stop for groups, can_stop in got)
 
 
+def test_workspaces_of_sweeps_with_and_without_room_for_spans(lib):
+    """The least one is the running state and a word per tile; the other one has room for the pieces of any number of spans."""
+    rng = random.Random(29)
+    up = lambda n: (n + 255) // 256 * 256  # noqa: E731
+    for _ in range(2000):
+        hq, s_q = rng.choice((1, 4, 8, 32, 64)), int(2 ** rng.uniform(0, 18))
+        shape = binding.PecShape(hq, 1, 128, binding.PEC_BF16, 0.0, 0)
+        least, best = [f(ctypes.byref(shape), s_q) for f in (lib.pec_sp_resumable_workspace_bytes, lib.pec_sp_resumable_best_workspace_bytes)]
+        assert least == 512 * s_q * hq + up(8 * s_q * hq) + up(4 * -(-s_q // 256) * hq)
+        spans = choice.sweep_spans(hq, 1, s_q, 1 << 20, 0, False)
+        assert best >= max(least, spans * (2 * 256 * 131 * 4 + 36))
+        assert best <= max(least, 70_000_000) and best >= lib.pec_sp_resumable_best_workspace_bytes(ctypes.byref(shape), s_q - 1)
+
+
 def test_small_batch_cases_run_with_and_without_a_list():
     got = []
     for n, hq, hkv, first in cases(small_batches.test_small_batches_match_oracle):
