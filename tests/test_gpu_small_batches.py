@@ -79,17 +79,23 @@ def test_list_with_an_item_heavier_than_its_buckets():
 
 
 def test_offsets_that_are_not_monotone_stay_inside_the_arrays():
-    """Clamped bounds: lengths that add up to more than there is, offsets below zero and beyond the end."""
+    """Clamped bounds: lengths that add up to more than there is, offsets below zero and beyond the end; out, lse and the
+    workspace each between bytes that stay as they are."""
     hq, hkv, tq, tk = 4, 2, 64, 20000
     q, _, _ = synth.qkv(9950, tq, 1, hq, hkv)
     _, k, v = synth.qkv(9951, 1, tk, hq, hkv)
     cq = torch.tensor([0, 1, 40, 39, 40, 41, -5, 900, 64], dtype=torch.int32, device=DEV)
     ck = torch.tensor([0, 20000, 100, 20000, 0, 19999, 50000, -7, 20000], dtype=torch.int32, device=DEV)
+    shape = pec.PecShape(hq, hkv, 128, pec.PEC_F32, 0.0, 0)
+    need = pec.lib().pec_colocated_workspace_bytes(ctypes.byref(shape), cq.numel() - 1, tq, tk)
     out = torch.zeros((tq + 2, hq, 128), dtype=torch.float32, device=DEV)
-    pec.pec_attn_colocated(q.to(DEV), k.to(DEV), v.to(DEV), cq, ck, True, out_dtype=torch.float32, out=out[1:-1],
-                           lse=torch.zeros((hq, tq), dtype=torch.float32, device=DEV))
+    lse = torch.zeros((3, hq, tq), dtype=torch.float32, device=DEV)
+    ws = torch.full((need + 8192,), 0xA5, dtype=torch.uint8, device=DEV)
+    pec.pec_attn_colocated(q.to(DEV), k.to(DEV), v.to(DEV), cq, ck, True, out_dtype=torch.float32, out=out[1:-1], lse=lse[1],
+                           workspace=ws[4096:-4096])
     torch.cuda.synchronize()
-    assert not out[0].any() and not out[-1].any()
+    assert not out[0].any() and not out[-1].any() and not lse[0].any() and not lse[2].any()
+    assert bool((ws[:4096] == 0xA5).all()) and bool((ws[-4096:] == 0xA5).all())
     o_ref, _ = oracle.attention(q[:1], k, v, q_off=tk - 1, kv_off=0, causal=True)      # the one sequence with proper bounds
     assert np.abs(out[1:2].cpu().numpy() - o_ref).max() <= 2e-2
 

@@ -20,6 +20,8 @@ CASES = [
     (256, 16384, 40, 1, 16128, 1024, True),      # wide group on one KV head
     (1280, 6000, 64, 8, 4720, 1280, True),       # more items than compute units: whole items inside spans
     (257, 20000, 16, 2, 9000, 2048, True),       # half of the keys in the future
+    (16700, 30000, 1, 1, 13300, 4096, True),     # 66 query tiles of a head: a workgroup finds its place in two rounds
+    (16641, 9000, 2, 1, 0, 2048, False),         # the same without a mask, the last tile has one row
 ]
 
 
@@ -31,7 +33,7 @@ def test_spans_match_oracle_whole_and_stopped(case):
     outliers = [(int(j), int(r), int(a)) for j, r, a in zip(keys, np.linspace(0, s_q - 1, 24), np.tile([2, 4, 8], 8))]
     q, k, v = synth.qkv_with_outlier_keys(50 + s_q + s_kv, s_q, s_kv, hq, hkv, outliers)
     qd, kd, vd = parity.gpu(q, k, v)
-    rows = np.unique(np.clip([0, 1, 31, 32, 255, 256, 511, 512, s_q // 2, s_q - 2, s_q - 1, *[o[1] for o in outliers[::3]]], 0, s_q - 1))
+    rows = np.unique(np.clip([0, 1, 31, 32, 255, 256, 511, 512, 16383, 16384, s_q // 2, s_q - 2, s_q - 1, *[o[1] for o in outliers[::3]]], 0, s_q - 1))
     runs = []
     for raised in (0, 1):
         stop = torch.full((1,), raised, dtype=torch.int32, device=DEV)

@@ -123,7 +123,8 @@ def test_merge_in_the_launch_cases():
 
 
 def test_sweeps_that_cannot_stop_are_those_whose_tiles_have_no_boundary_to_stop_at():
-    """Against the limits of fwd_il_kernel itself, tile by tile."""
+    """Against a restatement of where fwd_il_kernel lets a tile be left (its stop_limit), tile by tile: this holds the rule for a
+    whole call to it, not to the kernel, whose own limits test_gpu_small_sweeps.py sees in the number of calls."""
     rng, left = random.Random(17), 0
     for _ in range(20000):
         hq, sq, sk = rng.choice((1, 4, 8, 64)), rng.randint(1, 1500), rng.randint(0, 4000)
@@ -152,6 +153,7 @@ def test_span_cases():
     got = [(choice.sweep_spans(hq, hkv, sq, sk, q_off, causal), choice.sweep_can_stop(hq, sq, sk, q_off, chunk, causal))
            for sq, sk, hq, hkv, q_off, chunk, causal in spans.CASES]
     assert all(groups >= 16 and can_stop for groups, can_stop in got)
+    assert {causal for sq, *_, causal in spans.CASES if sq > 64 * 256} == {True, False}     # a wavefront's lanes, one tile each
 
 
 def test_workspaces_of_sweeps_with_and_without_room_for_spans(lib):
