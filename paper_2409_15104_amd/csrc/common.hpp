@@ -79,9 +79,8 @@ struct FwdParams {
     int32_t kv_split_len;
     int64_t split_out_stride, split_lse_stride;   // elements
     // key ranges of a decode step whose last workgroup per KV head merges them (fwd_split_kernel; null: a kernel of its own
-    // does): one word per KV head and range, the mark that this call writes there (last_workgroup()), and where the results go
+    // does): one word per KV head and range (last_workgroup()) and where the results go; `mark`: what this call writes there
     uint64_t* arrived;
-    uint64_t mark;
     void* merged_out;
     float* merged_lse;
     int32_t merged_f32;
@@ -118,6 +117,7 @@ struct FwdParams {
     int32_t batch, total_q, total_k, slot_capacity;
     struct SplitSeq* split_seqs;
     int32_t* n_split;
+    uint64_t mark;
 };
 struct SplitSeq {        // a one-token sequence whose keys are cut into ranges
     int32_t seq, slot0, n_ranges, pad;
