@@ -119,10 +119,10 @@ def _check(fn: str, status: int) -> None:
         raise PecError(fn, status)
 
 
-# Marshalling is on the path of every call, and the smallest ones (a decode step over a short cache: two launches, 7 us of
-# host time, 10 us of GPU time) are as long as it takes: addresses go over as plain integers, one shape struct is kept per
-# set of values, and the current stream is asked for its handle (0.2 us; building torch's Stream object takes 3.1 us).
-# Decode step over 4,096 keys: 15.8 -> 11.6 us per call.
+# Marshalling is on the path of every call, and the smallest ones (a decode step over a short cache: 10 us of GPU time, 9 of the
+# host's) are as long as it takes: addresses go over as plain integers, one shape struct is kept per set of values, and the
+# current stream is asked for its handle (0.2 us; building torch's Stream object takes 3.1 us).  Decode step over 4,096 keys,
+# when it still was two launches: 15.8 -> 11.6 us per call.
 @functools.lru_cache(maxsize=256)
 def _shape_of(n_q_heads, n_kv_heads, head_dim, out_dtype, scale, flags) -> PecShape:
     return PecShape(n_q_heads, n_kv_heads, head_dim, PEC_F32 if out_dtype == torch.float32 else PEC_BF16, scale, flags)

@@ -18,9 +18,9 @@
 //
 // Measured (microseconds, 256-row pipelined kernel -> this one): 512 rows x 2048 keys, 8 heads: 47.1 -> 14.8 (NT = 1,
 // 128 workgroups; the host needs 10 of them); 1024 x 8192, 8 heads: 157 -> 49 (NT = 1, 256 workgroups); 2048 x 8192, 8
-// heads: 158 -> 80 (NT = 2, 256 workgroups).  A step of 256 keys takes 1.17 us with NT = 1 -- 128 KiB at 112 GB/s, what
-// one compute unit gets from L2 -- and 1.68 us with NT = 2, where MFMAs and softmax of the two wavefronts of a SIMD add
-// up.  Tried and dropped: NT = 2 with Q in registers (spills in the loop); 64 rows as two wavefronts sharing each of
+// heads: 158 -> 80 (NT = 2, 256 workgroups).  A step of 256 keys takes 1.17 us with NT = 1 -- 128 KiB at 112 GB/s per
+// compute unit; whether that is the L2's rate, the latency of misses that the workgroups of an XCD share, or instruction
+// issue has not been measured -- and 1.68 us with NT = 2, where MFMAs and softmax of the two wavefronts of a SIMD add up.  Tried and dropped: NT = 2 with Q in registers (spills in the loop); 64 rows as two wavefronts sharing each of
 // four key streams (two barriers per step: 2.7 us per 256 keys); four-wavefront workgroups of the pipelined kernel, two
 // per compute unit (twice the tile loads: packed batches 11 ... 14 % slower).
 #pragma once

@@ -279,10 +279,11 @@ inline bool decode_on_split_kernel(int cu, int n_q_heads, int n_kv_heads, int64_
 
 // Whether the last workgroup of a KV head merges its ranges itself instead of a second launch (fwd_split_kernel.hpp).  That
 // takes it three trips to memory and the read of group x ranges partial results by one compute unit, against a launch: 2 us
-// of the host's time, and on the GPU (microseconds per step out of a captured graph, fresh caches, one launch / two), by
-// group x ranges: 3 9.6 / 9.9, 16 9.2 / 9.4, 32 10.4 / 10.8 and 96.7 / 97.4, 64 11.8 / 12.2 and 10.8 / 11.0, 128 15.4 / 14.8,
-// 12.6 / 12.3 and 10.5 / 9.7, 256 17.3 / 15.0 and 358.3 / 355.5, 1,024 22 / 12.  4,096 keys of 32 / 8 heads, called
-// over and over on one cache, where the host is the slower: 12.3 -> 10.2.
+// of the host's time, and on the GPU (microseconds per step of many in one graph, fresh caches, one launch / two, when words
+// were still marked in a way that a graph could replay), by group x ranges: 3 9.6 / 9.9, 16 9.2 / 9.4, 32 10.4 / 10.8 and
+// 96.7 / 97.4, 64 11.8 / 12.2 and 10.8 / 11.0, 128 15.4 / 14.8, 12.6 / 12.3 and 10.5 / 9.7, 256 17.3 / 15.0 and 358.3 / 355.5,
+// 1,024 22 / 12.  4,096 keys of 32 / 8 heads, called over and over on one cache, where the host is the slower: 11.85 -> 10.0;
+// as the first pass on new inputs, 27.7 ... 30.2 -> 27.0 ... 27.8.  Kernel times of that step: 9.4, against 6.4 + 4.1.
 inline bool merge_in_launch(int group, int64_t n_splits) { return group * n_splits <= 64; }
 
 // What the words of such a call hold once their ranges are there: call number n of a process, a mixer of 64 bits (splitmix64)

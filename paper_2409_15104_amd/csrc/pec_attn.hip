@@ -818,6 +818,7 @@ int pec_attn_colocated(const pec_shape_t* shape, const void* q, const void* k, c
     if (misaligned(q) || misaligned(k) || misaligned(v) || misaligned(out) || misaligned(workspace) ||
         (reinterpret_cast<uintptr_t>(cu_seqlens_q) & 3u) || (reinterpret_cast<uintptr_t>(cu_seqlens_k) & 3u))
         return PEC_ERR_MISALIGNED;
+    // (rows are chosen first, for ranges of kMaxRange keys, which is what that rule was measured with; the ranges then by the rows)
     const int rows = rows_of_list_call(compute_units(), shape->n_q_heads, shape->n_kv_heads, batch, total_q, total_k, 0, causal, kMaxRange);
     const int range_len = range_of_mixed_call(compute_units(), rows, shape->n_q_heads, shape->n_kv_heads, batch, total_q, total_k);
     const ColocLayout L = coloc_layout(shape->n_q_heads, batch, total_q, total_k, rows, total_k / range_len);
