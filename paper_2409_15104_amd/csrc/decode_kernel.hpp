@@ -4,8 +4,12 @@
 // The step is HBM-bound (K and V are read once, 512 bytes per key and KV head, against 1 Kflop),
 // so the design goal is bytes in flight: each wavefront owns private LDS rings of 32-key tiles filled
 // by direct global->LDS loads, two stages for K and three for V (all of the 160 KiB of LDS: V is
-// consumed last in a tile, so the extra stage goes to it), i.e. up to 40 KiB outstanding per
-// wavefront and 160 KiB per compute unit (4 wavefronts) to cover the memory latency at the HBM rate.  The g query heads that share a KV head are the 32 "query columns" of the same
+// consumed last in a tile, so the extra stage goes to it): room for 40 KiB outstanding per
+// wavefront and 160 KiB per compute unit (4 wavefronts).  The build has that much on its way only
+// ahead of the first tile: the compiler, which does not see the waits in inline asm, takes the Q
+// fragments for outstanding at every tile's first product and waits for vmcnt(0) there, so every
+// tile holds a trip to memory, with at most K(j+1) and V(j+2) on their way, 16 KiB per wavefront.
+// The g query heads that share a KV head are the 32 "query columns" of the same
 // transposed-score MFMA scheme as the prefill kernels (columns >= g carry zeros): the matrix
 // pipe is mostly idle and does not matter here.
 //
@@ -125,7 +129,8 @@ __global__ __launch_bounds__(kDecWaves * 64) void decode_kernel(const DecodePara
 
     // Issue order: K(0) V(0) K(1) V(1) V(2), then per tile j: K(j+2) V(j+3).  Loads retire in order, so
     // when tile j starts the requests younger than K(j) and V(j) are V(j+1) | K(j+1) V(j+2): 24 of them
-    // in the steady state, fewer at the end of the range (tiles past the end are not requested).
+    // in the steady state, fewer at the end of the range (tiles past the end are not requested).  These are what the
+    // waits below leave outstanding; the compiler's own wait for Q, ahead of the first product, does not (see the top).
     constexpr std::false_type ahead{};
     issue_k(ahead, 0);
     issue_v(ahead, 0);

@@ -8,21 +8,26 @@
 // in LDS at the end, so nothing but the result leaves the workgroup and no workspace is needed.
 //
 // Every wavefront has a private 8 KiB LDS stage for K and one for V and there is no barrier in the loop: K(j+1) is
-// requested as soon as the scores of tile j have read K(j), V(j+1) as soon as O += P(j) V(j) has read V(j), so 64 to
-// 128 KiB per compute unit are on their way at any time, and the two wavefronts of a SIMD drift apart until one does
-// its softmax under the other's MFMAs.
+// requested as soon as the scores of tile j have read K(j), V(j+1) as soon as O += P(j) V(j) has read V(j), and the loop's
+// own waits are counted so that the other of the two may still be on its way.  That holds in the build only for NT = 2 on
+// batches.  Elsewhere registers loaded ahead of the loop -- Q with NT = 1, the running O of a dense call with NT = 2 -- are
+// first used in it, and the compiler, which does not see the waits in inline asm, takes those loads for outstanding in every
+// iteration and adds waits down to vmcnt(0) of its own: with NT = 1 ahead of the scores, where V(j), requested at the end
+// of the step before, is waited for too, with NT = 2 within O += P(j) V(j), where K(j+1) is.  So with NT = 1 nothing is on
+// its way under the scores and every step holds one whole trip to memory; from then on it is 64 KiB per compute unit, K(j+1).
+// The two wavefronts of a SIMD drift apart until one does its softmax under the other's MFMAs.
 //
 // A decode step is the same thing with the query heads of a KV group as the rows and a key range as the work item.  At
-// 524,288 keys and 8 KV heads 256 workgroups read 2147 MB in 355 us, 6.0 TB/s -- what a kernel that only reads gets --
-// with 128 KiB per compute unit on their way.
+// 524,288 keys and 8 KV heads 256 workgroups read 2147 MB in 355 us, 6.0 TB/s, what a kernel that only reads gets.
 //
 // Measured (microseconds, 256-row pipelined kernel -> this one): 512 rows x 2048 keys, 8 heads: 47.1 -> 14.8 (NT = 1,
 // 128 workgroups; the host needs 10 of them); 1024 x 8192, 8 heads: 157 -> 49 (NT = 1, 256 workgroups); 2048 x 8192, 8
 // heads: 158 -> 80 (NT = 2, 256 workgroups).  A step of 256 keys takes 1.17 us with NT = 1 -- 128 KiB at 112 GB/s per
-// compute unit; whether that is the L2's rate, the latency of misses that the workgroups of an XCD share, or instruction
-// issue has not been measured -- and 1.68 us with NT = 2, where MFMAs and softmax of the two wavefronts of a SIMD add up.  Tried and dropped: NT = 2 with Q in registers (spills in the loop); 64 rows as two wavefronts sharing each of
-// four key streams (two barriers per step: 2.7 us per 256 keys); four-wavefront workgroups of the pipelined kernel, two
-// per compute unit (twice the tile loads: packed batches 11 ... 14 % slower).
+// compute unit, the trip to memory that nothing covers included; how much of the step that trip is has not been measured --
+// and 1.68 us with NT = 2, where MFMAs and softmax of the two wavefronts of a SIMD add up.  Tried and dropped: NT = 2 with Q
+// in registers (spills in the loop); 64 rows as two wavefronts sharing each of four key streams (two barriers per step:
+// 2.7 us per 256 keys); four-wavefront workgroups of the pipelined kernel, two per compute unit (twice the tile loads:
+// packed batches 11 ... 14 % slower).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -335,7 +340,7 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void fwd_split_kernel(const Fw
     for (int tile = wave; tile < n_tiles; tile += KS) {
         const bool more = tile + KS < n_tiles;
         const int key0 = tile * kSplitTile;
-        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");       // K(j); V(j) may still be on its way
+        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");       // K(j); V(j) may be on its way (but see the top for NT = 1)
         f32x16 s[NT];
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
@@ -401,7 +406,7 @@ __global__ __launch_bounds__(kSplitWaves * 64, 2) void fwd_split_kernel(const Fw
             }
         }
 
-        if (more) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");   // V(j); K(j+1) may still be on its way
+        if (more) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");   // V(j); K(j+1) may still be on its way (NT = 2, dense: see the top)
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
         for (int k2 = 0; k2 < 2; ++k2)

@@ -269,8 +269,9 @@ inline int64_t range_keys(int64_t sk, int64_t n_splits, int tile) {
 //     4,096 keys     16 ranges 18.2 / 11.4      64 ranges (64) 11.6 / 15.1
 //     32,768 keys    32 ranges 60.9 / 31.8     128 ranges (256) 33.6 / 41.9
 //     524,288 keys   32 ranges 766 / 356       128 ranges 384 / 372
-// The workgroup kernel wins while all of its workgroups run at once; a second round of them costs it the latency that
-// decode_kernel's deeper rings hide.  In one round (16 ranges of 8 KV heads), by the keys of a range: 32 keys 8.6 / 9.3,
+// The workgroup kernel wins while all of its workgroups run at once and loses with a second round of them (both kernels as
+// built wait for every request of a wavefront at each tile, so it is not the depth of decode_kernel's rings that wins; what
+// does has not been measured).  In one round (16 ranges of 8 KV heads), by the keys of a range: 32 keys 8.6 / 9.3,
 // 64 keys 10.1 / 9.5, 96 keys 11.8 / 10.1, 128 keys 14.9 / 10.7, 256 keys 22.1 / 12.6; 32 ranges, 64 heads on 64 KV heads
 // and 4 on 4 give the same to 1 us.  The line lies above two tiles; a range of exactly two would gain 0.6 us beyond it.
 inline bool decode_on_split_kernel(int cu, int n_q_heads, int n_kv_heads, int64_t sk, int64_t n_splits) {
