@@ -11,10 +11,14 @@
 //     P(j)   = exp2(S(j) - m(j)) etc.   ~112 VALU  (S(j), m(j) from the previous iteration)
 //     m(j+1), alpha(j+1) from S(j+1)    ~30 VALU   (masked tiles only, after the first 16 MFMAs)
 // which are independent of each other and get issued round-robin (3 to 4 VALU per MFMA).
-// Measured: an MFMA of this shape keeps the SIMD's vector issue port for about 23 of its 32
-// cycles, so only 4 to 5 plain VALU instructions per MFMA are free; every one beyond that costs
-// about 2 cycles, a transcendental about 5.  Hence the softmax reference m is kept lazily
-// (see row_max) and unmasked tiles do without a row maximum (see body).
+// Measured (bare loops, two wavefronts per SIMD; profiles/mfma_shapes_probe.hip): an MFMA of this
+// shape keeps the SIMD's vector issue port for 9 to 10 of its 32 cycles, a plain VALU instruction
+// for 4, a transcendental for 8.  So five plain ones per MFMA are free, or four and a transcendental,
+// and one beyond that costs its whole 4 or 8 cycles; the exponentials, FMAs, sums and conversions of
+// a tile, 3.5 per MFMA of which one is a transcendental, fill 28 of the 32, and one more per MFMA is
+// all that would fit.  In time none is free: MFMA alone runs at 1.76 GHz, with three and a
+// transcendental under it at 1.50, since power is what is short.  Hence the softmax reference m is
+// kept lazily (see row_max) and unmasked tiles do without a row maximum (see body).
 // MFMA operand layouts and LDS swizzles as described in common.hpp; K/V tiles go global -> LDS
 // directly (global_load_lds_dwordx4: no staging registers, no ds_write; the XOR swizzles are applied
 // on the global side by choosing which 16-byte chunk each lane fetches, a permutation inside one
