@@ -1,5 +1,5 @@
-// Bare loops of MFMAs behind the figures of mfma_shapes_counters.md (gfx950): what the two bf16 shapes cost in cycles, in
-// issue slots and, through the clock that the chip can hold, in power.  Stands alone, is part of no library:
+// Bare loops of MFMAs (gfx950): what the two bf16 shapes cost in cycles, in issue slots and, through the clock that the chip
+// can hold, in power.  Its figures stand beside it in this folder.  Stands alone, is part of no library:
 //     hipcc --offload-arch=gfx950 -O3 -std=c++17 -Xclang -target-feature -Xclang -packed-fp32-ops profiles/mfma_shapes_probe.hip -o probe
 //     ./probe
 // Every loop runs on 256 workgroups, one per compute unit.  A line gives the cycles that the matrix pipe of a SIMD has per
